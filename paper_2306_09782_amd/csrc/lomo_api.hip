@@ -328,7 +328,7 @@ lomo_status lomo_step_norm_pass(const lomo_tensor* tensors, int64_t n, double* a
         a.lda = t.K; a.ldb = t.N; a.ldo = t.K;
         a.acc = acc; a.flag_out = flags + i;
         a.family = LOMO_KERNEL_WGRAD_SQNORM;
-        if (dma_eligible(a)) grouped.push_back(a);
+        if (dma_eligible(a, true)) grouped.push_back(a);
         else if (launch_wgrad_sqnorm(a, route, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     }
     std::vector<GemmArgs> gram, direct;
@@ -359,7 +359,7 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
             d.M = t.K; d.Nn = t.T; d.C = t.N;
             d.lda = t.K; d.ldb = t.N; d.ldo = t.K;
             d.family = LOMO_KERNEL_DGRAD;
-            if (dma_eligible(d)) dgrads.push_back(d);
+            if (dma_eligible(d, false)) dgrads.push_back(d);
             else if (launch_dgrad(d, st) != hipSuccess) return LOMO_ERR_LAUNCH;
         }
         GemmArgs a{};
@@ -368,7 +368,7 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
         a.lda = t.K; a.ldb = t.N; a.ldo = t.K;
         a.s = s; a.s_dev = s_dev; a.flag_in = step_flag;
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
-        if (dma_eligible(a)) updates.push_back(a);
+        if (dma_eligible(a, true)) updates.push_back(a);
         else updates_plain.push_back(a);
     }
     if (!dgrads.empty() && launch_dma_group<false, EPI_STORE>(dgrads.data(), (int)dgrads.size(), st) != hipSuccess)
@@ -452,7 +452,7 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
             d.M = t.K; d.Nn = t.T; d.C = t.N;
             d.lda = t.K; d.ldb = t.N; d.ldo = t.K;
             d.family = LOMO_KERNEL_DGRAD;
-            if (dma_eligible(d)) dgrads.push_back(d);
+            if (dma_eligible(d, false)) dgrads.push_back(d);
             else if (launch_dgrad(d, st) != hipSuccess) return LOMO_ERR_LAUNCH;
         }
         GemmArgs a{};
@@ -462,7 +462,7 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
         a.lr = lr; a.inv_s = inv_loss_scale; a.clipv = clip_value;
         a.flag_out = flags + i;
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
-        if (dma_eligible(a)) updates.push_back(a);
+        if (dma_eligible(a, true)) updates.push_back(a);
         else updates_plain.push_back(a);
     }
     if (!dgrads.empty() && launch_dma_group<false, EPI_STORE>(dgrads.data(), (int)dgrads.size(), st) != hipSuccess)

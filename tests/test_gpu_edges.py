@@ -1,0 +1,128 @@
+"""The contraction kernels at the edges of their tiles and slices: sizes one step off a whole tile (256 and 128) or a
+whole slice (32 and 64 contraction indices), the smallest sizes, and a non-finite neighbour just outside a short slice.
+
+Bars as in test_gpu_parity.py: W within 1 fp16 ulp on 99.9 %, 2 everywhere; dX and Y also within 2^-20 of the sum of the
+absolute products where the sum cancels (fp32 sums of at most 2^12 terms); the norm within 2e-5; flags exact.  Every
+output lies in a larger buffer whose other elements must keep their bits."""
+import math
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import lomo_synth as S
+from oracle import lomo_oracle as O
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+PAD = 512          # guarded elements on either side of an output
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2306_09782_amd as L
+    if not os.path.exists(L.library_path()):
+        from paper_2306_09782_amd.build import build
+        build(verbose=False)
+    L.load_library()
+    return L
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def f16(seed, shape, sigma, scale=1.0):
+    return S.normal_f16_np(S.tensor_key(81, seed, shape[0], shape[1]), shape, S.normal_mult(sigma, scale))
+
+
+class Guarded:
+    """A device tensor inside a larger buffer of sevens."""
+
+    def __init__(self, shape, init=None):
+        n = shape[0] * shape[1]
+        self.whole = torch.full((n + 2 * PAD,), 7.0, dtype=torch.float16, device=DEV)
+        self.t = self.whole[PAD:PAD + n].view(shape)
+        if init is not None:
+            self.t.copy_(dev(init))
+
+    def host(self):
+        w = self.whole.cpu().numpy()
+        assert (w[:PAD] == 7).all() and (w[-PAD:] == 7).all(), "written outside the output"
+        return self.t.cpu().numpy()
+
+
+def product_ok(got, ref64, mag, what):
+    d = O.ulp_distance_f16(got, O.round_f16(ref64))
+    near = np.abs(got.astype(np.float64) - ref64) <= 2.0 ** -20 * mag
+    assert ((d <= 2) | near).all(), f"{what}: off by {d.max()} ulp"
+    assert ((d <= 1) | near).mean() >= 0.999, what
+
+
+def weights_ok(got, want, what):
+    d = O.ulp_distance_f16(got, want)
+    assert d.max() <= 2 and (d <= 1).mean() >= 0.999, (what, int(d.max()))
+
+
+SHAPES = [(1, 8, 8), (7, 8, 264), (31, 264, 8), (32, 256, 256), (33, 248, 520), (63, 136, 128), (65, 120, 384), (96, 384, 136),
+          (127, 256, 776), (128, 512, 512), (129, 264, 248), (255, 1032, 72), (257, 72, 1032), (260, 520, 2056), (777, 504, 504)]
+
+
+@pytest.mark.parametrize("T,K,N", SHAPES)
+def test_step_at_tile_and_slice_edges(L, T, K, N):
+    """Norm, visible update, dX and the clip-by-value update through the whole-pass calls."""
+    Sc = 256.0
+    X, dY, W = f16(1, (T, K), 1.0), f16(2, (T, N), 0.01, Sc), f16(3, (N, K), 0.02)
+    G = O.linear_grad(X, dY)
+    Wd, dX = Guarded((N, K), W), Guarded((T, K))
+    tensor = {"kind": "linear", "X": dev(X), "dY": dev(dY), "W": Wd.t, "dX": dX.t}
+    lst = L.make_tensor_list([tensor])          # holds addresses: `tensor` keeps them alive
+    ws = torch.empty(max(256, L.lomo_step_workspace_bytes(lst)), dtype=torch.uint8, device=DEV)
+    acc, flags = torch.zeros(1, dtype=torch.float64, device=DEV), torch.zeros(2, dtype=torch.int32, device=DEV)
+    L.lomo_step_norm_pass(lst, acc, flags, ws)
+    assert abs(float(acc.item()) / O.sqnorm(G) - 1) < 2e-5 and flags.cpu().tolist() == [0, 0]
+    lr = float(np.float32(30 * 2.0 ** -16 / (math.sqrt(T) * 0.01)))
+    L.lomo_step_update_pass(lst, lr, 1.0 / Sc, 1.0, flags[1:], ws)
+    weights_ok(Wd.host(), O.sgd_update(W, G, lr, 1.0, Sc), "W")
+    a64 = dY.astype(np.float64), W.astype(np.float64)
+    product_ok(dX.host(), a64[0] @ a64[1], np.abs(a64[0]) @ np.abs(a64[1]), "dX")
+    Wd.t.copy_(dev(W))
+    clipv = float(np.float32(0.005 * math.sqrt(T)))          # clips about half of the elements
+    L.lomo_step_update_pass_clip_value(lst, 0.02, 1.0 / Sc, clipv, flags, ws)
+    weights_ok(Wd.host(), O.sgd_update_clip_value(W, G, float(np.float32(0.02)), clipv, Sc), "W by value")
+    assert flags.cpu().tolist() == [0, 0]
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 8, 8), (33, 40, 264), (64, 264, 136), (127, 72, 384), (129, 520, 248), (257, 1032, 520),
+                                   (4100, 40, 3080), (3080, 104, 4104)])
+@pytest.mark.parametrize("residual", [False, True])
+def test_forward_at_tile_and_slice_edges(L, T, K, N, residual):
+    X, W, R = f16(4, (T, K), 1.0), f16(5, (N, K), 0.05), f16(6, (T, N), 1.0)
+    Y = Guarded((T, N))
+    if residual:
+        L.lomo_linear_forward_residual(dev(X), dev(W), dev(R), Y.t)
+    else:
+        L.lomo_linear_forward(dev(X), dev(W), Y.t)
+    x, w, r = X.astype(np.float64), W.astype(np.float64), R.astype(np.float64) if residual else 0.0
+    product_ok(Y.host(), x @ w.T + r, np.abs(x) @ np.abs(w).T + np.abs(r), "Y")
+
+
+@pytest.mark.parametrize("T,K,N", [(70, 264, 72), (300, 520, 1032), (33, 256, 40)])
+def test_non_finite_rows_stay_in_their_rows(L, T, K, N):
+    """The contraction lengths are not whole slices, so a short slice ends where the next row begins: an infinite row
+    must not reach its neighbours' sums (0 * inf), forwards or backwards."""
+    dY, W, X = f16(7, (T, N), 1.0), f16(8, (N, K), 0.05), f16(9, (T, K), 1.0)
+    for bad in (0, T // 2, T - 1):
+        d, x = dY.copy(), X.copy()
+        d[bad], x[bad] = np.inf, np.nan
+        dX, Y = Guarded((T, K)), Guarded((T, N))
+        L.lomo_linear_dgrad(dev(d), dev(W), dX.t)
+        L.lomo_linear_forward(dev(x), dev(W), Y.t)
+        others = np.arange(T) != bad
+        w = W.astype(np.float64)
+        got_dx, got_y = dX.host(), Y.host()
+        assert not np.isfinite(got_dx[bad]).any() and not np.isfinite(got_y[bad]).any()
+        a, b = dY[others].astype(np.float64), X[others].astype(np.float64)
+        product_ok(got_dx[others], a @ w, np.abs(a) @ np.abs(w), "dX")
+        product_ok(got_y[others], b @ w.T, np.abs(b) @ np.abs(w).T, "Y")
