@@ -56,7 +56,7 @@ lomo_status lomo_wgrad_sqnorm_route(const lomo_half* X, const lomo_half* dY, int
     a.lda = K; a.ldb = N; a.ldo = K;
     a.acc = acc; a.flag_out = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_SQNORM;
-    return from_hip(launch_wgrad_sqnorm(a, norm_algorithm, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_wgrad_sqnorm({a}, norm_algorithm, static_cast<hipStream_t>(stream)));
 }
 
 lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY, lomo_half* W, lomo_half* dX, int64_t T,
@@ -75,7 +75,7 @@ lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY,
         d.M = K; d.Nn = T; d.C = N;
         d.lda = K; d.ldb = N; d.ldo = K;
         d.family = LOMO_KERNEL_DGRAD;
-        hipError_t e = launch_dgrad(d, st);
+        hipError_t e = launch_dgrad({d}, st);
         if (e != hipSuccess) return LOMO_ERR_LAUNCH;
     }
     GemmArgs a{};
@@ -85,7 +85,7 @@ lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY,
     a.s = step_size(lr, inv_loss_scale, clip_coef);
     a.flag_in = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_UPDATE;
-    return from_hip(launch_wgrad_update(a, st));
+    return from_hip(launch_wgrad_update({a}, st));
 }
 
 size_t lomo_embedding_workspace_bytes(int64_t T, int64_t H) { return embedding_ws_bytes(T, H); }
@@ -318,7 +318,7 @@ lomo_status lomo_step_norm_pass(const lomo_tensor* tensors, int64_t n, double* a
     if (!acc || !flags) return LOMO_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(acc) & 7u) return LOMO_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    std::vector<GemmArgs> grouped;
+    std::vector<GemmArgs> norms;
     for (int64_t i = 0; i < n; ++i) {
         const lomo_tensor& t = tensors[i];
         if (t.kind != LOMO_TENSOR_LINEAR || t.T == 0 || t.K == 0 || t.N == 0) continue;
@@ -328,14 +328,9 @@ lomo_status lomo_step_norm_pass(const lomo_tensor* tensors, int64_t n, double* a
         a.lda = t.K; a.ldb = t.N; a.ldo = t.K;
         a.acc = acc; a.flag_out = flags + i;
         a.family = LOMO_KERNEL_WGRAD_SQNORM;
-        if (dma_eligible(a, true)) grouped.push_back(a);
-        else if (launch_wgrad_sqnorm(a, route, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+        norms.push_back(a);
     }
-    std::vector<GemmArgs> gram, direct;
-    choose_norm_route(route, grouped, gram, direct);
-    if (!gram.empty() && launch_gram_group(gram.data(), (int)gram.size(), st) != hipSuccess) return LOMO_ERR_LAUNCH;
-    if (!direct.empty() && launch_dma_group<true, EPI_SQNORM>(direct.data(), (int)direct.size(), st) != hipSuccess)
-        return LOMO_ERR_LAUNCH;
+    if (launch_wgrad_sqnorm(norms, route, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     cs = run_row_kernels(tensors, n, ws, ws_bytes, 0, 0.f, nullptr, acc, flags, nullptr, 0.f, 0.f, false, st);
     if (cs != LOMO_OK) return cs;
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
@@ -348,7 +343,7 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
     lomo_status cs = check_step(tensors, n, true, ws, ws_bytes);
     if (cs != LOMO_OK) return cs;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    std::vector<GemmArgs> dgrads, updates, updates_plain;
+    std::vector<GemmArgs> dgrads, updates;
     // every dgrad first: dX must come from the pre-update weights
     for (int64_t i = 0; i < n; ++i) {
         const lomo_tensor& t = tensors[i];
@@ -359,8 +354,7 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
             d.M = t.K; d.Nn = t.T; d.C = t.N;
             d.lda = t.K; d.ldb = t.N; d.ldo = t.K;
             d.family = LOMO_KERNEL_DGRAD;
-            if (dma_eligible(d, false)) dgrads.push_back(d);
-            else if (launch_dgrad(d, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+            dgrads.push_back(d);
         }
         GemmArgs a{};
         a.A = t.X; a.B = t.dY; a.Out = t.W;
@@ -368,15 +362,9 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
         a.lda = t.K; a.ldb = t.N; a.ldo = t.K;
         a.s = s; a.s_dev = s_dev; a.flag_in = step_flag;
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
-        if (dma_eligible(a, true)) updates.push_back(a);
-        else updates_plain.push_back(a);
+        updates.push_back(a);
     }
-    if (!dgrads.empty() && launch_dma_group<false, EPI_STORE>(dgrads.data(), (int)dgrads.size(), st) != hipSuccess)
-        return LOMO_ERR_LAUNCH;
-    if (!updates.empty() && launch_dma_group<true, EPI_UPDATE>(updates.data(), (int)updates.size(), st) != hipSuccess)
-        return LOMO_ERR_LAUNCH;
-    for (const GemmArgs& a : updates_plain)
-        if (launch_wgrad_update(a, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+    if (launch_dgrad(dgrads, st) != hipSuccess || launch_wgrad_update(updates, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     return run_row_kernels(tensors, n, ws, ws_bytes, 1, s, s_dev, nullptr, nullptr, step_flag, 0.f, 0.f,
                            options != nullptr && options->reuse_grouping != 0, st);
 }
@@ -423,7 +411,7 @@ lomo_status lomo_linear_backward_update_clip_value(const lomo_half* X, const lom
         d.M = K; d.Nn = T; d.C = N;
         d.lda = K; d.ldb = N; d.ldo = K;
         d.family = LOMO_KERNEL_DGRAD;
-        if (launch_dgrad(d, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+        if (launch_dgrad({d}, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     }
     GemmArgs a{};
     a.A = X; a.B = dY; a.Out = W;
@@ -432,7 +420,7 @@ lomo_status lomo_linear_backward_update_clip_value(const lomo_half* X, const lom
     a.lr = lr; a.inv_s = inv_loss_scale; a.clipv = clip_value;
     a.flag_out = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_UPDATE;
-    return from_hip(launch_wgrad_update_clipv(a, st));
+    return from_hip(launch_wgrad_update_clipv({a}, st));
 }
 
 lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t n, float lr, float inv_loss_scale,
@@ -442,7 +430,7 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
     if (!flags) return LOMO_ERR_NULL;
     if (!(clip_value >= 0.f)) return LOMO_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    std::vector<GemmArgs> dgrads, updates, updates_plain;
+    std::vector<GemmArgs> dgrads, updates;
     for (int64_t i = 0; i < n; ++i) {
         const lomo_tensor& t = tensors[i];
         if (t.kind != LOMO_TENSOR_LINEAR || t.T == 0 || t.K == 0 || t.N == 0) continue;
@@ -452,8 +440,7 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
             d.M = t.K; d.Nn = t.T; d.C = t.N;
             d.lda = t.K; d.ldb = t.N; d.ldo = t.K;
             d.family = LOMO_KERNEL_DGRAD;
-            if (dma_eligible(d, false)) dgrads.push_back(d);
-            else if (launch_dgrad(d, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+            dgrads.push_back(d);
         }
         GemmArgs a{};
         a.A = t.X; a.B = t.dY; a.Out = t.W;
@@ -462,15 +449,9 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
         a.lr = lr; a.inv_s = inv_loss_scale; a.clipv = clip_value;
         a.flag_out = flags + i;
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
-        if (dma_eligible(a, true)) updates.push_back(a);
-        else updates_plain.push_back(a);
+        updates.push_back(a);
     }
-    if (!dgrads.empty() && launch_dma_group<false, EPI_STORE>(dgrads.data(), (int)dgrads.size(), st) != hipSuccess)
-        return LOMO_ERR_LAUNCH;
-    if (!updates.empty() && launch_dma_group<true, EPI_CLIPV>(updates.data(), (int)updates.size(), st) != hipSuccess)
-        return LOMO_ERR_LAUNCH;
-    for (const GemmArgs& a : updates_plain)
-        if (launch_wgrad_update_clipv(a, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+    if (launch_dgrad(dgrads, st) != hipSuccess || launch_wgrad_update_clipv(updates, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     cs = run_row_kernels(tensors, n, ws, ws_bytes, 2, inv_loss_scale, nullptr, nullptr, flags, nullptr, lr, clip_value, false, st);
     if (cs != LOMO_OK) return cs;
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
@@ -489,7 +470,7 @@ lomo_status lomo_linear_dgrad(const lomo_half* dY, const lomo_half* W, lomo_half
     d.M = K; d.Nn = T; d.C = N;
     d.lda = K; d.ldb = N; d.ldo = K;
     d.family = LOMO_KERNEL_DGRAD;
-    return from_hip(launch_dgrad(d, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_dgrad({d}, static_cast<hipStream_t>(stream)));
 }
 
 lomo_status lomo_linear_forward(const lomo_half* X, const lomo_half* W, lomo_half* Y, int64_t T, int64_t K, int64_t N,

@@ -20,6 +20,9 @@
 
 #include <stdlib.h>
 
+#include <algorithm>
+#include <cmath>
+
 namespace lomo {
 
 constexpr int BK = 32;         // contraction slice per pipeline stage
@@ -214,74 +217,122 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t st) {
 }
 
 // Tile choice: 256 x 256 when that still gives every CU at least one tile, else 128 x 128.
-static inline bool use_big_tiles(int64_t M, int64_t Nn) {
-    const int64_t big = ((M + 255) / 256) * ((Nn + 255) / 256);
-    return big >= 192;
+template <bool B_STRIDED, int EPI, bool A_STRIDED>
+static hipError_t launch_generic(const GemmArgs& a, hipStream_t st) {
+    const int64_t big = ((a.M + 255) / 256) * ((a.Nn + 255) / 256);
+    return big >= 192 ? launch_one<256, 256, B_STRIDED, EPI, A_STRIDED>(a, st)
+                      : launch_one<128, 128, B_STRIDED, EPI, A_STRIDED>(a, st);
 }
 
-// LOMO_DISABLE_FAST=1 forces the generic kernel everywhere, LOMO_DISABLE_DMA=1 skips the
-// direct-to-LDS kernel (testing aids).
+// LOMO_DISABLE_FAST=1 (or LOMO_DISABLE_DMA=1) forces the kernel of this file everywhere (testing aid).
 static bool fast_enabled() {
     static const bool on = [] {
-        const char* e = getenv("LOMO_DISABLE_FAST");
-        return !(e && e[0] == '1');
+        for (const char* name : {"LOMO_DISABLE_FAST", "LOMO_DISABLE_DMA"}) {
+            const char* e = getenv(name);
+            if (e && e[0] == '1') return false;
+        }
+        return true;
     }();
     return on;
 }
 
-static bool dma_enabled() {
-    static const bool on = [] {
-        const char* e = getenv("LOMO_DISABLE_DMA");
-        return !(e && e[0] == '1');
-    }();
-    return on;
+// ---- which kernel runs a tensor -----------------------------------------------------------
+// Three shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), 128 x 128 with the contraction split over two groups
+// of waves, 64 x 64 with it split over four (lomo_gemm_ksplit.hip).  Larger tiles do more work per operand byte, smaller
+// ones occupy more of the 256 CUs and walk the contraction faster.  A tile's time on a CU is a fixed part (ramp-up and
+// epilogue) and a part per contraction index; measured (us; C = contraction length, one workgroup per CU):
+//   256 x 256: 3 + 0.0275 C with all CUs busy, 0.015 C with a few      (1184 TFLOP/s over 256 CUs)
+//   128 x 128: 2.6 + 0.0098 C                                           (856 TFLOP/s)
+//    64 x  64: 2.6 + 0.0042 C                                           (500 TFLOP/s)
+// e.g. dX of 1024 x 4096 with C = 22016 (64, 256 and 1024 tiles): 350, 199 and 424 us; of 256 x 4096 (16, 64, 256): 329, 176
+// and 94 us; Y of 1024 x 12288 with C = 4096 (192, 768, 3072): 99, 120 and 209 us.
+enum { TILE_256, TILE_128, TILE_64 };
+static const double kTileFixed[3] = {3.0, 2.6, 2.6}, kTilePerC[3] = {0.0275, 0.0098, 0.0042};
+constexpr double kCus = 256.0, kLaunch = 4.0;
+
+static double tiles_of(const GemmArgs& a, int tile) {
+    const int64_t e = 256 >> tile;
+    return (double)((a.M + e - 1) / e) * (double)((a.Nn + e - 1) / e);
+}
+static double tile_time(const GemmArgs& a, int tile) { return kTileFixed[tile] + kTilePerC[tile] * (double)a.C; }
+
+// A tensor by itself: whole rounds over the chip; a 256 x 256 tile is faster when it has the memory system to itself.
+static double single_time(const GemmArgs& a, int tile) {
+    const double t = tiles_of(a, tile);
+    if (tile == TILE_256 && t < kCus) return kLaunch + kTileFixed[0] + (0.015 + 0.0125 * t / kCus) * (double)a.C;
+    return kLaunch + ceil(t / kCus) * tile_time(a, tile);
 }
 
-hipError_t launch_wgrad_update(const GemmArgs& a, hipStream_t st) {
-    hipError_t e;
-    if (fast_enabled() && dma_enabled() && try_launch_dma<true, EPI_UPDATE>(a, st, &e)) return e;
-    if (fast_enabled() && try_launch_fast<true, EPI_UPDATE>(a, st, &e)) return e;
-    return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, true, EPI_UPDATE>(a, st)
-                                    : launch_one<128, 128, true, EPI_UPDATE>(a, st);
-}
-hipError_t launch_wgrad_update_clipv(const GemmArgs& a, hipStream_t st) {
-    hipError_t e;
-    if (fast_enabled() && dma_enabled() && try_launch_dma<true, EPI_CLIPV>(a, st, &e)) return e;
-    if (fast_enabled() && try_launch_fast<true, EPI_CLIPV>(a, st, &e)) return e;
-    return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, true, EPI_CLIPV>(a, st)
-                                    : launch_one<128, 128, true, EPI_CLIPV>(a, st);
-}
-hipError_t launch_wgrad_sqnorm(const GemmArgs& a, int norm_route, hipStream_t st) {
-    hipError_t e;
-    if (norm_route != LOMO_NORM_DIRECT && fast_enabled() && dma_enabled()) {
-        std::vector<GemmArgs> one(1, a), gram, direct;
-        choose_norm_route(norm_route, one, gram, direct);
-        if (!gram.empty()) return launch_gram_group(gram.data(), 1, st);
+// A list in one launch: its work spread over the chip plus half of its longest tile for the uneven end, and no less than
+// that tile by itself.
+static double group_time(const std::vector<GemmArgs>& list, int tile) {
+    if (list.empty()) return 0.0;
+    if (list.size() == 1) return single_time(list[0], tile);
+    double work = 0.0, longest = 0.0;
+    for (const GemmArgs& a : list) {
+        work += tiles_of(a, tile) * tile_time(a, tile);
+        longest = std::max(longest, tile_time(a, tile));
     }
-    if (fast_enabled() && dma_enabled() && try_launch_dma<true, EPI_SQNORM>(a, st, &e)) return e;
-    if (fast_enabled() && try_launch_fast<true, EPI_SQNORM>(a, st, &e)) return e;
-    return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, true, EPI_SQNORM>(a, st)
-                                    : launch_one<128, 128, true, EPI_SQNORM>(a, st);
+    return kLaunch + std::max(work / kCus + 0.5 * longest, longest);
 }
-hipError_t launch_dgrad(const GemmArgs& a, hipStream_t st) {
-    hipError_t e;
-    if (fast_enabled() && dma_enabled() && try_launch_dma<false, EPI_STORE>(a, st, &e)) return e;
-    if (fast_enabled() && try_launch_fast<false, EPI_STORE>(a, st, &e)) return e;
-    return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, false, EPI_STORE>(a, st)
-                                    : launch_one<128, 128, false, EPI_STORE>(a, st);
+
+template <bool B_STRIDED, int EPI, bool A_STRIDED>
+static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st) {
+    std::vector<GemmArgs> all, by[3];
+    for (const GemmArgs& a : list) {
+        if (!fast_enabled() || !dma_eligible<B_STRIDED, A_STRIDED>(a)) {      // beyond 32-bit offsets
+            const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        int best = TILE_256;
+        for (int tile = TILE_128; tile <= TILE_64; ++tile)
+            if (single_time(a, tile) < single_time(a, best)) best = tile;
+        by[best].push_back(a);
+        all.push_back(a);
+    }
+    if (all.empty()) return hipSuccess;
+    // a list of many tensors may fill the chip with large tiles although none of its tensors does
+    if (group_time(all, TILE_256) <= group_time(by[0], TILE_256) + group_time(by[1], TILE_128) + group_time(by[2], TILE_64)) {
+        by[TILE_256] = all;
+        by[TILE_128].clear();
+        by[TILE_64].clear();
+    }
+    hipError_t e = hipSuccess;
+    if (!by[TILE_256].empty())
+        e = launch_dma_group<B_STRIDED, EPI, A_STRIDED>(by[TILE_256].data(), (int)by[TILE_256].size(), st);
+    for (int tile = TILE_128; tile <= TILE_64 && e == hipSuccess; ++tile) {
+        if (by[tile].empty()) continue;
+        // workgroups start in list order: the longest walks first
+        std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
+        e = launch_ksplit_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile == TILE_64, st);
+    }
+    return e;
+}
+
+hipError_t launch_wgrad_update(const std::vector<GemmArgs>& list, hipStream_t st) {
+    return launch_list<true, EPI_UPDATE, true>(list, st);
+}
+hipError_t launch_wgrad_update_clipv(const std::vector<GemmArgs>& list, hipStream_t st) {
+    return launch_list<true, EPI_CLIPV, true>(list, st);
+}
+hipError_t launch_wgrad_sqnorm(const std::vector<GemmArgs>& list, int norm_route, hipStream_t st) {
+    if (norm_route == LOMO_NORM_DIRECT || !fast_enabled()) return launch_list<true, EPI_SQNORM, true>(list, st);
+    std::vector<GemmArgs> gram, direct;
+    choose_norm_route(norm_route, list, gram, direct);
+    if (!gram.empty()) {
+        const hipError_t e = launch_gram_group(gram.data(), (int)gram.size(), st);
+        if (e != hipSuccess) return e;
+    }
+    return launch_list<true, EPI_SQNORM, true>(direct, st);
+}
+hipError_t launch_dgrad(const std::vector<GemmArgs>& list, hipStream_t st) {
+    return launch_list<false, EPI_STORE, true>(list, st);
 }
 
 // Y = X W^T (EPI_STORE) or Y <- Y + X W^T rounded once (EPI_UPDATE with s = -1: the residual connection).
 hipError_t launch_forward(const GemmArgs& a, bool accumulate, hipStream_t st) {
-    hipError_t e;
-    if (accumulate) {
-        if (fast_enabled() && dma_enabled() && try_launch_dma_nt<EPI_UPDATE>(a, st, &e)) return e;
-        return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, false, EPI_UPDATE, false>(a, st)
-                                        : launch_one<128, 128, false, EPI_UPDATE, false>(a, st);
-    }
-    if (fast_enabled() && dma_enabled() && try_launch_dma_nt<EPI_STORE>(a, st, &e)) return e;
-    return use_big_tiles(a.M, a.Nn) ? launch_one<256, 256, false, EPI_STORE, false>(a, st)
-                                    : launch_one<128, 128, false, EPI_STORE, false>(a, st);
+    return accumulate ? launch_list<false, EPI_UPDATE, false>({a}, st) : launch_list<false, EPI_STORE, false>({a}, st);
 }
 
 }  // namespace lomo

@@ -31,54 +31,18 @@
 //     would otherwise drain it before every LDS read;
 //   * the first slices of the next tile are requested before the epilogue of the current one runs.
 #include "lomo_gemm_common.h"
+#include "lomo_gemm_dma_common.h"
 
 namespace lomo {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-
 namespace dma {
 
-constexpr int BM = 256, BN = 256, BK = 32, NS = 4;
+constexpr int BM = 256, BN = 256, NS = 4;
 constexpr int A_HALVES = BK * BM, B_HALVES = BK * BN, STAGE_HALVES = A_HALVES + B_HALVES;
 constexpr int EPI_UNIT_HALVES = 32 * 64;                 // staging block of the row epilogue: 32 rows x 64 columns (4 KiB)
 // four stages + 32 KiB behind them: two staging blocks per wave for the row epilogue (update, store), whose first
 // 256 bytes serve as the reduction scratch of the norm epilogue.  160 KiB in all, the whole LDS of a CU.
 constexpr int LDS_BYTES = NS * STAGE_HALVES * 2 + 8 * EPI_UNIT_HALVES * 2;
-constexpr int MAX_GROUP = 40;
-
-struct GroupTensor {
-    const uint16_t* A;
-    const uint16_t* B;
-    uint16_t* Out;
-    const uint16_t* Res;
-    int32_t* flag_out;
-    int M, Nn, C, lda, ldb, ldo;
-    int tiles_m, tiles_n, tile_begin;
-};
-
-// Buffer descriptors: word 3 asks for raw 32-bit data, `bytes` is where the range check ends.
-typedef int int4v __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-constexpr uint32_t BUFFER_WORD3 = 0x00020000u;
-constexpr uint32_t MAX_RANGE = 0xE0000000u;      // no descriptor covers more than this ...
-constexpr uint32_t OUTSIDE = 0xF0000000u;        // ... so a lane offset with these bits set is outside every one
-__device__ __forceinline__ int4v make_srd(const void* base, uint32_t bytes) {
-    const uint64_t b = (uint64_t)(uintptr_t)base;
-    return int4v{(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xffffu), (int)bytes, (int)BUFFER_WORD3};
-}
-__device__ __forceinline__ uint32_t range_bytes(int64_t halves) {
-    return halves <= 0 ? 0u : (2 * halves > (int64_t)MAX_RANGE ? MAX_RANGE : (uint32_t)(2 * halves));
-}
-
-struct GroupArgs {
-    double* acc;
-    const int32_t* flag_in;
-    float s, lr, inv_s, clipv;
-    const float* s_dev;
-    int n, total_tiles;
-    GroupTensor t[MAX_GROUP];
-};
-
 // Soft alignment of the workgroups of one XCD between rounds of the update kernels (timing only, no effect on results).
 // The 32 tiles that an XCD works on in a round share operand panels through its L2 as long as they walk the
 // contraction roughly in step; the update epilogue takes a different time on every CU (it waits for HBM), and without
@@ -98,21 +62,6 @@ __global__ void clear_round_counters(int rounds) {
 }
 
 __device__ __forceinline__ int swz_s(int r) { return ((r & 1) * 10) + ((r & 2) * 2); }
-__device__ __forceinline__ int swz_c(int n) { return ((n >> 1) & 3) ^ ((n >> 3) & 1); }
-
-// 16 bytes per lane from descriptor base + soff + voff to LDS address m0 + 16 * lane; zeros where voff is not below
-// the descriptor's range - soff (callers keep soff within the range).
-__device__ __forceinline__ void dma16(uint32_t voff, int4v srd, uint32_t soff, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(srd), "s"(soff), "s"(lds_addr) : "memory", "m0");
-}
-
-__device__ __forceinline__ half8 read_tr8(const uint16_t* p0, const uint16_t* p1) {
-    typedef __attribute__((address_space(3))) short4v* lds_p;
-    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p0));
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p1));
-    return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 // ---- row epilogue (update / store) --------------------------------------------------------------------
 // The accumulator layout gives a lane 16 bytes of one output row at a time, so a wave instruction on global
@@ -619,14 +568,16 @@ static bool dma_addressable(const GemmArgs& a) {
            ((a.M + BM - 1) / BM) * ((a.Nn + BN - 1) / BN) < (1 << 24);
 }
 
-bool dma_eligible(const GemmArgs& a, bool b_strided) {
-    return b_strided ? dma_addressable<true, true>(a) : dma_addressable<false, true>(a);
+template <bool B_STRIDED, bool A_STRIDED>
+bool dma_eligible(const GemmArgs& a) {
+    return dma_addressable<B_STRIDED, A_STRIDED>(a);
 }
-
-static int64_t dma_tiles(const GemmArgs& a) { return ((a.M + dma::BM - 1) / dma::BM) * ((a.Nn + dma::BN - 1) / dma::BN); }
+template bool dma_eligible<true, true>(const GemmArgs&);
+template bool dma_eligible<false, true>(const GemmArgs&);
+template bool dma_eligible<false, false>(const GemmArgs&);
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
-static hipError_t launch_dma_group_impl(const GemmArgs* list, int n, hipStream_t st) {
+hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st) {
     using namespace dma;
     auto kern = lomo_contract_dma_kernel<B_STRIDED, EPI, A_STRIDED>;
     // thread-safe one-time set-up (initialisation of a function-local static)
@@ -635,26 +586,8 @@ static hipError_t launch_dma_group_impl(const GemmArgs* list, int n, hipStream_t
     for (int first = 0; first < n; first += MAX_GROUP) {
         const int cnt = (n - first < MAX_GROUP) ? (n - first) : MAX_GROUP;
         GroupArgs ga{};
-        ga.acc = list[first].acc;
-        ga.flag_in = list[first].flag_in;
-        ga.s = list[first].s;
-        ga.s_dev = list[first].s_dev;
-        ga.lr = list[first].lr;
-        ga.inv_s = list[first].inv_s;
-        ga.clipv = list[first].clipv;
-        ga.n = cnt;
-        int tiles = 0;
-        for (int i = 0; i < cnt; ++i) {
-            const GemmArgs& a = list[first + i];
-            GroupTensor& t = ga.t[i];
-            t.A = a.A; t.B = a.B; t.Out = a.Out; t.Res = a.Res; t.flag_out = a.flag_out;
-            t.M = (int)a.M; t.Nn = (int)a.Nn; t.C = (int)a.C;
-            t.lda = (int)a.lda; t.ldb = (int)a.ldb; t.ldo = (int)a.ldo;
-            t.tiles_m = (int)((a.M + BM - 1) / BM); t.tiles_n = (int)((a.Nn + BN - 1) / BN);
-            t.tile_begin = tiles;
-            tiles += t.tiles_m * t.tiles_n;
-        }
-        ga.total_tiles = tiles;
+        fill_group(ga, list + first, cnt, BM, BN);
+        const int tiles = ga.total_tiles;
         const int grid = tiles < cu_count() ? tiles : cu_count();
         if ((EPI == EPI_UPDATE || EPI == EPI_CLIPV) && A_STRIDED && B_STRIDED) {     // the kernels that align their rounds
             int rounds = (tiles + grid - 1) / grid;
@@ -667,35 +600,11 @@ static hipError_t launch_dma_group_impl(const GemmArgs* list, int n, hipStream_t
     return hipSuccess;
 }
 
-template <bool B_STRIDED, int EPI>
-hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st) {
-    return launch_dma_group_impl<B_STRIDED, EPI, true>(list, n, st);
-}
-
-template <int EPI>
-bool try_launch_dma_nt(const GemmArgs& a, hipStream_t st, hipError_t* err) {
-    if (!dma_addressable<false, false>(a) || dma_tiles(a) < 192) return false;
-    *err = launch_dma_group_impl<false, EPI, false>(&a, 1, st);
-    return true;
-}
-template bool try_launch_dma_nt<EPI_STORE>(const GemmArgs&, hipStream_t, hipError_t*);
-template bool try_launch_dma_nt<EPI_UPDATE>(const GemmArgs&, hipStream_t, hipError_t*);
-
-// Single tensor: worth it when there are enough tiles to fill most of the chip.
-template <bool B_STRIDED, int EPI>
-bool try_launch_dma(const GemmArgs& a, hipStream_t st, hipError_t* err) {
-    if (!dma_addressable<B_STRIDED, true>(a) || dma_tiles(a) < 192) return false;
-    *err = launch_dma_group<B_STRIDED, EPI>(&a, 1, st);
-    return true;
-}
-
-template bool try_launch_dma<true, EPI_UPDATE>(const GemmArgs&, hipStream_t, hipError_t*);
-template bool try_launch_dma<true, EPI_CLIPV>(const GemmArgs&, hipStream_t, hipError_t*);
-template bool try_launch_dma<true, EPI_SQNORM>(const GemmArgs&, hipStream_t, hipError_t*);
-template bool try_launch_dma<false, EPI_STORE>(const GemmArgs&, hipStream_t, hipError_t*);
-template hipError_t launch_dma_group<true, EPI_UPDATE>(const GemmArgs*, int, hipStream_t);
-template hipError_t launch_dma_group<true, EPI_CLIPV>(const GemmArgs*, int, hipStream_t);
-template hipError_t launch_dma_group<true, EPI_SQNORM>(const GemmArgs*, int, hipStream_t);
-template hipError_t launch_dma_group<false, EPI_STORE>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<true, EPI_UPDATE, true>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<true, EPI_CLIPV, true>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<true, EPI_SQNORM, true>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<false, EPI_STORE, true>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<false, EPI_STORE, false>(const GemmArgs*, int, hipStream_t);
+template hipError_t launch_dma_group<false, EPI_UPDATE, false>(const GemmArgs*, int, hipStream_t);
 
 }  // namespace lomo

@@ -39,21 +39,17 @@ struct GemmArgs {
     const int32_t* flag_in;  // overflow flag to honour (EPI_UPDATE), may be null
 };
 
-// Whole-tile fast path (lomo_gemm_fast.hip): returns false when the shape is not eligible.
-template <bool B_STRIDED, int EPI>
-bool try_launch_fast(const GemmArgs& a, hipStream_t st, hipError_t* err);
-
-// Persistent 256 x 256 direct-to-LDS kernel (lomo_gemm_dma.hip).  try_launch_dma returns false when
-// the tensor is not eligible or too small; launch_dma_group runs a list of eligible tensors (same
-// epilogue, same acc / step flag / step size) in as few launches as the argument space allows.
-bool dma_eligible(const GemmArgs& a, bool b_strided);
-template <bool B_STRIDED, int EPI>
-bool try_launch_dma(const GemmArgs& a, hipStream_t st, hipError_t* err);
-template <bool B_STRIDED, int EPI>
+// Persistent 256 x 256 direct-to-LDS kernel (lomo_gemm_dma.hip): runs a list of eligible tensors (same epilogue, same acc /
+// step flag / step size) in as few launches as the argument space allows.
+template <bool B_STRIDED, bool A_STRIDED>
+bool dma_eligible(const GemmArgs& a);
+template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st);
-// Forward product Y = X W^T: A = W [M x C] and B = X [Nn x C], both contraction-contiguous.
-template <int EPI>
-bool try_launch_dma_nt(const GemmArgs& a, hipStream_t st, hipError_t* err);
+
+// Kernel with the contraction split over the waves of a workgroup (lomo_gemm_ksplit.hip), one workgroup per 128 x 128 or
+// 64 x 64 tile; takes lists and shapes as the persistent kernel does.
+template <bool B_STRIDED, int EPI, bool A_STRIDED>
+hipError_t launch_ksplit_group(const GemmArgs* list, int n, bool small_tile, hipStream_t st);
 
 // Gram route of the norm pass (lomo_gram.hip): ||dY^T X||^2 from X X^T and dY dY^T.  `a` is a norm-pass
 // contraction (A = X, B = dY, C = T).  Costs are in units of one 256 x 256 x 32 slice on one CU.
@@ -64,10 +60,11 @@ hipError_t launch_gram_group(const GemmArgs* list, int n, hipStream_t st);
 // Splits the eligible tensors of `all` between the two routes according to `mode` (LOMO_NORM_*).
 void choose_norm_route(int mode, const std::vector<GemmArgs>& all, std::vector<GemmArgs>& gram, std::vector<GemmArgs>& direct);
 
-hipError_t launch_wgrad_update(const GemmArgs& a, hipStream_t st);
-hipError_t launch_wgrad_update_clipv(const GemmArgs& a, hipStream_t st);
-hipError_t launch_wgrad_sqnorm(const GemmArgs& a, int norm_route, hipStream_t st);
-hipError_t launch_dgrad(const GemmArgs& a, hipStream_t st);
+// Lists of tensors with the same epilogue, acc, step flag and step size; the kernel of each follows from its shape.
+hipError_t launch_wgrad_update(const std::vector<GemmArgs>& list, hipStream_t st);
+hipError_t launch_wgrad_update_clipv(const std::vector<GemmArgs>& list, hipStream_t st);
+hipError_t launch_wgrad_sqnorm(const std::vector<GemmArgs>& list, int norm_route, hipStream_t st);
+hipError_t launch_dgrad(const std::vector<GemmArgs>& list, hipStream_t st);
 // A = W [M = N_out x C = K_in], B = X [Nn = T x C], Out = Y [T x N_out]; accumulate: Y <- rne16(Y + acc).
 hipError_t launch_forward(const GemmArgs& a, bool accumulate, hipStream_t st);
 

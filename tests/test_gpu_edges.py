@@ -71,6 +71,39 @@ SHAPES = [(1, 8, 8), (7, 8, 264), (31, 264, 8), (32, 256, 256), (33, 248, 520), 
 
 @pytest.mark.parametrize("T,K,N", SHAPES)
 def test_step_at_tile_and_slice_edges(L, T, K, N):
+    step_matches_oracle(L, T, K, N)
+
+
+# Ragged shapes for each kernel a tensor can go to (the small ones above take 64 x 64 tiles): (update, dX) run with
+# tiles of (128, 128), (256, 64), (256, 256), (128, 64), and a contraction of one index with many tiles
+@pytest.mark.parametrize("T,K,N", [(777, 1544, 1032), (300, 3080, 4104), (3080, 3336, 3848), (504, 1032, 1544), (1, 2056, 4104)])
+def test_step_in_each_tile_shape(L, T, K, N):
+    step_matches_oracle(L, T, K, N)
+
+
+@pytest.mark.parametrize("T", [129, 600])
+def test_lists_of_unequal_tensors(L, T):
+    """More tensors than one launch's table holds, contraction lengths from 8 to 4104, each result as if it were alone."""
+    shapes = [(264, 8), (8, 4104), (520, 1032)] * 15
+    tensors, alone = [], []
+    for i, (K, N) in enumerate(shapes):
+        X, dY, W = f16(20 + i, (T, K), 1.0), f16(90 + i, (T, N), 1.0), f16(160 + i, (N, K), 0.02)
+        tensors.append({"kind": "linear", "X": dev(X), "dY": dev(dY), "W": dev(W), "dX": torch.zeros(T, K, dtype=torch.float16, device=DEV)})
+        dX, W2 = torch.empty(T, K, dtype=torch.float16, device=DEV), dev(W)
+        L.lomo_linear_backward_update(tensors[-1]["X"], tensors[-1]["dY"], W2, dX, 1e-3, 1.0, 1.0)
+        alone.append((W2, dX))
+    lst = L.make_tensor_list(tensors)
+    ws = torch.empty(max(256, L.lomo_step_workspace_bytes(lst)), dtype=torch.uint8, device=DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    L.lomo_step_update_pass(lst, 1e-3, 1.0, 1.0, flag, ws)
+    for i, (t, (W2, dX)) in enumerate(zip(tensors, alone)):
+        weights_ok(t["W"].cpu().numpy(), W2.cpu().numpy(), f"W {i}")
+        d64, w64 = t["dY"].cpu().numpy().astype(np.float64), f16(160 + i, shapes[i][::-1], 0.02).astype(np.float64)
+        for got in (t["dX"], dX):
+            product_ok(got.cpu().numpy(), d64 @ w64, np.abs(d64) @ np.abs(w64), f"dX {i}")
+
+
+def step_matches_oracle(L, T, K, N):
     """Norm, visible update, dX and the clip-by-value update through the whole-pass calls."""
     Sc = 256.0
     X, dY, W = f16(1, (T, K), 1.0), f16(2, (T, N), 0.01, Sc), f16(3, (N, K), 0.02)
