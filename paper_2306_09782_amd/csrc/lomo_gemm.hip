@@ -1,4 +1,5 @@
-// MFMA contraction kernels of the LOMO hot path for gfx950 (CDNA4, wave64).
+// MFMA contraction kernel of the LOMO hot path for any shape, gfx950 (CDNA4, wave64), and the choice between the kernels.
+// What the direct-to-LDS kernels address with 32-bit offsets goes to them; this one serves what lies beyond.
 //
 // One kernel template serves the three dense steps of a linear tensor:
 //   * fused wgrad + SGD update (paper section 3.2, Algorithm 1: theta <- theta - lr * g, the
@@ -237,48 +238,38 @@ static bool fast_enabled() {
 }
 
 // ---- which kernel runs a tensor -----------------------------------------------------------
-// Three shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), 128 x 128 with the contraction split over two groups
-// of waves, 64 x 64 with it split over four (lomo_gemm_ksplit.hip).  Larger tiles do more work per operand byte, smaller
-// ones occupy more of the 256 CUs and walk the contraction faster.  A tile's time on a CU is a fixed part (ramp-up and
-// epilogue) and a part per contraction index; measured (us; C = contraction length, one workgroup per CU):
-//   256 x 256: 3 + 0.0275 C with all CUs busy, 0.015 C with a few      (1184 TFLOP/s over 256 CUs)
+// Four shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), and in lomo_gemm_ksplit.hip 128 x 128 with the
+// contraction split over two groups of waves, 128 x 64 and 64 x 64 with it split over four.  Larger tiles do more work per
+// operand byte, smaller ones occupy more of the 256 CUs and walk the contraction faster.  A tile's time on a CU is a fixed
+// part (ramp-up and epilogue) and a part per contraction index; measured (us; C = contraction length, one workgroup per CU):
+//   256 x 256: 3 + 0.0275 C with all CUs busy, 0.015 C with a few      (1220 TFLOP/s over 256 CUs)
 //   128 x 128: 2.6 + 0.0098 C                                           (856 TFLOP/s)
-//    64 x  64: 2.6 + 0.0042 C                                           (500 TFLOP/s)
-// e.g. dX of 1024 x 4096 with C = 22016 (64, 256 and 1024 tiles): 350, 199 and 424 us; of 256 x 4096 (16, 64, 256): 329, 176
-// and 94 us; Y of 1024 x 12288 with C = 4096 (192, 768, 3072): 99, 120 and 209 us.
-enum { TILE_256, TILE_128, TILE_64 };
-static const double kTileFixed[3] = {3.0, 2.6, 2.6}, kTilePerC[3] = {0.0275, 0.0098, 0.0042};
+//   128 x  64: 2.6 + 0.0053 C                                           (791 TFLOP/s)
+//    64 x  64: 2.6 + 0.0042 C                                           (499 TFLOP/s)
+// e.g. (in this order) dX of 1024 x 4096 with C = 22016 (64, 256, 512 and 1024 tiles): 350, 199, 241 and 424 us; of 777 x 2048
+// with C = 32000 (32, 112, 208, 416): -, 260, 171 and 271 us; of 256 x 4096 with C = 22016 (16, 64, 128, 256): 329, 176, 112 and
+// 94 us; Y of 1024 x 12288 with C = 4096 (192, 768, 1536, 3072): 99, 115, 134 and 209 us.
+static const double kTileFixed[N_TILES] = {3.0, 2.6, 2.6, 2.6}, kTilePerC[N_TILES] = {0.0275, 0.0098, 0.0053, 0.0042};
+static const int kTileM[N_TILES] = {256, 128, 128, 64}, kTileN[N_TILES] = {256, 128, 64, 64};
 constexpr double kCus = 256.0, kLaunch = 4.0;
 
 static double tiles_of(const GemmArgs& a, int tile) {
-    const int64_t e = 256 >> tile;
-    return (double)((a.M + e - 1) / e) * (double)((a.Nn + e - 1) / e);
+    return (double)((a.M + kTileM[tile] - 1) / kTileM[tile]) * (double)((a.Nn + kTileN[tile] - 1) / kTileN[tile]);
 }
 static double tile_time(const GemmArgs& a, int tile) { return kTileFixed[tile] + kTilePerC[tile] * (double)a.C; }
 
-// A tensor by itself: whole rounds over the chip; a 256 x 256 tile is faster when it has the memory system to itself.
+// A tensor's choice depends on its own shape only, never on the list it comes in: the kernels add in different orders, and a
+// tensor's result has the same bits alone and in any list.  Whole rounds over the chip; a 256 x 256 tile is faster when it
+// has the memory system to itself.
 static double single_time(const GemmArgs& a, int tile) {
     const double t = tiles_of(a, tile);
     if (tile == TILE_256 && t < kCus) return kLaunch + kTileFixed[0] + (0.015 + 0.0125 * t / kCus) * (double)a.C;
     return kLaunch + ceil(t / kCus) * tile_time(a, tile);
 }
 
-// A list in one launch: its work spread over the chip plus half of its longest tile for the uneven end, and no less than
-// that tile by itself.
-static double group_time(const std::vector<GemmArgs>& list, int tile) {
-    if (list.empty()) return 0.0;
-    if (list.size() == 1) return single_time(list[0], tile);
-    double work = 0.0, longest = 0.0;
-    for (const GemmArgs& a : list) {
-        work += tiles_of(a, tile) * tile_time(a, tile);
-        longest = std::max(longest, tile_time(a, tile));
-    }
-    return kLaunch + std::max(work / kCus + 0.5 * longest, longest);
-}
-
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st) {
-    std::vector<GemmArgs> all, by[3];
+    std::vector<GemmArgs> by[N_TILES];
     for (const GemmArgs& a : list) {
         if (!fast_enabled() || !dma_eligible<B_STRIDED, A_STRIDED>(a)) {      // beyond 32-bit offsets
             const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);
@@ -286,26 +277,18 @@ static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st)
             continue;
         }
         int best = TILE_256;
-        for (int tile = TILE_128; tile <= TILE_64; ++tile)
+        for (int tile = TILE_128; tile < N_TILES; ++tile)
             if (single_time(a, tile) < single_time(a, best)) best = tile;
         by[best].push_back(a);
-        all.push_back(a);
-    }
-    if (all.empty()) return hipSuccess;
-    // a list of many tensors may fill the chip with large tiles although none of its tensors does
-    if (group_time(all, TILE_256) <= group_time(by[0], TILE_256) + group_time(by[1], TILE_128) + group_time(by[2], TILE_64)) {
-        by[TILE_256] = all;
-        by[TILE_128].clear();
-        by[TILE_64].clear();
     }
     hipError_t e = hipSuccess;
     if (!by[TILE_256].empty())
         e = launch_dma_group<B_STRIDED, EPI, A_STRIDED>(by[TILE_256].data(), (int)by[TILE_256].size(), st);
-    for (int tile = TILE_128; tile <= TILE_64 && e == hipSuccess; ++tile) {
+    for (int tile = TILE_128; tile < N_TILES && e == hipSuccess; ++tile) {
         if (by[tile].empty()) continue;
         // workgroups start in list order: the longest walks first
         std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
-        e = launch_ksplit_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile == TILE_64, st);
+        e = launch_ksplit_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile, st);
     }
     return e;
 }

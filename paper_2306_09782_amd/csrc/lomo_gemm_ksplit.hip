@@ -6,36 +6,48 @@
 //   * the tile is 64 WM x 64 WN, and WK groups of WM x WN waves walk it together: group k takes the slices (32 contraction
 //     indices) k, k + WK, ... with a ring of LDS stages and fp32 accumulators of its own, and the groups' partial sums
 //     are added in fp32 through the LDS at the end.  128 x 128 x 2 puts two waves on every SIMD of a CU (one wave's LDS
-//     reads run behind the other's MFMAs); 64 x 64 x 4 gives four times the workgroups and a quarter of the serial walk,
-//     and its rings are private to one wave each, so its main loop has no barrier;
+//     reads run behind the other's MFMAs); 128 x 64 x 4 gives twice the workgroups and half of the serial
+//     walk at nearly the rate, 64 x 64 x 4 four times and a quarter, with rings private to one wave each: no barrier;
 //   * operands arrive by direct-to-LDS loads through buffer descriptors, as in the persistent kernel: the range check
 //     supplies the zeros outside the tensor, lanes behind the last column get an offset that no descriptor covers,
 //     the odd slice comes first and is masked by lane, slices behind the last one are out of range as a whole;
 //   * the fragments of the next slice are read while the current one is multiplied, so the stage of the current slice is
-//     already free when its multiplication starts: all four stages hold loads in flight.
+//     already free when its multiplication starts: all stages hold loads in flight.
 // One launch takes a list of tensors; workgroups start in list order, longest contraction first.
 //
 // Measured, before -> now (us per call; before: 256 x 256 tiles, or 128 x 128 with register-staged operands):
 //   dX of 1024 x 4096, C = 22016: 267 -> 199 (926 TFLOP/s);  of 960 x 4096, C = 22016: 579 -> 196
 //   Y of 1024 x 4096, C = 11008: 259 -> 118 (783);           dX of 256 x 4096, C = 32000: 450 -> 158
+//   dX of 777 x 2048, C = 32000: 128 x 64 tiles 171 (783; 64 x 64 tiles 271, 128 x 128 tiles 260)
 //   dX of 256 x 1024, C = 32000: 347 -> 138;                 Y of 256 x 1024, C = 2816: 51 -> 10 (the call's own cost)
 // The 128 x 128 tile reads 4 KiB of the LDS per 128 matrix clocks of a wave, 128 bytes per clock and CU: that port, shared
 // with the arriving loads, is its bound.  The 64 x 64 tile reads each operand byte from the L2 once per 64 products.
 #include "lomo_gemm_common.h"
 #include "lomo_gemm_dma_common.h"
 
+#include <type_traits>
+
 namespace lomo {
 
 namespace ksplit {
 
 using dma::BK;
-constexpr int NS = 4;      // LDS stages of each group
+// LDS stages of each group: as many as 160 KiB hold
+constexpr int stages(int wm, int wn, int wk) { return wk * (wm + wn) > 8 ? 3 : 4; }
 
 // chunk swizzle of a contraction-strided tile row of BX columns: the four rows that one transposing read touches start in
 // different quarters of the 256 bytes that the banks hold (rows of 64 columns: two rows side by side in them)
 template <int BX>
 __device__ __forceinline__ int swz_row(int r) {
     return BX == 64 ? (r & 2) * 2 : ((r & 1) * 10) + ((r & 2) * 2);
+}
+
+template <int N, typename F>
+__device__ __forceinline__ void static_for_pairs(F&& f) {
+    if constexpr (N > 0) {
+        static_for_pairs<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
 }
 
 }  // namespace ksplit
@@ -47,7 +59,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void lomo_contract_ksplit_kernel
     constexpr int TM = 64 * WM, TN = 64 * WN;
     constexpr int AH = BK * TM, BH = BK * TN, STAGE = AH + BH;                     // halves
     constexpr int NA = 4 / WN, NB = 4 / WM;                                        // load instructions of a wave per slice
-    constexpr int NS = ksplit::NS;
+    constexpr int NS = stages(WM, WN, WK);
     constexpr bool PRIVATE = WM * WN == 1;                                         // a ring belongs to one wave
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
 
@@ -217,7 +229,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void lomo_contract_ksplit_kernel
         arrive();                                   // stage u + 1 is here, stage u is in registers everywhere
         issue(u, false);
         __builtin_amdgcn_sched_barrier(0);
-        read_all(load, (u + 1) & (NS - 1));
+        read_all(load, (u + 1) % NS);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
@@ -235,18 +247,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void lomo_contract_ksplit_kernel
 
 #pragma unroll
     for (int st = 0; st < NS; ++st) issue(st, st == 0);
-    // slice 0 has landed: three younger ones in flight
+    // slice 0 has landed: NS - 1 younger ones in flight
     if constexpr (PRIVATE) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * (NA + NB)) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NS - 1) * (NA + NB)) : "memory");
     __builtin_amdgcn_sched_barrier(0);
     Frags f0, f1;
     read_all(f0, 0);
-    for (int kt = 0; kt < KT; kt += 4) {             // slices from KT on are zeros
-        step(f0, f1, 0);
-        step(f1, f0, 1);
-        if (kt + 2 >= KT) break;
-        step(f0, f1, 2);
-        step(f1, f0, 3);
+    for (int kt = 0; kt < KT;) {                     // slices from KT on are zeros
+        static_for_pairs<NS == 3 ? 3 : 2>([&](auto pair) {
+            constexpr int u = 2 * decltype(pair)::value;
+            if (kt >= KT) return;
+            step(f0, f1, u % NS);
+            step(f1, f0, (u + 1) % NS);
+            kt += 2;
+        });
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the LDS is free
     __builtin_amdgcn_sched_barrier(0);
@@ -378,7 +392,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void lomo_contract_ksplit_kernel
 
 template <int WM, int WN, int WK, bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_ksplit_tile(const GemmArgs* list, int n, hipStream_t st) {
-    constexpr int LDS = ksplit::NS * WK * (64 * WM + 64 * WN) * dma::BK * 2;
+    constexpr int LDS = ksplit::stages(WM, WN, WK) * WK * (64 * WM + 64 * WN) * dma::BK * 2;
     static_assert(LDS >= WM * WN * WK * 4 * 4096, "the partial sums are exchanged where the stages were");
     auto kern = lomo_contract_ksplit_kernel<WM, WN, WK, B_STRIDED, EPI, A_STRIDED>;
     // thread-safe one-time set-up (initialisation of a function-local static)
@@ -395,16 +409,19 @@ static hipError_t launch_ksplit_tile(const GemmArgs* list, int n, hipStream_t st
 }
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
-hipError_t launch_ksplit_group(const GemmArgs* list, int n, bool small_tile, hipStream_t st) {
-    return small_tile ? launch_ksplit_tile<1, 1, 4, B_STRIDED, EPI, A_STRIDED>(list, n, st)
-                      : launch_ksplit_tile<2, 2, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+hipError_t launch_ksplit_group(const GemmArgs* list, int n, int tile, hipStream_t st) {
+    switch (tile) {
+        case TILE_128: return launch_ksplit_tile<2, 2, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+        case TILE_128_64: return launch_ksplit_tile<2, 1, 4, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+        default: return launch_ksplit_tile<1, 1, 4, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+    }
 }
 
-template hipError_t launch_ksplit_group<true, EPI_UPDATE, true>(const GemmArgs*, int, bool, hipStream_t);
-template hipError_t launch_ksplit_group<true, EPI_CLIPV, true>(const GemmArgs*, int, bool, hipStream_t);
-template hipError_t launch_ksplit_group<true, EPI_SQNORM, true>(const GemmArgs*, int, bool, hipStream_t);
-template hipError_t launch_ksplit_group<false, EPI_STORE, true>(const GemmArgs*, int, bool, hipStream_t);
-template hipError_t launch_ksplit_group<false, EPI_STORE, false>(const GemmArgs*, int, bool, hipStream_t);
-template hipError_t launch_ksplit_group<false, EPI_UPDATE, false>(const GemmArgs*, int, bool, hipStream_t);
+template hipError_t launch_ksplit_group<true, EPI_UPDATE, true>(const GemmArgs*, int, int, hipStream_t);
+template hipError_t launch_ksplit_group<true, EPI_CLIPV, true>(const GemmArgs*, int, int, hipStream_t);
+template hipError_t launch_ksplit_group<true, EPI_SQNORM, true>(const GemmArgs*, int, int, hipStream_t);
+template hipError_t launch_ksplit_group<false, EPI_STORE, true>(const GemmArgs*, int, int, hipStream_t);
+template hipError_t launch_ksplit_group<false, EPI_STORE, false>(const GemmArgs*, int, int, hipStream_t);
+template hipError_t launch_ksplit_group<false, EPI_UPDATE, false>(const GemmArgs*, int, int, hipStream_t);
 
 }  // namespace lomo
