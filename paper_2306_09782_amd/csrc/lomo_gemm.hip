@@ -238,17 +238,9 @@ static bool fast_enabled() {
 }
 
 // ---- which kernel runs a tensor -----------------------------------------------------------
-// Four shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), and in lomo_gemm_ksplit.hip 128 x 128 with the
-// contraction split over two groups of waves, 128 x 64 and 64 x 64 with it split over four.  Larger tiles do more work per
-// operand byte, smaller ones occupy more of the 256 CUs and walk the contraction faster.  A tile's time on a CU is a fixed
-// part (ramp-up and epilogue) and a part per contraction index; measured (us; C = contraction length, one workgroup per CU):
-//   256 x 256: 3 + 0.0275 C with all CUs busy, 0.015 C with a few      (1220 TFLOP/s over 256 CUs)
-//   128 x 128: 2.6 + 0.0098 C                                           (856 TFLOP/s)
-//   128 x  64: 2.6 + 0.0053 C                                           (791 TFLOP/s)
-//    64 x  64: 2.6 + 0.0042 C                                           (499 TFLOP/s)
-// e.g. (in this order) dX of 1024 x 4096 with C = 22016 (64, 256, 512 and 1024 tiles): 350, 199, 241 and 424 us; of 777 x 2048
-// with C = 32000 (32, 112, 208, 416): -, 260, 171 and 271 us; of 256 x 4096 with C = 22016 (16, 64, 128, 256): 329, 176, 112 and
-// 94 us; Y of 1024 x 12288 with C = 4096 (192, 768, 1536, 3072): 99, 115, 134 and 209 us.
+// Four shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), and in lomo_gemm_tile.hip 128 x 128, 128 x 64 and
+// 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the 256 CUs and walk the contraction
+// faster.  A tile's time on a CU is a fixed part (ramp-up and epilogue) and a part per contraction index.
 static const double kTileFixed[N_TILES] = {3.0, 2.6, 2.6, 2.6}, kTilePerC[N_TILES] = {0.0275, 0.0098, 0.0053, 0.0042};
 static const int kTileM[N_TILES] = {256, 128, 128, 64}, kTileN[N_TILES] = {256, 128, 64, 64};
 constexpr double kCus = 256.0, kLaunch = 4.0;
@@ -258,8 +250,7 @@ static double tiles_of(const GemmArgs& a, int tile) {
 }
 static double tile_time(const GemmArgs& a, int tile) { return kTileFixed[tile] + kTilePerC[tile] * (double)a.C; }
 
-// A tensor's choice depends on its own shape only, never on the list it comes in: the kernels add in different orders, and a
-// tensor's result has the same bits alone and in any list.  Whole rounds over the chip; a 256 x 256 tile is faster when it
+// Whole rounds over the chip; a 256 x 256 tile is faster when it
 // has the memory system to itself.
 static double single_time(const GemmArgs& a, int tile) {
     const double t = tiles_of(a, tile);
@@ -288,7 +279,7 @@ static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st)
         if (by[tile].empty()) continue;
         // workgroups start in list order: the longest walks first
         std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
-        e = launch_ksplit_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile, st);
+        e = launch_tile_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile, st);
     }
     return e;
 }

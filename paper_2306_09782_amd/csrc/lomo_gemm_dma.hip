@@ -10,9 +10,10 @@
 // tensor ends, so the hardware's range check returns zeros for what lies behind the last row, and lanes whose
 // columns lie outside are given an offset no descriptor covers (loads return zero, stores are dropped; each
 // wave still issues the same number of vector-memory instructions, which the counted waits rely on).  The
-// contraction is cut into slices of 32 with the odd slice FIRST, where the loads are issued by the prologue and a
-// few extra instructions cost nothing; slices beyond the last one (their number is rounded up to a multiple
-// of four) and the prefetches past the end are out of range as a whole and move no data.
+// contraction is cut into slices of 32 and walked from the first to the last, which may be short: the rows of a
+// contraction-strided operand end with its range there, the lanes of a contraction-contiguous one are masked (its memory
+// goes on with the next row).  Slices beyond the last one (their number is rounded up to a multiple of four) and the
+// prefetches past the end are out of range as a whole and move no data.
 // Measured: a 7B layer's step at 2999 tokens 6.36 -> 3.20 ms (567 -> 1138 TFLOP/s; the register-staged kernel of
 // lomo_gemm.hip had every shape that was not whole tiles), at 4096 tokens 4.14 -> 4.13 ms: the descriptors' scalar offsets
 // also take half of the scalar instructions out of the main loop (120 -> 58 per four slices).
@@ -269,9 +270,19 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     int4v a_srd{}, b_srd{};
     uint32_t a_step = 0, b_step = 0;       // bytes from one slice to the next
     uint32_t a_next = 0, b_next = 0;       // byte offset of the slice to be requested next
-    uint32_t a_end = 0, b_end = 0;         // offsets from here on are behind the last slice
-    int first_rows = BK;                   // contraction length of the first slice
+    uint32_t a_end = 0, b_end = 0;         // range of the descriptor: a slice offset that reads nothing
+    uint32_t last = 0, tail = 0;           // contraction-contiguous operands: offset of the last slice; this lane's mask there
     int KT = 0;                            // slices walked: a multiple of 4
+
+    // From the last slice of a contraction-contiguous operand on (nothing follows it) the lanes behind the end are masked.
+    auto mask_a = [&] {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) a_voff[it] |= tail;
+    };
+    auto mask_b = [&] {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) b_voff[it] |= tail;
+    };
 
     // Locate tile number w of the concatenated list; set up the load state; return its coordinates.
     // A workgroup's tile numbers only grow, so the search for the tile's tensor resumes at the previous tile's.
@@ -319,13 +330,18 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         b_step = (uint32_t)BK * b_unit;
         const int used = (T.C + BK - 1) / BK;
         KT = (used + 3) & ~3;
-        first_rows = T.C - (used - 1) * BK;
-        a_next = a_step - (uint32_t)(BK - first_rows) * a_unit;
-        b_next = b_step - (uint32_t)(BK - first_rows) * b_unit;
-        a_end = A_STRIDED ? (uint32_t)a_srd[2] : (uint32_t)T.C * 2u;
-        b_end = B_STRIDED ? (uint32_t)b_srd[2] : (uint32_t)T.C * 2u;
-        if (a_next >= a_end) a_next = (uint32_t)a_srd[2];
-        if (b_next >= b_end) b_next = (uint32_t)b_srd[2];
+        a_next = b_next = 0;
+        a_end = (uint32_t)a_srd[2];
+        b_end = (uint32_t)b_srd[2];
+        if constexpr (!A_STRIDED || !B_STRIDED) {
+            last = (uint32_t)(used - 1) * (BK * 2u);
+            // swz_c(16 q + n) = swz_c(n): one mask for all of the lane's rows
+            tail = ((lane & 3) ^ swz_c(lane >> 2)) * 8 < T.C - (used - 1) * BK ? 0u : OUTSIDE;
+            if (last == 0) {
+                if constexpr (!A_STRIDED) mask_a();
+                if constexpr (!B_STRIDED) mask_b();
+            }
+        }
     };
 
     // One DMA instruction of the slice to be requested next: part 0 = A tile, part 1 = B tile; `it` selects this
@@ -337,39 +353,34 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
             dma16(a_voff[it], a_srd, a_next, l);
             if (it == 3) {
                 a_next += a_step;
-                if (a_next >= a_end) a_next = (uint32_t)a_srd[2];
+                if constexpr (A_STRIDED) {
+                    if (a_next >= a_end) a_next = a_end;
+                } else if (__builtin_expect(a_next >= last, 0)) {
+                    if (a_next == last) mask_a();
+                    else a_next = a_end;
+                }
             }
         } else {
             dma16(b_voff[it], b_srd, b_next, l);
             if (it == 3) {
                 b_next += b_step;
-                if (b_next >= b_end) b_next = (uint32_t)b_srd[2];
+                if constexpr (B_STRIDED) {
+                    if (b_next >= b_end) b_next = b_end;
+                } else if (__builtin_expect(b_next >= last, 0)) {
+                    if (b_next == last) mask_b();
+                    else b_next = b_end;
+                }
             }
         }
-    };
-    // The first slice: what lies behind its first_rows contraction indices is masked lane by lane.
-    auto issue_first = [&](int part, int it) {
-        const uint32_t l = lds_wave + (uint32_t)part * (A_HALVES * 2u) + (uint32_t)it * 1024u;
-        const int q = wave * 4 + it;
-        const int row = 2 * q + (lane >> 5);                                            // strided: this lane's contraction row
-        const int n = 16 * q + (lane >> 2), kc = ((lane & 3) ^ swz_c(n)) * 8;          // contiguous: its first index
-        const int c = ((part == 0) ? A_STRIDED : B_STRIDED) ? row : kc;
-        dma16((part == 0 ? a_voff[it] : b_voff[it]) | (c < first_rows ? 0u : OUTSIDE), part == 0 ? a_srd : b_srd, 0u, l);
     };
     // Slices 0..2 and the A part of slice 3 of the tile that `setup` selected.
     auto issue_prologue = [&] {
 #pragma unroll
         for (int st = 0; st < 3; ++st) {
 #pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                if (st == 0) issue_first(0, it);
-                else issue1(st, 0, it);
-            }
+            for (int it = 0; it < 4; ++it) issue1(st, 0, it);
 #pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                if (st == 0) issue_first(1, it);
-                else issue1(st, 1, it);
-            }
+            for (int it = 0; it < 4; ++it) issue1(st, 1, it);
         }
 #pragma unroll
         for (int it = 0; it < 4; ++it) issue1(3, 0, it);
@@ -493,7 +504,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
                 half_slice(fa1, fb1, fa0, fb0, (u + 1) & 3, 0, false, u, 0);
             }
         }
-        // drain: the loads past the end (re-reads) have landed, all waves are done with the LDS stages
+        // drain: the loads past the end (zeros) have landed, all waves are done with the LDS stages
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
         // epilogue arguments of the tile just finished

@@ -46,11 +46,11 @@ bool dma_eligible(const GemmArgs& a);
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st);
 
-// Kernel with the contraction split over the waves of a workgroup (lomo_gemm_ksplit.hip), one workgroup per tile; takes lists
-// and shapes as the persistent kernel does.  Tiles are (m) x (n) as in GemmArgs.
+// Kernel of smaller tiles (lomo_gemm_tile.hip), one workgroup per tile; takes lists and shapes as the persistent kernel does and
+// gives the same bits.  Tiles are (m) x (n) as in GemmArgs.
 enum { TILE_256, TILE_128, TILE_128_64, TILE_64, N_TILES };
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
-hipError_t launch_ksplit_group(const GemmArgs* list, int n, int tile, hipStream_t st);
+hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t st);
 
 // Gram route of the norm pass (lomo_gram.hip): ||dY^T X||^2 from X X^T and dY dY^T.  `a` is a norm-pass
 // contraction (A = X, B = dY, C = T).  Costs are in units of one 256 x 256 x 32 slice on one CU.

@@ -164,12 +164,7 @@ def test_block_step_matches_oracle(L, T, H, F, visible):
     assert abs(res["norm"] / want["norm"] - 1) < 1e-3 and abs(res["norm"] / want["norm"] - 1) < 1e-4
     assert abs(res["clip_coef"] / want["clip_coef"] - 1) < 1e-4
     ulps_ok(dWd.cpu().numpy(), want["W_d"], "W_d")
-    # A sum of da next to the midpoint of two fp16 values rounds either way (fp32 sums in any order), which moves its dgu by an
-    # ulp and W_gu by lr / S |difference|^T |xn|; two ulps of a weight that the update brought close to zero are less than that.
-    got_gu, dgu_off = dWgu.cpu().numpy(), np.abs(blk.dgu.cpu().numpy().astype(np.float64) - want["dgu"].astype(np.float64))
-    moved = lr * want["clip_coef"] / scale * (dgu_off.T @ np.abs(saved["xn"].astype(np.float64)))
-    off = np.abs(got_gu.astype(np.float64) - want["W_gu"].astype(np.float64))
-    ulps_ok(got_gu, want["W_gu"], "W_gu", near=(moved > 0) & (off <= moved + 2 * np.spacing(np.abs(want["W_gu"])).astype(np.float64)))
+    ulps_ok(dWgu.cpu().numpy(), want["W_gu"], "W_gu")
     ulps_ok(dw.cpu().numpy(), want["w"], "gain")
     if visible:
         for got, new, old in ((dWd, want["W_d"], W_d), (dWgu, want["W_gu"], W_gu)):

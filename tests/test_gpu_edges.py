@@ -160,3 +160,35 @@ def test_non_finite_rows_stay_in_their_rows(L, T, K, N):
         a, b = dY[others].astype(np.float64), X[others].astype(np.float64)
         product_ok(got_dx[others], a @ w, np.abs(a) @ np.abs(w), "dX")
         product_ok(got_y[others], b @ w.T, np.abs(b) @ np.abs(w).T, "Y")
+
+
+def test_bits_do_not_depend_on_the_size_of_the_call(L):
+    """Every element is one chain of fp32 sums over the contraction, in the same order in every kernel: a token's Y and dX
+    have the same bits in a batch of 3080 as in one of 8, a row of W the same update in a tensor of 4104 rows as in one of
+    8.  The sizes take the call through all tile shapes; none of the contractions is a whole number of slices."""
+    T, K, N = 3080, 1032, 4104
+    X, dY, W, R = dev(f16(10, (T, K), 1.0)), dev(f16(11, (T, N), 1.0)), dev(f16(12, (N, K), 0.02)), dev(f16(13, (T, N), 1.0))
+    new = lambda *shape: torch.empty(*shape, dtype=torch.float16, device=DEV)
+
+    def by_token(rows):
+        x, d, r = X[rows].contiguous(), dY[rows].contiguous(), R[rows].contiguous()
+        n = x.shape[0]
+        Y, Y2, dX = new(n, N), new(n, N), new(n, K)
+        L.lomo_linear_forward(x, W, Y)
+        L.lomo_linear_forward_residual(x, W, r, Y2)
+        L.lomo_linear_dgrad(d, W, dX)
+        return Y, Y2, dX
+
+    def by_feature(rows):
+        d, w, w2 = dY[:, rows].contiguous(), W[rows].clone(), W[rows].clone()
+        flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+        L.lomo_linear_backward_update(X, d, w, None, 1e-4, 1.0, 1.0)
+        L.lomo_linear_backward_update_clip_value(X, d, w2, None, 1e-4, 1.0, 30.0, flag)
+        return w, w2
+
+    for part, total, size in ((by_token, T, 1), (by_feature, N, 8)):
+        whole = part(slice(0, total))
+        for count in (size, 8, 72, 264, 776, 1544):
+            rows = slice(total - count, total)
+            for k, (a, b) in enumerate(zip(part(rows), whole)):
+                assert torch.equal(a.view(torch.int16), b[rows].view(torch.int16)), (part.__name__, count, k)
