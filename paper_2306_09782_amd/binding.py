@@ -23,7 +23,7 @@ EXPORTED_SYMBOLS = (
     "lomo_linear_dgrad", "lomo_swiglu_backward", "lomo_rmsnorm_backward", "lomo_attention_backward",
     "lomo_linear_forward", "lomo_rmsnorm_forward", "lomo_swiglu_forward", "lomo_rope_forward", "lomo_attention_forward",
     "lomo_cross_entropy", "lomo_embedding_forward", "lomo_linear_forward_residual", "lomo_cross_entropy_mean",
-    "lomo_probe_mfma", "lomo_probe_copy", "lomo_vector_update_static",
+    "lomo_probe_mfma", "lomo_probe_copy", "lomo_vector_update_static", "lomo_contraction_tiles",
 )
 
 
@@ -103,6 +103,7 @@ def load_library():
         "lomo_cross_entropy_mean": (c_int, [P, P, c_double, P, P, P, I64, I64, P]),
         "lomo_probe_mfma": (c_int, [P, I64, c_int, c_int, c_int, P, I64, POINTER(c_double), P]),
         "lomo_probe_copy": (c_int, [P, P, c_size_t, P]),
+        "lomo_contraction_tiles": (c_int, [c_int, POINTER(c_int64), I64, POINTER(c_int32)]),
         "lomo_timing_enable": (c_int, [c_int]),
         "lomo_timing_read": (c_int, [c_int, POINTER(c_double), POINTER(c_int64)]),
     }
@@ -260,6 +261,14 @@ def lomo_timing_read(family: int):
     ms, n = c_double(0.0), c_int64(0)
     _check(load_library().lomo_timing_read(family, ctypes.byref(ms), ctypes.byref(n)))
     return ms.value, n.value
+
+
+def lomo_contraction_tiles(family: int, shapes):
+    """Tile (columns, rows) of each of the linear tensors `shapes` [(T, K, N), ...] in one call of a kernel family."""
+    flat = [int(v) for s in shapes for v in s]
+    arr, out = (c_int64 * max(1, len(flat)))(*flat), (c_int32 * max(1, 2 * len(shapes)))()
+    _check(load_library().lomo_contraction_tiles(family, arr, len(shapes), out))
+    return [(out[2 * i], out[2 * i + 1]) for i in range(len(shapes))]
 
 
 def make_tensor_list(tensors):

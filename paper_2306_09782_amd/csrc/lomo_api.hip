@@ -457,6 +457,27 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
 }
 
+lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles) {
+    if (n < 0) return LOMO_ERR_SHAPE;
+    const bool forward = family == LOMO_KERNEL_FORWARD, dgrad = family == LOMO_KERNEL_DGRAD;
+    if (!forward && !dgrad && family != LOMO_KERNEL_WGRAD_SQNORM && family != LOMO_KERNEL_WGRAD_UPDATE) return LOMO_ERR_SHAPE;
+    if (n > 0 && (!shapes || !tiles)) return LOMO_ERR_NULL;
+    std::vector<GemmArgs> list;
+    for (int64_t i = 0; i < n; ++i) {
+        const int64_t T = shapes[3 * i], K = shapes[3 * i + 1], N = shapes[3 * i + 2];
+        if (T <= 0 || K <= 0 || N <= 0) return LOMO_ERR_SHAPE;
+        GemmArgs a{};
+        a.M = forward ? N : K;
+        a.Nn = forward || dgrad ? T : N;
+        a.C = forward ? K : dgrad ? N : T;
+        list.push_back(a);
+    }
+    std::vector<int> tile_of;
+    choose_tiles(list, forward || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE, tile_of);
+    for (int64_t i = 0; i < n; ++i) tile_size(tile_of[i], tiles + 2 * i, tiles + 2 * i + 1);
+    return LOMO_OK;
+}
+
 lomo_status lomo_linear_dgrad(const lomo_half* dY, const lomo_half* W, lomo_half* dX, int64_t T, int64_t K, int64_t N,
                               void* stream) {
     if (T < 0 || K < 0 || N < 0 || (K & 7) || (N & 7)) return LOMO_ERR_SHAPE;

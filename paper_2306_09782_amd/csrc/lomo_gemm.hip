@@ -239,39 +239,158 @@ static bool fast_enabled() {
 
 // ---- which kernel runs a tensor -----------------------------------------------------------
 // Four shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), and in lomo_gemm_tile.hip 128 x 128, 128 x 64 and
-// 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the 256 CUs and walk the contraction
-// faster.  A tile's time on a CU is a fixed part (ramp-up and epilogue) and a part per contraction index.
-static const double kTileFixed[N_TILES] = {3.0, 2.6, 2.6, 2.6}, kTilePerC[N_TILES] = {0.0275, 0.0098, 0.0053, 0.0042};
-static const int kTileM[N_TILES] = {256, 128, 128, 64}, kTileN[N_TILES] = {256, 128, 64, 64};
-constexpr double kCus = 256.0, kLaunch = 4.0;
+// 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the CUs and walk the contraction faster.
+// The kernels of a pass run one behind the other, so what counts is the sum of their times over the whole list: tensors that
+// would leave most of the chip idle alone fill each other's rounds in the persistent kernel, and one leaves it only where
+// that makes the pass shorter (a long contraction with few tiles).  All kernels give the same bits, so the list a tensor
+// comes in does not show in its result.
+//
+// The times, in microseconds, are fitted to 65 shapes of output (256 x 256 to 11008 x 4096) and contraction (256 to 11008) in
+// each kernel and product: root mean square error 7 to 13 %; choosing by them costs 1 % on average over the best kernel of
+// each.  A tile takes a fixed part (ramp-up and epilogue) and a part per contraction index; the latter is at least `latency`
+// and, with every CU busy, `through` for each tile that a CU has.  Measured at C = 4096, dX (us; in the order above):
+//   1024 x 1024 outputs 65, 41, 34, 17;   4096 x 1024: 70, 36, 46, 55;   4096 x 4096: 118, 132, 166, 222.
+// Lists, measured with all of one shape of tile against the former choice by each tensor alone (dX, us): 7B layers at 1024
+// tokens 1528 against 1960 for four, at 2048 tokens 2647 against 3642; 24 layers of width 1024 at 2048 tokens 1443 against
+// 2077, their updates 1219 against 1826.
+struct TileCost {
+    int m, n, per_cu;             // tile; workgroups that a CU holds
+    double fixed[3];              // by Product
+    double latency, through;
+};
+static const TileCost kTile[N_TILES] = {
+    {256, 256, 1, {7.0, 9.0, 4.8}, 0.0135, 0.0260},
+    {128, 128, 1, {2.8, 4.2, 2.5}, 0.0057, 0.0082},
+    {128, 64, 2, {1.9, 2.9, 3.0}, 0.0043, 0.0055},
+    {64, 64, 2, {1.4, 2.0, 3.0}, 0.0027, 0.0036},
+};
+constexpr double kLaunch = 4.0;          // launch and drain
+constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take one of the two starting choices as it is
 
-static double tiles_of(const GemmArgs& a, int tile) {
-    return (double)((a.M + kTileM[tile] - 1) / kTileM[tile]) * (double)((a.Nn + kTileN[tile] - 1) / kTileN[tile]);
+namespace {
+struct Shape {
+    int64_t M, Nn, C;
+    double count;
+    int tile;
+};
+}  // namespace
+
+// Time of the launches of one tile shape.
+static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int product, double cus) {
+    const TileCost& k = kTile[tile];
+    double tiles = 0.0, indices = 0.0, longest = 0.0;       // indices: contraction indices walked by all tiles together
+    for (size_t i = 0; i < n_shapes; ++i) {
+        const Shape& s = shapes[i];
+        if (s.tile != tile) continue;
+        const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
+        tiles += n;
+        indices += n * (double)s.C;
+        longest = std::max(longest, (double)s.C);
+    }
+    if (tiles == 0.0) return 0.0;
+    const double per_cu = tiles / cus, mean = indices / tiles, f = k.fixed[product];
+    if (tile == TILE_256) {
+        // one round: a tile is faster when it has the memory system to itself.  More: whole rounds
+        if (per_cu <= 1.0) return kLaunch + f + (k.latency + (k.through - k.latency) * per_cu) * longest;
+        return kLaunch + std::max(ceil(per_cu) * (f + k.through * mean), f + k.through * longest);
+    }
+    // a partly filled round costs 0.7 of a full one, or what it has of it
+    const double rounds = std::max(per_cu, floor(per_cu) + (per_cu > floor(per_cu) ? 0.7 : 0.0));
+    const double waves = ceil(per_cu / k.per_cu);
+    return kLaunch + std::max(waves * f + mean * std::max(k.latency * waves, k.through * rounds),
+                              f + longest * std::max(k.latency, 0.7 * k.through));
 }
-static double tile_time(const GemmArgs& a, int tile) { return kTileFixed[tile] + kTilePerC[tile] * (double)a.C; }
 
-// Whole rounds over the chip; a 256 x 256 tile is faster when it
-// has the memory system to itself.
-static double single_time(const GemmArgs& a, int tile) {
-    const double t = tiles_of(a, tile);
-    if (tile == TILE_256 && t < kCus) return kLaunch + kTileFixed[0] + (0.015 + 0.0125 * t / kCus) * (double)a.C;
-    return kLaunch + ceil(t / kCus) * tile_time(a, tile);
+static double pass_time(const std::vector<Shape>& shapes, int product, double cus) {
+    double t = 0.0;
+    for (int tile = 0; tile < N_TILES; ++tile) t += launch_time(shapes.data(), shapes.size(), tile, product, cus);
+    return t;
+}
+
+static int best_alone(Shape one, int product, double cus) {
+    int to = one.tile = TILE_256;
+    double best = launch_time(&one, 1, TILE_256, product, cus);
+    for (one.tile = TILE_128; one.tile < N_TILES; ++one.tile) {
+        const double t = launch_time(&one, 1, one.tile, product, cus);
+        if (t < best) {
+            best = t;
+            to = one.tile;
+        }
+    }
+    return to;
+}
+
+// Two starting choices, all tensors in the persistent kernel and each in the one that is best for it alone; from both, one
+// shape after the other (longest contraction first) moves to where the pass is shortest.
+void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of) {
+    const double cus = (double)cu_count();
+    if (list.size() == 1) {
+        tile_of.assign(1, best_alone({list[0].M, list[0].Nn, list[0].C, 1.0, 0}, product, cus));
+        return;
+    }
+    std::vector<Shape> shapes;
+    std::vector<size_t> shape_of(list.size());
+    for (size_t i = 0; i < list.size(); ++i) {
+        const GemmArgs& a = list[i];
+        size_t k = 0;
+        while (k < shapes.size() && !(shapes[k].M == a.M && shapes[k].Nn == a.Nn && shapes[k].C == a.C)) ++k;
+        if (k == shapes.size()) shapes.push_back({a.M, a.Nn, a.C, 0.0, TILE_256});
+        shapes[k].count += 1.0;
+        shape_of[i] = k;
+    }
+    std::vector<size_t> order(shapes.size());
+    for (size_t k = 0; k < order.size(); ++k) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return shapes[x].C > shapes[y].C; });
+    auto improve = [&](std::vector<Shape>& v) {
+        double best = pass_time(v, product, cus);
+        for (int sweep = 0; sweep < 3 && v.size() <= kGreedyShapes; ++sweep) {
+            bool moved = false;
+            for (size_t k : order) {
+                const int was = v[k].tile;
+                int to = was;
+                for (int tile = 0; tile < N_TILES; ++tile) {
+                    if (tile == was) continue;
+                    v[k].tile = tile;
+                    const double t = pass_time(v, product, cus);
+                    if (t < best) {
+                        best = t;
+                        to = tile;
+                    }
+                }
+                v[k].tile = to;
+                moved |= to != was;
+            }
+            if (!moved) break;
+        }
+        return best;
+    };
+    std::vector<Shape> alone = shapes;
+    for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0}, product, cus);
+    if (shapes.size() == 1 || improve(alone) < improve(shapes)) shapes.swap(alone);
+    tile_of.resize(list.size());
+    for (size_t i = 0; i < list.size(); ++i) tile_of[i] = shapes[shape_of[i]].tile;
+}
+
+void tile_size(int tile, int32_t* m, int32_t* n) {
+    *m = kTile[tile].m;
+    *n = kTile[tile].n;
 }
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st) {
-    std::vector<GemmArgs> by[N_TILES];
+    std::vector<GemmArgs> fit, by[N_TILES];
     for (const GemmArgs& a : list) {
-        if (!fast_enabled() || !dma_eligible<B_STRIDED, A_STRIDED>(a)) {      // beyond 32-bit offsets
-            const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);
-            if (e != hipSuccess) return e;
+        if (fast_enabled() && dma_eligible<B_STRIDED, A_STRIDED>(a)) {
+            fit.push_back(a);
             continue;
         }
-        int best = TILE_256;
-        for (int tile = TILE_128; tile < N_TILES; ++tile)
-            if (single_time(a, tile) < single_time(a, best)) best = tile;
-        by[best].push_back(a);
+        const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);      // beyond 32-bit offsets
+        if (e != hipSuccess) return e;
     }
+    if (fit.empty()) return hipSuccess;
+    std::vector<int> tile_of;
+    choose_tiles(fit, EPI == EPI_SQNORM ? PRODUCT_NORM : EPI == EPI_STORE ? PRODUCT_STORE : PRODUCT_UPDATE, tile_of);
+    for (size_t i = 0; i < fit.size(); ++i) by[tile_of[i]].push_back(fit[i]);
     hipError_t e = hipSuccess;
     if (!by[TILE_256].empty())
         e = launch_dma_group<B_STRIDED, EPI, A_STRIDED>(by[TILE_256].data(), (int)by[TILE_256].size(), st);

@@ -52,6 +52,13 @@ enum { TILE_256, TILE_128, TILE_128_64, TILE_64, N_TILES };
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t st);
 
+int cu_count();      // of the current device; 256 where there is none
+
+// The tile shape of every tensor of a pass (M, Nn and C are read).  Product: what the epilogue does.
+enum Product { PRODUCT_STORE, PRODUCT_UPDATE, PRODUCT_NORM };
+void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of);
+void tile_size(int tile, int32_t* m, int32_t* n);
+
 // Gram route of the norm pass (lomo_gram.hip): ||dY^T X||^2 from X X^T and dY dY^T.  `a` is a norm-pass
 // contraction (A = X, B = dY, C = T).  Costs are in units of one 256 x 256 x 32 slice on one CU.
 bool gram_eligible(const GemmArgs& a);
@@ -61,7 +68,7 @@ hipError_t launch_gram_group(const GemmArgs* list, int n, hipStream_t st);
 // Splits the eligible tensors of `all` between the two routes according to `mode` (LOMO_NORM_*).
 void choose_norm_route(int mode, const std::vector<GemmArgs>& all, std::vector<GemmArgs>& gram, std::vector<GemmArgs>& direct);
 
-// Lists of tensors with the same epilogue, acc, step flag and step size; the kernel of each follows from its shape.
+// Lists of tensors with the same epilogue, acc, step flag and step size; choose_tiles picks the kernels.
 hipError_t launch_wgrad_update(const std::vector<GemmArgs>& list, hipStream_t st);
 hipError_t launch_wgrad_update_clipv(const std::vector<GemmArgs>& list, hipStream_t st);
 hipError_t launch_wgrad_sqnorm(const std::vector<GemmArgs>& list, int norm_route, hipStream_t st);

@@ -104,6 +104,37 @@ def test_lists_of_unequal_tensors(L, T):
         product_ok(dX.cpu().numpy(), d64 @ w64, np.abs(d64) @ np.abs(w64), f"dX {i}")
 
 
+def test_a_list_takes_other_tiles_than_its_tensors_alone(L):
+    """Whole-tile tensors that alone are cut into small tiles share the persistent kernel in a list, the long contraction
+    excepted: same bits, and the list's norm is the sum of the norms."""
+    shapes = [(512, 1024, 1024), (512, 2816, 1024)] * 30 + [(512, 1024, 32000)]
+    fam = {k: L.KERNEL_FAMILIES.index(k) for k in ("dgrad", "wgrad_update", "wgrad_sqnorm")}
+    for f in fam.values():
+        together, alone = L.lomo_contraction_tiles(f, shapes), [L.lomo_contraction_tiles(f, [s])[0] for s in shapes]
+        assert together[0] == (256, 256) and alone[0] != (256, 256)
+    assert L.lomo_contraction_tiles(fam["dgrad"], shapes)[-1] != (256, 256)
+    tensors, alone, total = [], [], 0.0
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    normal = lambda shape, sigma: torch.randn(shape, generator=gen, device=DEV, dtype=torch.float16) * sigma
+    for T, K, N in shapes:
+        t = {"kind": "linear", "X": normal((T, K), 1.0), "dY": normal((T, N), 1.0), "W": normal((N, K), 0.02),
+             "dX": torch.zeros(T, K, dtype=torch.float16, device=DEV)}
+        tensors.append(t)
+        dX, W2, acc = torch.empty_like(t["dX"]), t["W"].clone(), torch.zeros(1, dtype=torch.float64, device=DEV)
+        L.lomo_wgrad_sqnorm(t["X"], t["dY"], acc)
+        L.lomo_linear_backward_update(t["X"], t["dY"], W2, dX, 1e-3, 1.0, 1.0)
+        total += float(acc.item())
+        alone.append((W2, dX))
+    lst = L.make_tensor_list(tensors)
+    ws = torch.empty(max(256, L.lomo_step_workspace_bytes(lst)), dtype=torch.uint8, device=DEV)
+    acc, flags = torch.zeros(1, dtype=torch.float64, device=DEV), torch.zeros(len(shapes) + 1, dtype=torch.int32, device=DEV)
+    L.lomo_step_norm_pass(lst, acc, flags, ws)
+    assert abs(float(acc.item()) / total - 1) < 1e-6 and not flags.any()          # fp32 sums over a tile, fp64 over tiles
+    L.lomo_step_update_pass(lst, 1e-3, 1.0, 1.0, flags[-1:], ws)
+    for i, (t, (W2, dX)) in enumerate(zip(tensors, alone)):
+        assert torch.equal(t["W"].view(torch.int16), W2.view(torch.int16)) and torch.equal(t["dX"].view(torch.int16), dX.view(torch.int16)), i
+
+
 def step_matches_oracle(L, T, K, N):
     """Norm, visible update, dX and the clip-by-value update through the whole-pass calls."""
     Sc = 256.0

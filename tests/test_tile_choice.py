@@ -1,0 +1,45 @@
+"""Which shape of tile the contractions of a call take (host function, no GPU): alone, a tensor of few tiles takes small ones; in
+a list whose tensors fill the chip together, all stay in the persistent kernel, except a long contraction of few tiles."""
+import pytest
+
+import paper_2306_09782_amd as L
+
+UPDATE, NORM, DGRAD, FORWARD = (L.KERNEL_FAMILIES.index(k) for k in ("wgrad_update", "wgrad_sqnorm", "dgrad", "forward"))
+
+
+def layer_stack(H, F, T, layers):
+    return ([(T, F, H), (T, H, F), (T, H, F)] + [(T, H, H)] * 4) * layers
+
+
+@pytest.mark.parametrize("H,F,T,layers", [(4096, 11008, 1024, 4), (4096, 11008, 2048, 2), (4096, 11008, 1024, 32),
+                                          (5120, 13824, 1024, 3), (5120, 13824, 4096, 3), (8192, 22016, 2048, 1),
+                                          (2048, 5504, 2048, 8), (2048, 5504, 1000, 8), (1024, 2816, 512, 24),
+                                          (1024, 2816, 2048, 24), (1024, 2816, 4096, 24)])
+@pytest.mark.parametrize("family", [UPDATE, NORM, DGRAD])
+def test_lists_that_fill_the_chip_stay_together(H, F, T, layers, family):
+    assert set(L.lomo_contraction_tiles(family, layer_stack(H, F, T, layers))) == {(256, 256)}
+
+
+@pytest.mark.parametrize("family,shape", [(UPDATE, (512, 1024, 1024)), (NORM, (512, 1024, 1024)), (DGRAD, (512, 1024, 1024)),
+                                          (FORWARD, (256, 1024, 3072)), (DGRAD, (1024, 4096, 4096)), (DGRAD, (256, 1024, 32000))])
+def test_a_tensor_of_few_tiles_takes_small_ones_alone(family, shape):
+    assert L.lomo_contraction_tiles(family, [shape])[0] != (256, 256)
+
+
+@pytest.mark.parametrize("family,shape", [(UPDATE, (4096, 4096, 11008)), (NORM, (4096, 4096, 4096)), (DGRAD, (4096, 11008, 4096)),
+                                          (FORWARD, (8192, 4096, 12288)), (UPDATE, (1024, 4096, 32000))])
+def test_a_tensor_of_many_tiles_takes_large_ones_alone(family, shape):
+    assert L.lomo_contraction_tiles(family, [shape]) == [(256, 256)]
+
+
+def test_only_the_long_contraction_leaves_a_list():
+    stack = layer_stack(1024, 2816, 512, 24)
+    *rest, vocabulary = L.lomo_contraction_tiles(DGRAD, stack + [(512, 1024, 32000)])
+    assert set(rest) == {(256, 256)} and vocabulary != (256, 256)
+
+
+def test_bad_arguments():
+    assert L.lomo_contraction_tiles(UPDATE, []) == []
+    for family, shape in ((UPDATE, (0, 8, 8)), (L.KERNEL_FAMILIES.index("embedding"), (8, 8, 8))):
+        with pytest.raises(L.LomoError):
+            L.lomo_contraction_tiles(family, [shape])
