@@ -463,6 +463,7 @@ lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n,
     if (!forward && !dgrad && family != LOMO_KERNEL_WGRAD_SQNORM && family != LOMO_KERNEL_WGRAD_UPDATE) return LOMO_ERR_SHAPE;
     if (n > 0 && (!shapes || !tiles)) return LOMO_ERR_NULL;
     std::vector<GemmArgs> list;
+    std::vector<int64_t> at;
     for (int64_t i = 0; i < n; ++i) {
         const int64_t T = shapes[3 * i], K = shapes[3 * i + 1], N = shapes[3 * i + 2];
         if (T <= 0 || K <= 0 || N <= 0) return LOMO_ERR_SHAPE;
@@ -470,11 +471,19 @@ lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n,
         a.M = forward ? N : K;
         a.Nn = forward || dgrad ? T : N;
         a.C = forward ? K : dgrad ? N : T;
+        a.lda = K;
+        a.ldb = forward ? K : N;
+        a.ldo = forward ? N : K;
+        tiles[2 * i] = tiles[2 * i + 1] = 0;
+        if (!(forward ? dma_eligible<false, false>(a) : dgrad ? dma_eligible<false, true>(a) : dma_eligible<true, true>(a))) continue;
+        a.persistent_only = !forward && (dgrad ? beyond_descriptor<false, true>(a) : beyond_descriptor<true, true>(a));
         list.push_back(a);
+        at.push_back(i);
     }
+    if (list.empty()) return LOMO_OK;
     std::vector<int> tile_of;
     choose_tiles(list, forward || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE, tile_of);
-    for (int64_t i = 0; i < n; ++i) tile_size(tile_of[i], tiles + 2 * i, tiles + 2 * i + 1);
+    for (size_t k = 0; k < list.size(); ++k) tile_size(tile_of[k], tiles + 2 * at[k], tiles + 2 * at[k] + 1);
     return LOMO_OK;
 }
 

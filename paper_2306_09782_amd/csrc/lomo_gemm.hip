@@ -1,5 +1,6 @@
 // MFMA contraction kernel of the LOMO hot path for any shape, gfx950 (CDNA4, wave64), and the choice between the kernels.
-// What the direct-to-LDS kernels address with 32-bit offsets goes to them; this one serves what lies beyond.
+// What the direct-to-LDS kernels address with 32-bit offsets goes to them; this one serves rows too long for that (from 7 million
+// elements on).
 //
 // One kernel template serves the three dense steps of a linear tensor:
 //   * fused wgrad + SGD update (paper section 3.2, Algorithm 1: theta <- theta - lr * g, the
@@ -272,6 +273,7 @@ struct Shape {
     int64_t M, Nn, C;
     double count;
     int tile;
+    bool fixed;      // stays in the persistent kernel
 };
 }  // namespace
 
@@ -309,6 +311,7 @@ static double pass_time(const std::vector<Shape>& shapes, int product, double cu
 
 static int best_alone(Shape one, int product, double cus) {
     int to = one.tile = TILE_256;
+    if (one.fixed) return to;
     double best = launch_time(&one, 1, TILE_256, product, cus);
     for (one.tile = TILE_128; one.tile < N_TILES; ++one.tile) {
         const double t = launch_time(&one, 1, one.tile, product, cus);
@@ -325,7 +328,7 @@ static int best_alone(Shape one, int product, double cus) {
 void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of) {
     const double cus = (double)cu_count();
     if (list.size() == 1) {
-        tile_of.assign(1, best_alone({list[0].M, list[0].Nn, list[0].C, 1.0, 0}, product, cus));
+        tile_of.assign(1, best_alone({list[0].M, list[0].Nn, list[0].C, 1.0, 0, list[0].persistent_only}, product, cus));
         return;
     }
     std::vector<Shape> shapes;
@@ -334,7 +337,7 @@ void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<in
         const GemmArgs& a = list[i];
         size_t k = 0;
         while (k < shapes.size() && !(shapes[k].M == a.M && shapes[k].Nn == a.Nn && shapes[k].C == a.C)) ++k;
-        if (k == shapes.size()) shapes.push_back({a.M, a.Nn, a.C, 0.0, TILE_256});
+        if (k == shapes.size()) shapes.push_back({a.M, a.Nn, a.C, 0.0, TILE_256, a.persistent_only});
         shapes[k].count += 1.0;
         shape_of[i] = k;
     }
@@ -346,6 +349,7 @@ void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<in
         for (int sweep = 0; sweep < 3 && v.size() <= kGreedyShapes; ++sweep) {
             bool moved = false;
             for (size_t k : order) {
+                if (v[k].fixed) continue;
                 const int was = v[k].tile;
                 int to = was;
                 for (int tile = 0; tile < N_TILES; ++tile) {
@@ -365,7 +369,7 @@ void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<in
         return best;
     };
     std::vector<Shape> alone = shapes;
-    for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0}, product, cus);
+    for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0, s.fixed}, product, cus);
     if (shapes.size() == 1 || improve(alone) < improve(shapes)) shapes.swap(alone);
     tile_of.resize(list.size());
     for (size_t i = 0; i < list.size(); ++i) tile_of[i] = shapes[shape_of[i]].tile;
@@ -382,6 +386,7 @@ static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st)
     for (const GemmArgs& a : list) {
         if (fast_enabled() && dma_eligible<B_STRIDED, A_STRIDED>(a)) {
             fit.push_back(a);
+            fit.back().persistent_only = beyond_descriptor<B_STRIDED, A_STRIDED>(a);
             continue;
         }
         const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);      // beyond 32-bit offsets

@@ -14,6 +14,9 @@
 // contraction-strided operand end with its range there, the lanes of a contraction-contiguous one are masked (its memory
 // goes on with the next row).  Slices beyond the last one (their number is rounded up to a multiple of four) and the
 // prefetches past the end are out of range as a whole and move no data.
+// A contraction-strided operand may be larger than a descriptor covers (3.5 GiB: the output gradient of a projection to a
+// vocabulary of 32000 from 58 500 tokens on): the descriptor's base then moves on with the walk, once per GiB, in an
+// instantiation of its own.
 // Measured: a 7B layer's step at 2999 tokens 6.36 -> 3.20 ms (567 -> 1138 TFLOP/s; the register-staged kernel of
 // lomo_gemm.hip had every shape that was not whole tiles), at 4096 tokens 4.14 -> 4.13 ms: the descriptors' scalar offsets
 // also take half of the scalar instructions out of the main loop (120 -> 58 per four slices).
@@ -208,9 +211,9 @@ struct RowEpilogue {
 
 // A_STRIDED = false: the A operand is contraction-contiguous as well (forward product Y = X W^T with A = W),
 // fetched and read like the contraction-contiguous B.
-// TAIL: some tensor's contraction ends inside a slice and an operand is contraction-contiguous (the masks cost 0.5 % of the
-// time of the others).
-template <bool B_STRIDED, int EPI, bool A_STRIDED, bool TAIL>
+// EDGE: some tensor's contraction ends inside a slice and an operand is contraction-contiguous, or a contraction-strided operand
+// is larger than a descriptor covers (checking for the former costs 0.5 % of the time of the others).
+template <bool B_STRIDED, int EPI, bool A_STRIDED, bool EDGE>
 __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga) {
     using namespace dma;
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -273,7 +276,11 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     uint32_t a_step = 0, b_step = 0;       // bytes from one slice to the next
     uint32_t a_next = 0, b_next = 0;       // byte offset of the slice to be requested next
     uint32_t a_end = 0, b_end = 0;         // offsets from here on are behind the last slice
-    uint32_t last = 0, tail = 0;           // TAIL: offset of the last slice; this lane's mask there
+    // EDGE only: offset of a contraction-contiguous operand's last slice and this lane's mask there; bytes from a
+    // contraction-strided operand's base to its end, and the slice offset from which on the base moves
+    uint32_t last = 0, tail = 0;
+    int64_t a_left = 0, b_left = 0;
+    uint32_t a_move = ~0u, b_move = ~0u;
     int KT = 0;                            // slices walked: a multiple of 4
 
     // From the last slice of a contraction-contiguous operand on (nothing follows it) the lanes behind the end are masked.
@@ -284,6 +291,16 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     auto mask_b = [&] {
 #pragma unroll
         for (int it = 0; it < 4; ++it) b_voff[it] |= tail;
+    };
+
+    // Puts the base of a strided operand at its next slice.
+    auto move_base = [](int4v& srd, int64_t& left, uint32_t& next, uint32_t& end, uint32_t& move) {
+        left -= next;
+        const uint64_t base = (((uint64_t)(uint32_t)srd[1] << 32) | (uint32_t)srd[0]) + next;
+        srd = make_srd((const void*)base, range_bytes(left / 2));
+        next = 0;
+        end = (uint32_t)srd[2];
+        move = left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
     };
 
     // Locate tile number w of the concatenated list; set up the load state; return its coordinates.
@@ -335,7 +352,15 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         a_next = b_next = 0;
         a_end = A_STRIDED ? (uint32_t)a_srd[2] : (uint32_t)T.C * 2u;
         b_end = B_STRIDED ? (uint32_t)b_srd[2] : (uint32_t)T.C * 2u;
-        if constexpr (TAIL) {
+        if constexpr (EDGE) {
+            if constexpr (A_STRIDED) {
+                a_left = 2 * (a_rows * T.lda - a_org);
+                a_move = a_left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
+            }
+            if constexpr (B_STRIDED) {
+                b_left = 2 * (b_rows * T.ldb - b_org);
+                b_move = b_left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
+            }
             last = (uint32_t)(used - 1) * (BK * 2u);
             // swz_c(16 q + n) = swz_c(n): one mask for all of the lane's rows
             tail = ((lane & 3) ^ swz_c(lane >> 2)) * 8 < T.C - (used - 1) * BK ? 0u : OUTSIDE;
@@ -355,7 +380,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
             dma16(a_voff[it], a_srd, a_next, l);
             if (it == 3) {
                 a_next += a_step;
-                if constexpr (TAIL && !A_STRIDED) {
+                if constexpr (EDGE && !A_STRIDED) {
                     if (__builtin_expect(a_next >= last, 0)) {
                         if (a_next == last) mask_a();
                         else a_next = (uint32_t)a_srd[2];
@@ -368,7 +393,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
             dma16(b_voff[it], b_srd, b_next, l);
             if (it == 3) {
                 b_next += b_step;
-                if constexpr (TAIL && !B_STRIDED) {
+                if constexpr (EDGE && !B_STRIDED) {
                     if (__builtin_expect(b_next >= last, 0)) {
                         if (b_next == last) mask_b();
                         else b_next = (uint32_t)b_srd[2];
@@ -498,6 +523,12 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         // KT is a multiple of 4: the body is unrolled over the four LDS stages so that every LDS
         // address is a register plus an immediate.
         for (int kt = 0; kt < KT; kt += 4) {
+            if constexpr (EDGE && A_STRIDED) {
+                if (__builtin_expect(a_next >= a_move, 0)) move_base(a_srd, a_left, a_next, a_end, a_move);
+            }
+            if constexpr (EDGE && B_STRIDED) {
+                if (__builtin_expect(b_next >= b_move, 0)) move_base(b_srd, b_left, b_next, b_end, b_move);
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 // first half of slice kt+u; reads its second half's fragments; loads the B part of slice kt+u+3
@@ -572,31 +603,36 @@ int cu_count() {
     return n;
 }
 
-// What the kernel's 32-bit offsets and descriptors can address.  A strided operand is addressed from one tile column
-// through all its rows (8 slices more than it has, so that no slice offset wraps around); everything else a tile at a time.
-template <bool B_STRIDED, bool A_STRIDED>
-static bool dma_addressable(const GemmArgs& a) {
-    using namespace dma;
-    const int64_t span = (int64_t)MAX_RANGE / 2;
-    const int64_t c8 = a.C + 8 * BK;
-    return a.M > 0 && a.Nn > 0 && a.C > 0 && a.M < (1 << 30) && a.Nn < (1 << 30) && a.C < (1 << 30) &&
-           (A_STRIDED ? c8 * a.lda < span : (int64_t)BM * a.lda + c8 < span) &&
-           (B_STRIDED ? c8 * a.ldb < span : (int64_t)BN * a.ldb + c8 < span) && (int64_t)BN * a.ldo < span &&
-           ((a.M + BM - 1) / BM) * ((a.Nn + BN - 1) / BN) < (1 << 24);
-}
-
+// What the kernels' 32-bit offsets can address: of a contraction-strided operand the slices requested between two moves of its
+// base (rows of up to 8 million elements), of everything else a tile's rows.
 template <bool B_STRIDED, bool A_STRIDED>
 bool dma_eligible(const GemmArgs& a) {
-    return dma_addressable<B_STRIDED, A_STRIDED>(a);
+    using namespace dma;
+    const int64_t span = (int64_t)MAX_RANGE / 2, run = ((int64_t)MAX_RANGE - (int64_t)MOVE_BASE) / 2;
+    return a.M > 0 && a.Nn > 0 && a.C > 0 && a.M < (1 << 30) && a.Nn < (1 << 30) && a.C < (1 << 30) &&
+           (A_STRIDED ? 5 * BK * a.lda < run : (int64_t)BM * a.lda + a.C + 8 * BK < span) &&
+           (B_STRIDED ? 5 * BK * a.ldb < run : (int64_t)BN * a.ldb + a.C + 8 * BK < span) && (int64_t)BN * a.ldo < span &&
+           ((a.M + BM - 1) / BM) * ((a.Nn + BN - 1) / BN) < (1 << 24);
 }
 template bool dma_eligible<true, true>(const GemmArgs&);
 template bool dma_eligible<false, true>(const GemmArgs&);
 template bool dma_eligible<false, false>(const GemmArgs&);
 
-template <bool B_STRIDED, int EPI, bool A_STRIDED, bool TAIL>
+// A contraction-strided operand is larger than a descriptor covers (8 slices more than it has, so that no slice offset
+// wraps around): the persistent kernel moves its base, the others cannot.
+template <bool B_STRIDED, bool A_STRIDED>
+bool beyond_descriptor(const GemmArgs& a) {
+    const int64_t span = (int64_t)dma::MAX_RANGE / 2, rows = a.C + 8 * dma::BK;
+    return (A_STRIDED && rows * a.lda >= span) || (B_STRIDED && rows * a.ldb >= span);
+}
+template bool beyond_descriptor<true, true>(const GemmArgs&);
+template bool beyond_descriptor<false, true>(const GemmArgs&);
+template bool beyond_descriptor<false, false>(const GemmArgs&);
+
+template <bool B_STRIDED, int EPI, bool A_STRIDED, bool EDGE>
 static hipError_t launch_dma(const GemmArgs* list, int n, hipStream_t st) {
     using namespace dma;
-    auto kern = lomo_contract_dma_kernel<B_STRIDED, EPI, A_STRIDED, TAIL>;
+    auto kern = lomo_contract_dma_kernel<B_STRIDED, EPI, A_STRIDED, EDGE>;
     // thread-safe one-time set-up (initialisation of a function-local static)
     static const hipError_t cfg0 = allow_dynamic_lds(kern, LDS_BYTES);
     if (cfg0 != hipSuccess) return cfg0;
@@ -619,10 +655,9 @@ static hipError_t launch_dma(const GemmArgs* list, int n, hipStream_t st) {
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st) {
-    if constexpr (!A_STRIDED || !B_STRIDED) {
-        for (int i = 0; i < n; ++i)
-            if (list[i].C % dma::BK != 0) return launch_dma<B_STRIDED, EPI, A_STRIDED, true>(list, n, st);
-    }
+    for (int i = 0; i < n; ++i)
+        if (((!A_STRIDED || !B_STRIDED) && list[i].C % dma::BK != 0) || beyond_descriptor<B_STRIDED, A_STRIDED>(list[i]))
+            return launch_dma<B_STRIDED, EPI, A_STRIDED, true>(list, n, st);
     return launch_dma<B_STRIDED, EPI, A_STRIDED, false>(list, n, st);
 }
 

@@ -17,6 +17,7 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 constexpr uint32_t BUFFER_WORD3 = 0x00020000u;
 constexpr uint32_t MAX_RANGE = 0xE0000000u;      // no descriptor covers more than this ...
 constexpr uint32_t OUTSIDE = 0xF0000000u;        // ... so a lane offset with these bits set is outside every one
+constexpr uint32_t MOVE_BASE = 0x40000000u;      // the base of a larger operand moves when its slice offset reaches this
 __device__ __forceinline__ int4v make_srd(const void* base, uint32_t bytes) {
     const uint64_t b = (uint64_t)(uintptr_t)base;
     return int4v{(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xffffu), (int)bytes, (int)BUFFER_WORD3};

@@ -25,6 +25,7 @@ enum Epilogue : int {
 // dgrad: A = W, B = dY (contiguous), Out = dX; M = K_in, Nn = T, C = N_out.
 struct GemmArgs {
     int family;              // LOMO_KERNEL_* of this launch (host side only: timing)
+    bool persistent_only;    // host side only: the small-tile kernels cannot address an operand
     const uint16_t* A;
     const uint16_t* B;
     uint16_t* Out;
@@ -43,6 +44,8 @@ struct GemmArgs {
 // step flag / step size) in as few launches as the argument space allows.
 template <bool B_STRIDED, bool A_STRIDED>
 bool dma_eligible(const GemmArgs& a);
+template <bool B_STRIDED, bool A_STRIDED>
+bool beyond_descriptor(const GemmArgs& a);      // the persistent kernel only
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st);
 
@@ -54,7 +57,7 @@ hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t 
 
 int cu_count();      // of the current device; 256 where there is none
 
-// The tile shape of every tensor of a pass (M, Nn and C are read).  Product: what the epilogue does.
+// The tile shape of every tensor of a pass (M, Nn, C and persistent_only are read).  Product: what the epilogue does.
 enum Product { PRODUCT_STORE, PRODUCT_UPDATE, PRODUCT_NORM };
 void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of);
 void tile_size(int tile, int32_t* m, int32_t* n);

@@ -223,3 +223,51 @@ def test_bits_do_not_depend_on_the_size_of_the_call(L):
             rows = slice(total - count, total)
             for k, (a, b) in enumerate(zip(part(rows), whole)):
                 assert torch.equal(a.view(torch.int16), b[rows].view(torch.int16)), (part.__name__, count, k)
+
+
+# X, dY or W between 2 GiB and the 3.5 GiB that a descriptor covers, and beyond; the last contraction index is not the end of
+# a slice.  (T, K, N)
+@pytest.mark.parametrize("T,K,N", [(41003, 264, 32000), (60003, 264, 32000), (60003, 32008, 264)])
+def test_large_activations(L, T, K, N):
+    """Update and norm: bit for bit those of pieces of the output, whose operands are small, and sampled against 64 bits."""
+    gen = torch.Generator(device=DEV).manual_seed(T + K)
+    X = torch.randn(T, K, generator=gen, device=DEV, dtype=torch.float16)
+    dY = torch.randn(T, N, generator=gen, device=DEV, dtype=torch.float16)
+    W, s = torch.zeros(N, K, device=DEV, dtype=torch.float16), 2.0 ** -5
+    acc, flag = torch.zeros(1, dtype=torch.float64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    L.lomo_wgrad_sqnorm(X, dY, acc, flag)
+    L.lomo_linear_backward_update(X, dY, W, None, s, 1.0, 1.0, flag)
+    assert int(flag.item()) == 0
+    by_rows, step = N > K, 4000
+    total = 0.0
+    for at in range(0, max(N, K), step):
+        cut = slice(at, at + step)
+        x, d, w = (X, dY[:, cut].contiguous(), W[cut]) if by_rows else (X[:, cut].contiguous(), dY, W[:, cut])
+        W2, acc2 = torch.zeros(w.shape, device=DEV, dtype=torch.float16), torch.zeros(1, dtype=torch.float64, device=DEV)
+        L.lomo_linear_backward_update(x, d, W2, None, s, 1.0, 1.0)
+        L.lomo_wgrad_sqnorm(x, d, acc2)
+        total += float(acc2.item())
+        assert torch.equal(W2.view(torch.int16), w.contiguous().view(torch.int16)), at
+    assert abs(float(acc.item()) / total - 1) < 1e-6
+    n, k = [0, 17, N // 2, N - 1], [0, 9, K // 2, K - 1]
+    d, x = dY[:, n].double().cpu().numpy(), X[:, k].double().cpu().numpy()
+    product_ok(W[n][:, k].cpu().numpy(), -s * (d.T @ x), s * (np.abs(d).T @ np.abs(x)), "W")
+    dY[T - 1, N - 1] = np.inf                  # the very last element is still read
+    L.lomo_wgrad_sqnorm(X, dY, acc, flag)
+    assert int(flag.item()) == 1
+
+
+@pytest.mark.parametrize("T,K,N", [(264, 16384, 70008), (264, 16384, 128264)])
+def test_large_weights(L, T, K, N):
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    dY = torch.randn(T, N, generator=gen, device=DEV, dtype=torch.float16)
+    W = torch.randn(N, K, generator=gen, device=DEV, dtype=torch.float16).mul_(0.02)
+    dX = torch.empty(T, K, device=DEV, dtype=torch.float16)
+    L.lomo_linear_dgrad(dY, W, dX)
+    for at in range(0, K, 4096):
+        piece = torch.empty(T, 4096, device=DEV, dtype=torch.float16)
+        L.lomo_linear_dgrad(dY, W[:, at:at + 4096].contiguous(), piece)
+        assert torch.equal(piece.view(torch.int16), dX[:, at:at + 4096].contiguous().view(torch.int16)), at
+    t, k = [0, 100, T - 1], [0, 9, K // 2, K - 1]
+    d, w = dY[t].double().cpu().numpy(), W[:, k].double().cpu().numpy()
+    product_ok(dX[t][:, k].cpu().numpy(), d @ w, np.abs(d) @ np.abs(w), "dX")

@@ -38,6 +38,19 @@ def test_only_the_long_contraction_leaves_a_list():
     assert set(rest) == {(256, 256)} and vocabulary != (256, 256)
 
 
+@pytest.mark.parametrize("family,shape", [(UPDATE, (65536, 4096, 32000)), (NORM, (60000, 264, 32000)), (UPDATE, (60000, 32008, 264)),
+                                          (DGRAD, (264, 16384, 128256)), (FORWARD, (65536, 32000, 8))])
+def test_operands_larger_than_a_descriptor_covers(family, shape):
+    """More than 3.5 GiB of X, dY or W: the persistent kernel, whose descriptors move with the walk."""
+    assert L.lomo_contraction_tiles(family, [shape])[0] == ((256, 256) if family != FORWARD else (64, 64))
+
+
+def test_only_very_long_rows_leave_the_kernels_with_descriptors():
+    for family in (UPDATE, NORM, DGRAD, FORWARD):
+        assert L.lomo_contraction_tiles(family, [(8, 9_000_000, 8)]) == [(0, 0)]
+        assert L.lomo_contraction_tiles(family, [(8, 7_000_000, 8)])[0] != (0, 0)
+
+
 def test_bad_arguments():
     assert L.lomo_contraction_tiles(UPDATE, []) == []
     for family, shape in ((UPDATE, (0, 8, 8)), (L.KERNEL_FAMILIES.index("embedding"), (8, 8, 8))):
