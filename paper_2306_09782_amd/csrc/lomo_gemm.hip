@@ -226,14 +226,11 @@ static hipError_t launch_generic(const GemmArgs& a, hipStream_t st) {
                       : launch_one<128, 128, B_STRIDED, EPI, A_STRIDED>(a, st);
 }
 
-// LOMO_DISABLE_FAST=1 (or LOMO_DISABLE_DMA=1) forces the kernel of this file everywhere (testing aid).
+// LOMO_DISABLE_FAST=1 in the environment of the first call takes every contraction to the kernel of this file (testing aid).
 static bool fast_enabled() {
     static const bool on = [] {
-        for (const char* name : {"LOMO_DISABLE_FAST", "LOMO_DISABLE_DMA"}) {
-            const char* e = getenv(name);
-            if (e && e[0] == '1') return false;
-        }
-        return true;
+        const char* e = getenv("LOMO_DISABLE_FAST");
+        return !(e && e[0] == '1');
     }();
     return on;
 }
