@@ -74,12 +74,17 @@ def test_step_at_tile_and_slice_edges(L, T, K, N):
     step_matches_oracle(L, T, K, N)
 
 
-# Ragged shapes for each kernel a tensor can go to (the small ones above take 64 x 64 tiles): (update, dX) run with
-# tiles of (128 x 64, 128 x 64), (256 x 256, 64 x 64), (256 x 256, 256 x 256), (128 x 128, 128 x 64), (256 x 256, 128 x 128),
-# and a contraction of one index with many tiles
-@pytest.mark.parametrize("T,K,N", [(777, 1544, 1032), (300, 3080, 4104), (3080, 3336, 3848), (904, 1160, 2056), (1016, 2056, 3080),
-                                   (1, 2056, 4104)])
+# Ragged shapes for each kernel a tensor can go to, and a contraction of one index with many tiles
+TILES = {(777, 1544, 1032): ((128, 64), (128, 64), (128, 64)), (300, 3080, 4104): ((256, 256), (64, 64), (256, 256)),
+         (3080, 3336, 3848): ((256, 256), (256, 256), (256, 256)), (904, 1160, 2056): ((128, 128), (128, 64), (128, 128)),
+         (1016, 2056, 3080): ((128, 128), (128, 128), (128, 128)), (1, 2056, 4104): ((128, 64), (64, 64), (256, 256)),
+         (777, 504, 504): ((64, 64), (64, 64), (64, 64))}
+
+
+@pytest.mark.parametrize("T,K,N", TILES)
 def test_step_in_each_tile_shape(L, T, K, N):
+    got = [L.lomo_contraction_tiles(L.KERNEL_FAMILIES.index(f), [(T, K, N)])[0] for f in ("wgrad_update", "dgrad", "wgrad_sqnorm")]
+    assert tuple(got) == TILES[T, K, N], "this shape no longer exercises the kernels it is here for: choose another"
     step_matches_oracle(L, T, K, N)
 
 
@@ -173,7 +178,34 @@ def test_forward_at_tile_and_slice_edges(L, T, K, N, residual):
     product_ok(Y.host(), x @ w.T + r, np.abs(x) @ np.abs(w).T + np.abs(r), "Y")
 
 
-@pytest.mark.parametrize("T,K,N", [(70, 264, 72), (300, 520, 1032), (33, 256, 40)])
+# (T, K, N): tiles of the product, of the product with a residual
+FORWARD_TILES = {(129, 520, 248): ((64, 64), (64, 64)), (264, 1032, 4104): ((128, 64), (128, 64)), (520, 2056, 2056): ((128, 64), (128, 64)),
+                 (504, 1032, 5512): ((128, 128), (128, 128)), (1016, 2056, 3080): ((128, 128), (128, 128)),
+                 (3080, 104, 4104): ((256, 256), (256, 256))}
+
+
+@pytest.mark.parametrize("T,K,N", FORWARD_TILES)
+@pytest.mark.parametrize("residual", ["none", "own buffer", "in place"])
+def test_forward_in_each_tile_shape(L, T, K, N, residual):
+    # the product with a residual has the form and the epilogue of an update of an N x T output over K indices
+    forward, update = L.KERNEL_FAMILIES.index("forward"), L.KERNEL_FAMILIES.index("wgrad_update")
+    got = L.lomo_contraction_tiles(forward, [(T, K, N)])[0], L.lomo_contraction_tiles(update, [(K, N, T)])[0]
+    assert got == FORWARD_TILES[T, K, N], "this shape no longer exercises the kernels it is here for: choose another"
+    X, W, R = f16(14, (T, K), 1.0), f16(15, (N, K), 0.05), f16(16, (T, N), 1.0)
+    Y = Guarded((T, N), R if residual == "in place" else None)
+    if residual == "none":
+        L.lomo_linear_forward(dev(X), dev(W), Y.t)
+    elif residual == "in place":
+        L.lomo_linear_forward(dev(X), dev(W), Y.t, True)
+    else:
+        L.lomo_linear_forward_residual(dev(X), dev(W), dev(R), Y.t)
+    x, w, r = X.astype(np.float64), W.astype(np.float64), 0.0 if residual == "none" else R.astype(np.float64)
+    product_ok(Y.host(), x @ w.T + r, np.abs(x) @ np.abs(w).T + np.abs(r), "Y")
+
+
+# 64 x 64 tiles, then 128 x 64, 128 x 128 and 256 x 256 in both products
+@pytest.mark.parametrize("T,K,N", [(70, 264, 72), (300, 520, 1032), (33, 256, 40), (520, 2056, 2056), (1016, 2056, 3080),
+                                   (3080, 3336, 3848)])
 def test_non_finite_rows_stay_in_their_rows(L, T, K, N):
     """The contraction lengths are not whole slices, so a short slice ends where the next row begins: an infinite row
     must not reach its neighbours' sums (0 * inf), forwards or backwards."""
@@ -217,6 +249,10 @@ def test_bits_do_not_depend_on_the_size_of_the_call(L):
         L.lomo_linear_backward_update_clip_value(X, d, w2, None, 1e-4, 1.0, 30.0, flag)
         return w, w2
 
+    tiles = {part: {L.lomo_contraction_tiles(L.KERNEL_FAMILIES.index(f), [shape(n)])[0] for n in (8, 72, 264, 776, 1544, whole)}
+             for part, f, shape, whole in (("Y", "forward", lambda n: (n, K, N), T), ("dX", "dgrad", lambda n: (n, K, N), T),
+                                           ("W", "wgrad_update", lambda n: (T, K, n), N))}
+    assert tiles["Y"] == {(64, 64), (128, 64), (128, 128), (256, 256)} and len(tiles["dX"]) > 1 and len(tiles["W"]) > 2, tiles
     for part, total, size in ((by_token, T, 1), (by_feature, N, 8)):
         whole = part(slice(0, total))
         for count in (size, 8, 72, 264, 776, 1544):

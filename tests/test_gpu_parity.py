@@ -71,10 +71,10 @@ LINEAR_SHAPES = [
     (33, 8, 8),            # one partial tile
     (1, 520, 1032),        # a single token: rank-one gradient
     (300, 776, 392),
-    (70, 3600, 3320),      # 15 x 13 tiles of 256 x 256, ragged tails
+    (70, 3600, 3320),      # 15 x 13 tiles of 256 x 256, ragged tails, three slices of 32 in a round of four
     (64, 4096, 4096),      # 256 full 256 x 256 tiles
-    # edges of the persistent 256 x 256 x 32 kernels: the shortest contraction they take (one round of their four
-    # stages) and an odd number of rounds, the smallest tile count they take (192), for the weight gradient ...
+    # the persistent 256 x 256 x 32 kernel: one whole round of its four stages, an odd number of rounds, 192 and 256 whole
+    # tiles, for the weight gradient ...
     (128, 4096, 4096),
     (384, 3072, 4096),
     # ... and for dgrad (tokens are the tile rows there, N is contracted)
@@ -125,8 +125,8 @@ def test_linear_sqnorm_update_dgrad(L, T, K, N):
 
 
 def _random_linear_shapes():
-    """Seeded shapes around the boundaries between the three contraction kernels: ragged ones for the guarded kernel,
-    multiples of 128 for the whole-tile kernel, and a few with 256-multiples and token counts next to a multiple of 64."""
+    """Seeded shapes of up to a thousand features: ragged ones, multiples of 128, and a few with 256-multiples and token counts
+    next to a multiple of 64 (which of the kernels' edges they meet depends on the choice of the tile)."""
     rng = np.random.default_rng(20240611)
     shapes = []
     for _ in range(10):
