@@ -21,7 +21,7 @@
  *     changes a result between calls (what it does keep: the event pool of lomo_timing_*, one-time
  *     kernel attributes, the fixed scratch array of lomo_vector_update_static, described with that
  *     call, and a 16 KB array of counters through which the workgroups of the fused update kernel
- *     keep in step, cleared before every such launch: it affects timing only).  Every choice that
+ *     keep in step, cleared before every launch that uses it: it affects timing only).  Every choice that
  *     changes how a result is computed is an argument.  Calls
  *     launch on `stream` (a hipStream_t, NULL = default stream) and never synchronise.  `acc` and
  *     `overflow_flag` are zeroed by the caller before pass 1.

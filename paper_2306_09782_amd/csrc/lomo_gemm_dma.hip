@@ -54,7 +54,7 @@ constexpr int LDS_BYTES = NS * STAGE_HALVES * 2 + 8 * EPI_UNIT_HALVES * 2;
 // before its last reader asks for it (measured on the 7B stack: 22 GiB fetched per launch instead of 15.6).  Every
 // workgroup that has finished the main loop of a round adds one to the counter of (next round, XCD) and, before it
 // enters the next main loop, waits a bounded time until the others of its XCD have done so.  The counters are cleared
-// by a small kernel in front of every launch.  Launches that overlap on one GPU share them: a workgroup may then
+// by a small kernel in front of every launch of more than one round.  Launches that overlap on one GPU share them: a workgroup may then
 // wait less, or up to the bound once (after which it stops waiting), never for ever.
 constexpr int SYNC_ROUNDS = 512;        // rounds beyond this run free
 constexpr int SYNC_POLLS = 24;          // x 2048 clocks: the longest wait, about 30 us
@@ -642,7 +642,8 @@ static hipError_t launch_dma(const GemmArgs* list, int n, hipStream_t st) {
         fill_group(ga, list + first, cnt, BM, BN);
         const int tiles = ga.total_tiles;
         const int grid = tiles < cu_count() ? tiles : cu_count();
-        if ((EPI == EPI_UPDATE || EPI == EPI_CLIPV) && A_STRIDED && B_STRIDED) {     // the kernels that align their rounds
+        // the kernels that align their rounds; a single round reads no counter
+        if ((EPI == EPI_UPDATE || EPI == EPI_CLIPV) && A_STRIDED && B_STRIDED && tiles > grid) {
             int rounds = (tiles + grid - 1) / grid;
             if (rounds > SYNC_ROUNDS) rounds = SYNC_ROUNDS;
             hipLaunchKernelGGL(clear_round_counters, dim3((unsigned)((rounds * 8 + 255) / 256)), dim3(256), 0, st, rounds);
