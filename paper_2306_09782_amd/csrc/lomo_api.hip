@@ -5,6 +5,7 @@
 
 #include <math.h>
 
+#include <new>
 #include <vector>
 
 using namespace lomo;
@@ -56,7 +57,7 @@ lomo_status lomo_wgrad_sqnorm_route(const lomo_half* X, const lomo_half* dY, int
     a.lda = K; a.ldb = N; a.ldo = K;
     a.acc = acc; a.flag_out = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_SQNORM;
-    return from_hip(launch_wgrad_sqnorm({a}, norm_algorithm, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_wgrad_sqnorm(&a, 1, norm_algorithm, static_cast<hipStream_t>(stream)));
 }
 
 lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY, lomo_half* W, lomo_half* dX, int64_t T,
@@ -75,7 +76,7 @@ lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY,
         d.M = K; d.Nn = T; d.C = N;
         d.lda = K; d.ldb = N; d.ldo = K;
         d.family = LOMO_KERNEL_DGRAD;
-        hipError_t e = launch_dgrad({d}, st);
+        hipError_t e = launch_dgrad(&d, 1, st);
         if (e != hipSuccess) return LOMO_ERR_LAUNCH;
     }
     GemmArgs a{};
@@ -85,7 +86,7 @@ lomo_status lomo_linear_backward_update(const lomo_half* X, const lomo_half* dY,
     a.s = step_size(lr, inv_loss_scale, clip_coef);
     a.flag_in = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_UPDATE;
-    return from_hip(launch_wgrad_update({a}, st));
+    return from_hip(launch_wgrad_update(&a, 1, st));
 }
 
 size_t lomo_embedding_workspace_bytes(int64_t T, int64_t H) { return embedding_ws_bytes(T, H); }
@@ -330,7 +331,7 @@ lomo_status lomo_step_norm_pass(const lomo_tensor* tensors, int64_t n, double* a
         a.family = LOMO_KERNEL_WGRAD_SQNORM;
         norms.push_back(a);
     }
-    if (launch_wgrad_sqnorm(norms, route, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+    if (launch_wgrad_sqnorm(norms.data(), norms.size(), route, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     cs = run_row_kernels(tensors, n, ws, ws_bytes, 0, 0.f, nullptr, acc, flags, nullptr, 0.f, 0.f, false, st);
     if (cs != LOMO_OK) return cs;
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
@@ -364,7 +365,9 @@ static lomo_status update_pass(const lomo_tensor* tensors, int64_t n, float s, c
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
         updates.push_back(a);
     }
-    if (launch_dgrad(dgrads, st) != hipSuccess || launch_wgrad_update(updates, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+    if (launch_dgrad(dgrads.data(), dgrads.size(), st) != hipSuccess ||
+        launch_wgrad_update(updates.data(), updates.size(), st) != hipSuccess)
+        return LOMO_ERR_LAUNCH;
     return run_row_kernels(tensors, n, ws, ws_bytes, 1, s, s_dev, nullptr, nullptr, step_flag, 0.f, 0.f,
                            options != nullptr && options->reuse_grouping != 0, st);
 }
@@ -411,7 +414,7 @@ lomo_status lomo_linear_backward_update_clip_value(const lomo_half* X, const lom
         d.M = K; d.Nn = T; d.C = N;
         d.lda = K; d.ldb = N; d.ldo = K;
         d.family = LOMO_KERNEL_DGRAD;
-        if (launch_dgrad({d}, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+        if (launch_dgrad(&d, 1, st) != hipSuccess) return LOMO_ERR_LAUNCH;
     }
     GemmArgs a{};
     a.A = X; a.B = dY; a.Out = W;
@@ -420,7 +423,7 @@ lomo_status lomo_linear_backward_update_clip_value(const lomo_half* X, const lom
     a.lr = lr; a.inv_s = inv_loss_scale; a.clipv = clip_value;
     a.flag_out = overflow_flag;
     a.family = LOMO_KERNEL_WGRAD_UPDATE;
-    return from_hip(launch_wgrad_update_clipv({a}, st));
+    return from_hip(launch_wgrad_update_clipv(&a, 1, st));
 }
 
 lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t n, float lr, float inv_loss_scale,
@@ -451,13 +454,15 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
         a.family = LOMO_KERNEL_WGRAD_UPDATE;
         updates.push_back(a);
     }
-    if (launch_dgrad(dgrads, st) != hipSuccess || launch_wgrad_update_clipv(updates, st) != hipSuccess) return LOMO_ERR_LAUNCH;
+    if (launch_dgrad(dgrads.data(), dgrads.size(), st) != hipSuccess ||
+        launch_wgrad_update_clipv(updates.data(), updates.size(), st) != hipSuccess)
+        return LOMO_ERR_LAUNCH;
     cs = run_row_kernels(tensors, n, ws, ws_bytes, 2, inv_loss_scale, nullptr, nullptr, flags, nullptr, lr, clip_value, false, st);
     if (cs != LOMO_OK) return cs;
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
 }
 
-lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles) {
+lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles) try {
     if (n < 0) return LOMO_ERR_SHAPE;
     const bool forward = family == LOMO_KERNEL_FORWARD, dgrad = family == LOMO_KERNEL_DGRAD;
     if (!forward && !dgrad && family != LOMO_KERNEL_WGRAD_SQNORM && family != LOMO_KERNEL_WGRAD_UPDATE) return LOMO_ERR_SHAPE;
@@ -480,11 +485,13 @@ lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n,
         list.push_back(a);
         at.push_back(i);
     }
-    if (list.empty()) return LOMO_OK;
-    std::vector<int> tile_of;
-    choose_tiles(list, forward || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE, tile_of);
+    std::vector<int> tile_of(list.size());
+    const int product = forward || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE;
+    choose_tiles(list.data(), list.size(), product, tile_of.data());
     for (size_t k = 0; k < list.size(); ++k) tile_size(tile_of[k], tiles + 2 * at[k], tiles + 2 * at[k] + 1);
     return LOMO_OK;
+} catch (const std::bad_alloc&) {
+    return LOMO_ERR_LAUNCH;
 }
 
 lomo_status lomo_linear_dgrad(const lomo_half* dY, const lomo_half* W, lomo_half* dX, int64_t T, int64_t K, int64_t N,
@@ -500,7 +507,7 @@ lomo_status lomo_linear_dgrad(const lomo_half* dY, const lomo_half* W, lomo_half
     d.M = K; d.Nn = T; d.C = N;
     d.lda = K; d.ldb = N; d.ldo = K;
     d.family = LOMO_KERNEL_DGRAD;
-    return from_hip(launch_dgrad({d}, static_cast<hipStream_t>(stream)));
+    return from_hip(launch_dgrad(&d, 1, static_cast<hipStream_t>(stream)));
 }
 
 lomo_status lomo_linear_forward(const lomo_half* X, const lomo_half* W, lomo_half* Y, int64_t T, int64_t K, int64_t N,

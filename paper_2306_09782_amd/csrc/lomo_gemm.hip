@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <new>
 
 namespace lomo {
 
@@ -322,15 +323,11 @@ static int best_alone(Shape one, int product, double cus) {
 
 // Two starting choices, all tensors in the persistent kernel and each in the one that is best for it alone; from both, one
 // shape after the other (longest contraction first) moves to where the pass is shortest.
-void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of) {
+void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     const double cus = (double)cu_count();
-    if (list.size() == 1) {
-        tile_of.assign(1, best_alone({list[0].M, list[0].Nn, list[0].C, 1.0, 0, list[0].persistent_only}, product, cus));
-        return;
-    }
     std::vector<Shape> shapes;
-    std::vector<size_t> shape_of(list.size());
-    for (size_t i = 0; i < list.size(); ++i) {
+    std::vector<size_t> shape_of(n);
+    for (size_t i = 0; i < n; ++i) {
         const GemmArgs& a = list[i];
         size_t k = 0;
         while (k < shapes.size() && !(shapes[k].M == a.M && shapes[k].Nn == a.Nn && shapes[k].C == a.C)) ++k;
@@ -368,8 +365,7 @@ void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<in
     std::vector<Shape> alone = shapes;
     for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0, s.fixed}, product, cus);
     if (shapes.size() == 1 || improve(alone) < improve(shapes)) shapes.swap(alone);
-    tile_of.resize(list.size());
-    for (size_t i = 0; i < list.size(); ++i) tile_of[i] = shapes[shape_of[i]].tile;
+    for (size_t i = 0; i < n; ++i) tile_of[i] = shapes[shape_of[i]].tile;
 }
 
 void tile_size(int tile, int32_t* m, int32_t* n) {
@@ -378,56 +374,72 @@ void tile_size(int tile, int32_t* m, int32_t* n) {
 }
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
-static hipError_t launch_list(const std::vector<GemmArgs>& list, hipStream_t st) {
-    std::vector<GemmArgs> fit, by[N_TILES];
-    for (const GemmArgs& a : list) {
-        if (fast_enabled() && dma_eligible<B_STRIDED, A_STRIDED>(a)) {
-            fit.push_back(a);
-            fit.back().persistent_only = beyond_descriptor<B_STRIDED, A_STRIDED>(a);
-            continue;
-        }
-        const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(a, st);      // beyond 32-bit offsets
-        if (e != hipSuccess) return e;
-    }
-    if (fit.empty()) return hipSuccess;
-    std::vector<int> tile_of;
-    choose_tiles(fit, EPI == EPI_SQNORM ? PRODUCT_NORM : EPI == EPI_STORE ? PRODUCT_STORE : PRODUCT_UPDATE, tile_of);
-    for (size_t i = 0; i < fit.size(); ++i) by[tile_of[i]].push_back(fit[i]);
-    hipError_t e = hipSuccess;
-    if (!by[TILE_256].empty())
-        e = launch_dma_group<B_STRIDED, EPI, A_STRIDED>(by[TILE_256].data(), (int)by[TILE_256].size(), st);
-    for (int tile = TILE_128; tile < N_TILES && e == hipSuccess; ++tile) {
-        if (by[tile].empty()) continue;
-        // workgroups start in list order: the longest walks first
-        std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
-        e = launch_tile_group<B_STRIDED, EPI, A_STRIDED>(by[tile].data(), (int)by[tile].size(), tile, st);
-    }
-    return e;
+static hipError_t launch_with(int tile, const GemmArgs* list, size_t n, hipStream_t st) {
+    return tile == TILE_256 ? launch_dma_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, st)
+                            : launch_tile_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, tile, st);
 }
 
-hipError_t launch_wgrad_update(const std::vector<GemmArgs>& list, hipStream_t st) {
-    return launch_list<true, EPI_UPDATE, true>(list, st);
+// A list of one allocates no host memory; for longer ones a failed allocation is an error code like a refused launch.
+template <bool B_STRIDED, int EPI, bool A_STRIDED>
+static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) try {
+    constexpr int product = EPI == EPI_SQNORM ? PRODUCT_NORM : EPI == EPI_STORE ? PRODUCT_STORE : PRODUCT_UPDATE;
+    auto any_shape = [](const GemmArgs& a) { return !fast_enabled() || !dma_eligible<B_STRIDED, A_STRIDED>(a); };
+    if (n == 1) {
+        if (any_shape(*list)) return launch_generic<B_STRIDED, EPI, A_STRIDED>(*list, st);
+        const Shape s{list->M, list->Nn, list->C, 1.0, TILE_256, beyond_descriptor<B_STRIDED, A_STRIDED>(*list)};
+        return launch_with<B_STRIDED, EPI, A_STRIDED>(best_alone(s, product, (double)cu_count()), list, 1, st);
+    }
+    std::vector<GemmArgs> fit, by[N_TILES];
+    for (size_t i = 0; i < n; ++i) {
+        if (any_shape(list[i])) {
+            const hipError_t e = launch_generic<B_STRIDED, EPI, A_STRIDED>(list[i], st);
+            if (e != hipSuccess) return e;
+        } else {
+            fit.push_back(list[i]);
+            fit.back().persistent_only = beyond_descriptor<B_STRIDED, A_STRIDED>(list[i]);
+        }
+    }
+    std::vector<int> tile_of(fit.size());
+    choose_tiles(fit.data(), fit.size(), product, tile_of.data());
+    for (size_t i = 0; i < fit.size(); ++i) by[tile_of[i]].push_back(fit[i]);
+    for (int tile = 0; tile < N_TILES; ++tile) {
+        if (by[tile].empty()) continue;
+        // workgroups of the small tiles start in list order: the longest walks first
+        if (tile != TILE_256)
+            std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
+        const hipError_t e = launch_with<B_STRIDED, EPI, A_STRIDED>(tile, by[tile].data(), by[tile].size(), st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+} catch (const std::bad_alloc&) {
+    return hipErrorOutOfMemory;
 }
-hipError_t launch_wgrad_update_clipv(const std::vector<GemmArgs>& list, hipStream_t st) {
-    return launch_list<true, EPI_CLIPV, true>(list, st);
+
+hipError_t launch_wgrad_update(const GemmArgs* list, size_t n, hipStream_t st) {
+    return launch_list<true, EPI_UPDATE, true>(list, n, st);
 }
-hipError_t launch_wgrad_sqnorm(const std::vector<GemmArgs>& list, int norm_route, hipStream_t st) {
-    if (norm_route == LOMO_NORM_DIRECT || !fast_enabled()) return launch_list<true, EPI_SQNORM, true>(list, st);
+hipError_t launch_wgrad_update_clipv(const GemmArgs* list, size_t n, hipStream_t st) {
+    return launch_list<true, EPI_CLIPV, true>(list, n, st);
+}
+hipError_t launch_wgrad_sqnorm(const GemmArgs* list, size_t n, int norm_route, hipStream_t st) try {
+    if (norm_route == LOMO_NORM_DIRECT || !fast_enabled()) return launch_list<true, EPI_SQNORM, true>(list, n, st);
     std::vector<GemmArgs> gram, direct;
-    choose_norm_route(norm_route, list, gram, direct);
+    choose_norm_route(norm_route, std::vector<GemmArgs>(list, list + n), gram, direct);
     if (!gram.empty()) {
         const hipError_t e = launch_gram_group(gram.data(), (int)gram.size(), st);
         if (e != hipSuccess) return e;
     }
-    return launch_list<true, EPI_SQNORM, true>(direct, st);
+    return launch_list<true, EPI_SQNORM, true>(direct.data(), direct.size(), st);
+} catch (const std::bad_alloc&) {
+    return hipErrorOutOfMemory;
 }
-hipError_t launch_dgrad(const std::vector<GemmArgs>& list, hipStream_t st) {
-    return launch_list<false, EPI_STORE, true>(list, st);
+hipError_t launch_dgrad(const GemmArgs* list, size_t n, hipStream_t st) {
+    return launch_list<false, EPI_STORE, true>(list, n, st);
 }
 
 // Y = X W^T (EPI_STORE) or Y <- Y + X W^T rounded once (EPI_UPDATE with s = -1: the residual connection).
 hipError_t launch_forward(const GemmArgs& a, bool accumulate, hipStream_t st) {
-    return accumulate ? launch_list<false, EPI_UPDATE, false>({a}, st) : launch_list<false, EPI_STORE, false>({a}, st);
+    return accumulate ? launch_list<false, EPI_UPDATE, false>(&a, 1, st) : launch_list<false, EPI_STORE, false>(&a, 1, st);
 }
 
 }  // namespace lomo

@@ -59,7 +59,7 @@ int cu_count();      // of the current device; 256 where there is none
 
 // The tile shape of every tensor of a pass (M, Nn, C and persistent_only are read).  Product: what the epilogue does.
 enum Product { PRODUCT_STORE, PRODUCT_UPDATE, PRODUCT_NORM };
-void choose_tiles(const std::vector<GemmArgs>& list, int product, std::vector<int>& tile_of);
+void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of);
 void tile_size(int tile, int32_t* m, int32_t* n);
 
 // Gram route of the norm pass (lomo_gram.hip): ||dY^T X||^2 from X X^T and dY dY^T.  `a` is a norm-pass
@@ -72,10 +72,10 @@ hipError_t launch_gram_group(const GemmArgs* list, int n, hipStream_t st);
 void choose_norm_route(int mode, const std::vector<GemmArgs>& all, std::vector<GemmArgs>& gram, std::vector<GemmArgs>& direct);
 
 // Lists of tensors with the same epilogue, acc, step flag and step size; choose_tiles picks the kernels.
-hipError_t launch_wgrad_update(const std::vector<GemmArgs>& list, hipStream_t st);
-hipError_t launch_wgrad_update_clipv(const std::vector<GemmArgs>& list, hipStream_t st);
-hipError_t launch_wgrad_sqnorm(const std::vector<GemmArgs>& list, int norm_route, hipStream_t st);
-hipError_t launch_dgrad(const std::vector<GemmArgs>& list, hipStream_t st);
+hipError_t launch_wgrad_update(const GemmArgs* list, size_t n, hipStream_t st);
+hipError_t launch_wgrad_update_clipv(const GemmArgs* list, size_t n, hipStream_t st);
+hipError_t launch_wgrad_sqnorm(const GemmArgs* list, size_t n, int norm_route, hipStream_t st);
+hipError_t launch_dgrad(const GemmArgs* list, size_t n, hipStream_t st);
 // A = W [M = N_out x C = K_in], B = X [Nn = T x C], Out = Y [T x N_out]; accumulate: Y <- rne16(Y + acc).
 hipError_t launch_forward(const GemmArgs& a, bool accumulate, hipStream_t st);
 
