@@ -497,7 +497,7 @@ def main():
         whole = args.workload == wl.name and not args.per_tensor_calls and not args.no_dgrad
         traffic, traffic_src = profiled_traffic(wl.name) if whole else (None, None)
         algorithmic_bytes = sum(2 * s.T * (s.N + s.K) + 4 * s.N * s.K for s in wl.tensors if s.kind == "linear")
-        roofline = {"kernel": "fused wgrad + SGD update (lomo_contract_dma_kernel<true, EPI_UPDATE>)", "bound": "mfma",
+        roofline = {"kernel": "fused wgrad + SGD update (lomo_contract_dma_kernel<EPI_UPDATE>)", "bound": "mfma",
                     "achieved": k1["tflops"], "peak": PEAK_FP16_TFLOPS, "unit": "TFLOP/s",
                     "frac": k1["tflops"] / PEAK_FP16_TFLOPS, "traffic": traffic, "traffic_source": traffic_src,
                     "flops_per_launch": main_rec["flops_per_pass"] * args.steps / k1["launches"],

@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "liblomo.so")
 OBJ_DIR = os.path.join(ROOT, "_build", "lomo")
-SOURCES = ["lomo_api.hip", "lomo_gemm.hip", "lomo_gemm_dma.hip", "lomo_gemm_tile.hip", "lomo_gram.hip", "lomo_chain.hip",
+SOURCES = ["lomo_api.hip", "lomo_gemm.hip", "lomo_gemm_dma.hip", "lomo_gemm_wide.hip", "lomo_gemm_tile.hip", "lomo_gram.hip", "lomo_chain.hip",
            "lomo_attention.hip", "lomo_attention_fwd.hip", "lomo_forward.hip", "lomo_rowops.hip", "lomo_timing.hip",
            "lomo_ceiling.hip", "lomo_static.hip"]
 

@@ -375,8 +375,9 @@ void tile_size(int tile, int32_t* m, int32_t* n) {
 
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_with(int tile, const GemmArgs* list, size_t n, hipStream_t st) {
-    return tile == TILE_256 ? launch_dma_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, st)
-                            : launch_tile_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, tile, st);
+    if (tile != TILE_256) return launch_tile_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, tile, st);
+    if constexpr (B_STRIDED) return launch_dma_group<EPI>(list, (int)n, st);
+    else return launch_wide_group<EPI, A_STRIDED>(list, (int)n, st);
 }
 
 // A list of one allocates no host memory; for longer ones a failed allocation is an error code like a refused launch.

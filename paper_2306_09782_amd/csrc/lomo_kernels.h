@@ -40,14 +40,17 @@ struct GemmArgs {
     const int32_t* flag_in;  // overflow flag to honour (EPI_UPDATE), may be null
 };
 
-// Persistent 256 x 256 direct-to-LDS kernel (lomo_gemm_dma.hip): runs a list of eligible tensors (same epilogue, same acc /
-// step flag / step size) in as few launches as the argument space allows.
+// Persistent 256 x 256 direct-to-LDS kernels: run a list of eligible tensors (same epilogue, same acc / step flag / step size)
+// in as few launches as the argument space allows.  Both operands contraction-strided (lomo_gemm_dma.hip): norm and updates;
+// B or both contraction-contiguous (lomo_gemm_wide.hip): dgrad and forward.
 template <bool B_STRIDED, bool A_STRIDED>
 bool dma_eligible(const GemmArgs& a);
 template <bool B_STRIDED, bool A_STRIDED>
-bool beyond_descriptor(const GemmArgs& a);      // the persistent kernel only
-template <bool B_STRIDED, int EPI, bool A_STRIDED>
+bool beyond_descriptor(const GemmArgs& a);      // the persistent kernels only
+template <int EPI>
 hipError_t launch_dma_group(const GemmArgs* list, int n, hipStream_t st);
+template <int EPI, bool A_STRIDED>
+hipError_t launch_wide_group(const GemmArgs* list, int n, hipStream_t st);
 
 // Kernel of smaller tiles (lomo_gemm_tile.hip), one workgroup per tile; takes lists and shapes as the persistent kernel does and
 // gives the same bits.  Tiles are (m) x (n) as in GemmArgs.
