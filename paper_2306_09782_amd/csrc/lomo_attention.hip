@@ -11,320 +11,341 @@
 // fp16 storage, fp32 accumulation on the MFMA units; P and dS pass through fp16 before the products that
 // consume them (fp16 training holds them as fp16 tensors); dq, dk, dv are rounded once, after the rotation.
 //
-// Two deterministic kernels, no atomics: one workgroup per (sequence, head, block of 64 keys) walks the query
-// blocks at or below it and accumulates dk, dv; one per (sequence, head, block of 64 queries) walks the key
-// blocks up to it and accumulates dq.  Both recompute S, P, dP, dS per 64 x 64 block (32x32x16 MFMA, four
-// waves in 2 x 2); the loop operand of the next block is fetched into registers while the current one is
-// multiplied.  Transposed operands come from LDS through ds_read_b64_tr_b16.
+// Two deterministic kernels, no atomics.  The first: a workgroup per (sequence, head, block of queries) forms delta, walks
+// the key blocks up to the diagonal and accumulates dq.  The second: a workgroup per (sequence, head, block of keys) walks
+// the query blocks from the diagonal on and accumulates dk, dv.  Both recompute S, P, dP, dS, in blocks of 32 x 32 per
+// wave that lie with the wave's own rows along the lanes (see lomo_attention_common.h): rotary pairs, P and dS never leave the
+// lane pair that made them.
+//
+// Measured, us, against the kernels before (64 x 64 blocks over four waves, P and dS through LDS, tiles through registers, delta
+// by a kernel of its own): 1 x 8192 tokens, 32 heads 2545 -> 1945 (706 TFLOP/s of the five products, 988 of the seven executed);
+// 8 x 1024, 40 heads 668 -> 554; 8 x 512, 32 heads 170 -> 140; 1 x 1024 93 -> 79; 3 x 320 41 -> 41.  At 8192 tokens the matrix pipes are
+// 53 % (dq) and 49 % (dk, dv) busy at 1.85 GHz.  A quarter fewer vector instructions (scales folded into lse and delta)
+// gave 1 %.
 #include "lomo_attention_common.h"
 
 namespace lomo {
 
 namespace attn {
 
+constexpr int BWD_LDS_BYTES = LDS_BYTES + 2 * 2 * BLK * 4;      // + lse and delta of a pair's queries
+
 struct Args {
     const uint16_t* qkv;   // [T x 3H]
     const uint16_t* o;     // [T x H]
     const uint16_t* dO;    // [T x H]
     const float* lse;      // [T x nh]
-    const float* delta;    // [T x nh]
+    float* delta;          // [T x nh], written by the dq kernel
     const float* cosv;     // [s x 64] or null
     const float* sinv;
     uint16_t* dqkv;        // [T x 3H]
     int s, nh, H;
 };
 
-}  // namespace attn
-
-// delta[t][n] = sum_c dO[t][128 n + c] * o[t][128 n + c]: sixteen lanes per (token, head), eight columns each.
-__global__ __launch_bounds__(256) void attention_delta_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dO,
-                                                              float* __restrict__ delta, int64_t rows) {
-    const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);     // row = t * nh + n
-    const int part = threadIdx.x & 15;
-    float sum = 0.f;
-    if (row < rows) {
-        const half8 a = *reinterpret_cast<const half8*>(o + row * attn::D + part * 8);
-        const half8 b = *reinterpret_cast<const half8*>(dO + row * attn::D + part * 8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sum = fmaf((float)a[e], (float)b[e], sum);
-    }
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (row < rows && part == 0) delta[row] = sum;
-}
-
-// MODE 0: workgroup = (key block j, head, sequence): dk, dv.  MODE 1: workgroup = (query block i, head, sequence): dq.
-template <int MODE>
-__global__ __launch_bounds__(256, 2) void attention_backward_kernel(attn::Args a) {
-    using namespace attn;
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    // Two [64 x 128] tiles for the operand pair that moves with the loop (MODE 0: Q_i and dO_i; MODE 1: K_j and
-    // V_j); the pair that stays is held as MFMA fragments in registers.  Less LDS, two workgroups per CU.
-    uint16_t* sA = smem;
-    uint16_t* sB = sA + TILE;
-    uint16_t* sP = sB + TILE;
-    uint16_t* sDS = sP + BLK * PS;
-    float* sL = reinterpret_cast<float*>(sDS + BLK * PS);
-    float* sDelta = sL + BLK;
-    float* sOut = reinterpret_cast<float*>(smem);     // [64 x PO] fp32, after the loop (over both tiles and into sP)
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave & 1, wc = wave >> 1;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int g4 = lane >> 4, j16 = lane & 15;
-    const int mhalf = g4 & 1, kh = g4 >> 1, rib = j16 >> 2, piece = j16 & 3;
-    const int tr_row = 8 * kh + rib, tr_col = 16 * mhalf + 4 * piece;
-    // swizzles of the rows a transposing read touches in the big tiles: rows 16 ks + tr_row and + 4
-    const int tr_sw0 = ((rib << 2) | (2 * kh)) << 3, tr_sw1 = ((rib << 2) | (2 * kh + 1)) << 3;
-
-    // Workgroups are dealt to the 8 XCDs round-robin; give each XCD a contiguous run of (sequence, head) pairs so
-    // that the blocks of one head, which re-read the same q, k, v, dO rows, meet in one L2.
-    const int nb = a.s / BLK;
-    int pos;
-    {
-        const int G = gridDim.x, x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
-        const int q = G >> 3, r = G & 7;
-        pos = x * q + (x < r ? x : r) + local;
-    }
-    const int head = pos / nb, within = pos - head * nb;
-    const int n = head % a.nh, b = head / a.nh;
-    const int fixed = (MODE == 0) ? within : nb - 1 - within;   // heaviest blocks first
-    const int64_t ld3 = 3 * (int64_t)a.H, ldh = a.H;
-    const int64_t t0 = (int64_t)b * a.s;
-    const uint16_t* gq = a.qkv + (int64_t)n * D;
-    const uint16_t* gk = gq + a.H;
-    const uint16_t* gv = gk + a.H;
-    const uint16_t* gdo = a.dO + (int64_t)n * D;
-    const float scale = 0.08838834764831845f;     // 1 / sqrt(128)
-    // exp(x) as the hardware's 2^y with y = x log2(e): its relative error (about 1e-6 for |x| < 30) is far
-    // below half an fp16 ulp, and the softmax phase is bound by vector ALU work, not by the matrix cores
-    const float log2e = 1.4426950408889634f, scale_log2e = scale * log2e;
-
-    // the operand pair that stays: K_j, V_j (MODE 0) or Q_i, dO_i with lse and delta (MODE 1), through LDS
-    // once into the registers of the wave that multiplies with them
-    u32x4 r0[4], r1[4];
-    if (MODE == 0) {
-        fetch_tile(r0, gk + (t0 + (int64_t)fixed * BLK) * ld3, ld3);
-        fetch_tile(r1, gv + (t0 + (int64_t)fixed * BLK) * ld3, ld3);
-    } else {
-        fetch_tile(r0, gq + (t0 + (int64_t)fixed * BLK) * ld3, ld3);
-        fetch_tile(r1, gdo + (t0 + (int64_t)fixed * BLK) * ldh, ldh);
-        if (tid < BLK) {
-            sL[tid] = a.lse[(t0 + (int64_t)fixed * BLK + tid) * a.nh + n] * log2e;
-            sDelta[tid] = a.delta[(t0 + (int64_t)fixed * BLK + tid) * a.nh + n];
-        }
-    }
-    stash_tile(r0, sA);
-    stash_tile(r1, sB);
-    __syncthreads();
-    half8 fx[D / 16], fy[D / 16];
-    {
-        const int row = ((MODE == 0) ? 32 * wc : 32 * wr) + l32;     // MODE 0: this wave's keys; MODE 1: its queries
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            fx[ks] = *reinterpret_cast<const half8*>(sA + row * PD + ((16 * ks + 8 * lh) ^ (swz(row) << 3)));
-            fy[ks] = *reinterpret_cast<const half8*>(sB + row * PD + ((16 * ks + 8 * lh) ^ (swz(row) << 3)));
-        }
-    }
-
-    floatx16 acc0[2], acc1[2];     // MODE 0: dv, dk;  MODE 1: dq (acc1 unused)
+// The rotary step backwards on the lane's row at position `pos`: the pair (c, c + 64) lies in the same register of acc[i] and
+// acc[i + 2].
+__device__ __forceinline__ void rotate_back(floatx16 (&acc)[4], const Args& a, int pos) {
+    const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            acc0[i][r] = 0.f;
-            acc1[i][r] = 0.f;
-        }
-
-    const int first = (MODE == 0) ? fixed : 0;
-    const int last = (MODE == 0) ? nb - 1 : fixed;
-    float rl = 0.f, rd = 0.f;
-    auto fetch_moving = [&](int blk) {
-        const int64_t row0 = t0 + (int64_t)blk * BLK;
-        if (MODE == 0) {
-            fetch_tile(r0, gq + row0 * ld3, ld3);
-            fetch_tile(r1, gdo + row0 * ldh, ldh);
-            if (tid < BLK) {
-                rl = a.lse[(row0 + tid) * a.nh + n];
-                rd = a.delta[(row0 + tid) * a.nh + n];
-            }
-        } else {
-            fetch_tile(r0, gk + row0 * ld3, ld3);
-            fetch_tile(r1, gv + row0 * ld3, ld3);
-        }
-    };
-    fetch_moving(first);
-
-    for (int blk = first; blk <= last; ++blk) {
-        __syncthreads();     // everybody is done with the tiles of the previous block
-        stash_tile(r0, sA);
-        stash_tile(r1, sB);
-        if (MODE == 0 && tid < BLK) {
-            sL[tid] = rl * log2e;
-            sDelta[tid] = rd;
-        }
-        __syncthreads();
-        if (blk < last) fetch_moving(blk + 1);     // in flight while this block is multiplied
-
-        // ---- S^T = K Q^T and dP^T = V dO^T for this wave's 32 keys x 32 queries: the keys are the MFMA rows, so a
-        // lane owns one query (one lse, one delta) and four consecutive keys per register group
-        floatx16 accS, accP;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            accS[r] = 0.f;
-            accP[r] = 0.f;
-        }
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            const int mrow = ((MODE == 0) ? 32 * wr : 32 * wc) + l32;
-            const int off = mrow * PD + ((16 * ks + 8 * lh) ^ (swz(mrow) << 3));
-            if (MODE == 0) {      // moving Q_i, dO_i come from LDS; K_j, V_j from registers
-                const half8 fq = *reinterpret_cast<const half8*>(sA + off);
-                const half8 fd = *reinterpret_cast<const half8*>(sB + off);
-                accS = __builtin_amdgcn_mfma_f32_32x32x16_f16(fx[ks], fq, accS, 0, 0, 0);
-                accP = __builtin_amdgcn_mfma_f32_32x32x16_f16(fy[ks], fd, accP, 0, 0, 0);
-            } else {              // moving K_j, V_j come from LDS; Q_i, dO_i from registers
-                const half8 fk = *reinterpret_cast<const half8*>(sA + off);
-                const half8 fv = *reinterpret_cast<const half8*>(sB + off);
-                accS = __builtin_amdgcn_mfma_f32_32x32x16_f16(fk, fx[ks], accS, 0, 0, 0);
-                accP = __builtin_amdgcn_mfma_f32_32x32x16_f16(fv, fy[ks], accP, 0, 0, 0);
-            }
-        }
-        // ---- P and dS in fp16, [query][key]: four consecutive keys per 8-byte store
-        {
-            const bool diag = blk == fixed;
-            const int qrow = 32 * wr + l32;
-            const float lq = sL[qrow], dq = sDelta[qrow];
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int key0 = 32 * wc + 8 * q4 + 4 * lh;
-                half4 hp, hd;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = 4 * q4 + e;
-                    float p = __builtin_amdgcn_exp2f(fmaf(scale_log2e, accS[r], -lq));
-                    float ds = scale * p * (accP[r] - dq);
-                    if (diag && key0 + e > qrow) {
-                        p = 0.f;
-                        ds = 0.f;
-                    }
-                    hp[e] = (_Float16)p;
-                    hd[e] = (_Float16)ds;
-                }
-                *reinterpret_cast<half4*>(sP + qrow * PS + key0) = hp;
-                *reinterpret_cast<half4*>(sDS + qrow * PS + key0) = hd;
-            }
-        }
-        __syncthreads();
-
-        if (MODE == 0) {
-            // dv^T[dcol][key] += dO^T P,  dk^T[dcol][key] += Q^T dS   (contraction over the 64 queries)
-#pragma unroll
-            for (int ks = 0; ks < BLK / 16; ++ks) {
-                const uint16_t* pp = sP + (16 * ks + tr_row) * PS + 32 * wc + tr_col;
-                const uint16_t* pd = sDS + (16 * ks + tr_row) * PS + 32 * wc + tr_col;
-                const half8 bP = read_tr8(pp, pp + 4 * PS);
-                const half8 bD = read_tr8(pd, pd + 4 * PS);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int col = 64 * wr + 32 * i + tr_col;
-                    const int o0 = (16 * ks + tr_row) * PD + (col ^ tr_sw0), o1 = (16 * ks + tr_row + 4) * PD + (col ^ tr_sw1);
-                    acc0[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_tr8(sB + o0, sB + o1), bP, acc0[i], 0, 0, 0);
-                    acc1[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_tr8(sA + o0, sA + o1), bD, acc1[i], 0, 0, 0);
-                }
-            }
-        } else {
-            // dq^T[dcol][query] += K^T dS^T   (contraction over the 64 keys)
-#pragma unroll
-            for (int ks = 0; ks < BLK / 16; ++ks) {
-                const half8 bD = *reinterpret_cast<const half8*>(sDS + (32 * wc + l32) * PS + 16 * ks + 8 * lh);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int col = 64 * wr + 32 * i + tr_col;
-                    const int o0 = (16 * ks + tr_row) * PD + (col ^ tr_sw0), o1 = (16 * ks + tr_row + 4) * PD + (col ^ tr_sw1);
-                    acc0[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(read_tr8(sA + o0, sA + o1), bD, acc0[i], 0, 0, 0);
-                }
-            }
-        }
-    }
-
-    // ---- results: through LDS as fp32 so that the rotary pairs (c, c + 64) meet and stores are 16 bytes wide
-    const int64_t orow0 = t0 + (int64_t)fixed * BLK;
-    auto emit = [&](floatx16 (&acc)[2], int64_t colbase, bool rotate) {
-        // thread: row = tid / 4, sixteen pairs (c, c + 64) with c = 16 * (tid % 4) ...
-        const int row = tid >> 2, c0 = 16 * (tid & 3);
-        const int pos = fixed * BLK + row;
-        float4 co[4], si[4];
-        if (rotate) {      // the table rows of this thread, requested before the exchange through LDS
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                co[u] = *reinterpret_cast<const float4*>(a.cosv + pos * 64 + c0 + 4 * u);
-                si[u] = *reinterpret_cast<const float4*>(a.sinv + pos * 64 + c0 + 4 * u);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                sOut[(32 * wc + l32) * PO + 64 * wr + 32 * i + 8 * (r >> 2) + 4 * lh + (r & 3)] = acc[i][r];
-        __syncthreads();
-        const float* src = sOut + row * PO;
-        half8 lo[2], hi[2];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float4 x1 = *reinterpret_cast<const float4*>(src + c0 + 4 * u);
-            const float4 x2 = *reinterpret_cast<const float4*>(src + c0 + 64 + 4 * u);
-            const float a1[4] = {x1.x, x1.y, x1.z, x1.w}, a2[4] = {x2.x, x2.y, x2.z, x2.w};
-            float cc[4] = {1.f, 1.f, 1.f, 1.f}, ss[4] = {0.f, 0.f, 0.f, 0.f};
-            if (rotate) {
-                cc[0] = co[u].x; cc[1] = co[u].y; cc[2] = co[u].z; cc[3] = co[u].w;
-                ss[0] = si[u].x; ss[1] = si[u].y; ss[2] = si[u].z; ss[3] = si[u].w;
-            }
+        for (int g = 0; g < 4; ++g) {
+            const float4 co = *reinterpret_cast<const float4*>(a.cosv + (int64_t)pos * 64 + 32 * i + 8 * g + 4 * lh);
+            const float4 si = *reinterpret_cast<const float4*>(a.sinv + (int64_t)pos * 64 + 32 * i + 8 * g + 4 * lh);
+            const float cc[4] = {co.x, co.y, co.z, co.w}, ss[4] = {si.x, si.y, si.z, si.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float y1 = a1[e], y2 = a2[e];
-                if (rotate) {
-                    y1 = fmaf(a2[e], ss[e], a1[e] * cc[e]);
-                    y2 = fmaf(-a1[e], ss[e], a2[e] * cc[e]);
-                }
-                lo[u >> 1][4 * (u & 1) + e] = (_Float16)y1;
-                hi[u >> 1][4 * (u & 1) + e] = (_Float16)y2;
+                const float x1 = acc[i][4 * g + e], x2 = acc[i + 2][4 * g + e];
+                acc[i][4 * g + e] = fmaf(x2, ss[e], x1 * cc[e]);
+                acc[i + 2][4 * g + e] = fmaf(-x1, ss[e], x2 * cc[e]);
             }
         }
-        uint16_t* dst = a.dqkv + (orow0 + row) * ld3 + colbase + (int64_t)n * D + c0;
-        *reinterpret_cast<half8*>(dst) = lo[0];
-        *reinterpret_cast<half8*>(dst + 8) = lo[1];
-        *reinterpret_cast<half8*>(dst + 64) = hi[0];
-        *reinterpret_cast<half8*>(dst + 72) = hi[1];
+}
+
+}  // namespace attn
+
+// exp(x) is the hardware's 2^y with y = x log2(e): its relative error (about 1e-6 for |x| < 30) is far below half an fp16 ulp.
+
+template <int SPLIT>
+__global__ __launch_bounds__(256, 2) void attention_backward_dq_kernel(attn::Args a) {
+    using namespace attn;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];      // two pairs of tiles: K, V
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = SPLIT == 2 ? wave >> 1 : 0;             // which half of the tiles
+    const int l32 = lane & 31, lh = lane >> 5;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+
+    const int nb = (a.s + ROWS<SPLIT> - 1) / ROWS<SPLIT>;
+    const int pos = xcd_position();
+    const int head = pos / nb, within = pos - head * nb;
+    const int n = head % a.nh, b = head / a.nh;
+    const int q0 = (nb - 1 - within) * ROWS<SPLIT>;          // heaviest blocks first
+    const int qw = q0 + 32 * (SPLIT == 2 ? wave & 1 : wave);      // this wave's queries
+    const bool active = qw < a.s;                            // s is a multiple of 64
+    const int last = ((q0 + ROWS<SPLIT> < a.s ? q0 + ROWS<SPLIT> : a.s) - 1) / BLK;      // key blocks of the workgroup
+    const int64_t ld3 = 3 * (int64_t)a.H, ldh = a.H;
+    const int64_t t0 = (int64_t)b * a.s;
+    const uint16_t* gq = a.qkv + (int64_t)n * D;
+    const uint16_t* gk = gq + a.H + t0 * ld3;
+    const uint16_t* gv = gk + a.H;
+    const int64_t t = t0 + qw + l32;                         // the lane's query
+
+    const TileLoad load(ld3);
+    const TileRead rd;
+    auto fetch = [&](int blk, int buf) {
+        const int64_t off = (int64_t)blk * BLK * ld3;
+        load.issue(gk + off, lds0 + (uint32_t)buf * (PAIR * 2u), wave);
+        load.issue(gv + off, lds0 + (uint32_t)buf * (PAIR * 2u) + TILE * 2u, wave);
     };
-    const bool rot = a.cosv != nullptr;
-    if (MODE == 0) {
-        emit(acc0, 2 * (int64_t)a.H, false);    // dv
-        emit(acc1, (int64_t)a.H, rot);          // dk
-    } else {
-        emit(acc0, 0, rot);                     // dq
+    fetch(0, 0);
+
+    half8 fq[D / 16], fd[D / 16];
+    float lq = 0.f, delta = 0.f;
+    if (active) {
+        load_fragments(fq, gq + t * ld3);
+        load_fragments(fd, a.dO + t * ldh + (int64_t)n * D);
+        half8 fo[D / 16];
+        load_fragments(fo, a.o + t * ldh + (int64_t)n * D);
+        lq = a.lse[t * a.nh + n] * LOG2E;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) delta = fmaf((float)fo[ks][e], (float)fd[ks][e], delta);
+        typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+        const u32x2v sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(delta), __float_as_uint(delta), false, false);
+        delta = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        if (lh == 0 && part == 0) a.delta[t * a.nh + n] = delta;
     }
+
+    const float scaled_delta = SCALE * delta;
+
+    floatx16 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+
+    // Keys 32 h .. + 31 of the pair in `buf` against this wave's queries; diag: they have the queries' positions.
+    auto block = [&](int buf, int h, bool diag) {
+        const TileRead r0 = rd.at(buf * PAIR + 32 * h * D);
+        const uint16_t *sK = smem, *sV = smem + TILE;
+        floatx16 S, P;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) S[r] = P[r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            S = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(sK, ks), fq[ks], S, 0, 0, 0);
+            P = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(sV, ks), fd[ks], P, 0, 0, 0);
+        }
+        interleave<4, 2, 2, 6, 4>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(SCALE * LOG2E, S[r], -lq));
+            P[r] = p * fmaf(SCALE, P[r], -scaled_delta);
+        }
+        if (diag) {
+            mask(P, [&](int r) { return 8 * (r >> 2) + 4 * lh + (r & 3) > l32; });
+        }
+        uint32_t pk[8];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) pk[r >> 1] = pack2(P[r], P[r + 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        // dq^T[dcol][query] += k^T[dcol][key] dS^T[key][query], 16 keys at a time
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const half8 f = fragment_of(pk, ks);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(sK, i, ks), f, acc[i], 0, 0, 0);
+        }
+        interleave<4, 1, 2, 6, 2>();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    for (int blk = 0; blk <= last; ++blk) {
+        const int buf = blk & 1;
+        // the block's tiles have landed; everybody is done with the other pair
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (blk < last) fetch(blk + 1, buf ^ 1);      // in flight while this block is multiplied
+        if (!active) continue;
+#pragma nounroll
+        for (int h = part; h < (SPLIT == 2 ? part + 1 : 2); ++h) {
+            const int ahead = qw / 32 - (2 * blk + h);      // of this half's keys
+            if (ahead >= 0) block(buf, h, ahead == 0);
+        }
+    }
+    if constexpr (SPLIT == 2) {
+        float* xch = reinterpret_cast<float*>(smem) + (wave & 1) * 64 * 64 + lane;
+        __syncthreads();      // the tiles are free
+        if (part == 1) put_registers(acc, xch);
+        __syncthreads();
+        if (part == 1) return;
+        add_registers(acc, xch);
+    }
+    if (!active) return;
+    if (a.cosv != nullptr) rotate_back(acc, a, qw + l32);
+    store_rows(acc, 1.f, a.dqkv + t * ld3 + (int64_t)n * D);
+}
+
+template <int SPLIT>
+__global__ __launch_bounds__(256, 2) void attention_backward_dkdv_kernel(attn::Args a) {
+    using namespace attn;
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];      // two pairs of tiles: Q, dO; their lse and delta
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = SPLIT == 2 ? wave >> 1 : 0;             // which half of the tiles
+    const int l32 = lane & 31, lh = lane >> 5;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    float* stats = reinterpret_cast<float*>(smem + 2 * PAIR);      // [pair][lse log2(e) | delta / sqrt(d)][64]
+
+    const int nb = (a.s + ROWS<SPLIT> - 1) / ROWS<SPLIT>;
+    const int pos = xcd_position();
+    const int head = pos / nb;
+    const int n = head % a.nh, b = head / a.nh;
+    const int k0 = (pos - head * nb) * ROWS<SPLIT>;          // heaviest blocks first
+    const int kw = k0 + 32 * (SPLIT == 2 ? wave & 1 : wave);      // this wave's keys
+    const bool active = kw < a.s;                            // s is a multiple of 64
+    const int first = k0 / BLK, last = a.s / BLK - 1;
+    const int64_t ld3 = 3 * (int64_t)a.H, ldh = a.H;
+    const int64_t t0 = (int64_t)b * a.s;
+    const uint16_t* gq = a.qkv + (int64_t)n * D + t0 * ld3;
+    const uint16_t* gdo = a.dO + (int64_t)n * D + t0 * ldh;
+    const float* gstat = (wave == 0 ? a.lse : a.delta) + t0 * a.nh + n;      // wave 0 and 1
+    const int64_t t = t0 + kw + l32;                         // the lane's key
+
+    const TileLoad load_q(ld3), load_do(ldh);
+    float stat = 0.f;
+    const TileRead rd;
+    auto fetch = [&](int blk, int buf) {
+        load_q.issue(gq + (int64_t)blk * BLK * ld3, lds0 + (uint32_t)buf * (PAIR * 2u), wave);
+        load_do.issue(gdo + (int64_t)blk * BLK * ldh, lds0 + (uint32_t)buf * (PAIR * 2u) + TILE * 2u, wave);
+        if (wave < 2) stat = gstat[((int64_t)blk * BLK + lane) * a.nh];
+    };
+    fetch(first, 0);
+
+    half8 fk[D / 16], fv[D / 16];
+    if (active) {
+        load_fragments(fk, a.qkv + a.H + (int64_t)n * D + t * ld3);
+        load_fragments(fv, a.qkv + 2 * (int64_t)a.H + (int64_t)n * D + t * ld3);
+    }
+
+    floatx16 dk[4], dv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dk[i][r] = dv[i][r] = 0.f;
+
+    // Queries 32 h .. + 31 of the pair in `buf` against this wave's keys; diag: they have the keys' positions.
+    auto block = [&](int buf, int h, bool diag) {
+        const TileRead r0 = rd.at(buf * PAIR + 32 * h * D);
+        const uint16_t *sQ = smem, *sD = smem + TILE;
+        const float* sL = stats + 2 * buf * BLK + 32 * h + 4 * lh;
+        floatx16 S, P;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) S[r] = P[r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            S = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(sQ, ks), fk[ks], S, 0, 0, 0);
+            P = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(sD, ks), fv[ks], P, 0, 0, 0);
+        }
+        interleave<4, 2, 2, 6, 4>();
+        __builtin_amdgcn_sched_barrier(0);
+        // register r <-> query 8 (r / 4) + 4 lh + r % 4
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 l4 = *reinterpret_cast<const float4*>(sL + 8 * g), d4 = *reinterpret_cast<const float4*>(sL + BLK + 8 * g);
+            const float lq[4] = {l4.x, l4.y, l4.z, l4.w}, dq[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = 4 * g + e;
+                S[r] = __builtin_amdgcn_exp2f(fmaf(SCALE * LOG2E, S[r], -lq[e]));
+                P[r] = S[r] * fmaf(SCALE, P[r], -dq[e]);
+            }
+        }
+        if (diag) {
+            auto above = [&](int r) { return l32 > 8 * (r >> 2) + 4 * lh + (r & 3); };
+            mask(S, above);
+            mask(P, above);
+        }
+        uint32_t pp[8], pd[8];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            pp[r >> 1] = pack2(S[r], S[r + 1]);
+            pd[r >> 1] = pack2(P[r], P[r + 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // dv^T[dcol][key] += dO^T P,  dk^T[dcol][key] += q^T dS, 16 queries at a time
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const half8 fp = fragment_of(pp, ks), fd = fragment_of(pd, ks);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                dv[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(sD, i, ks), fp, dv[i], 0, 0, 0);
+                dk[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(sQ, i, ks), fd, dk[i], 0, 0, 0);
+            }
+        }
+        interleave<4, 1, 2, 14, 2>();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    for (int blk = first; blk <= last; ++blk) {
+        const int buf = (blk - first) & 1;
+        if (wave < 2) stats[(2 * buf + wave) * BLK + lane] = stat * (wave == 0 ? LOG2E : SCALE);
+        // the block's tiles have landed; everybody is done with the other pair
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (blk < last) fetch(blk + 1, buf ^ 1);      // in flight while this block is multiplied
+        if (!active) continue;
+#pragma nounroll
+        for (int h = part; h < (SPLIT == 2 ? part + 1 : 2); ++h) {
+            const int behind = 2 * blk + h - kw / 32;      // this half's queries
+            if (behind >= 0) block(buf, h, behind == 0);
+        }
+    }
+    if constexpr (SPLIT == 2) {
+        float* xch = reinterpret_cast<float*>(smem) + (wave & 1) * 128 * 64 + lane;
+        __syncthreads();      // the tiles are free
+        if (part == 1) {
+            put_registers(dv, xch);
+            put_registers(dk, xch + 64 * 64);
+        }
+        __syncthreads();
+        if (part == 1) return;
+        add_registers(dv, xch);
+        add_registers(dk, xch + 64 * 64);
+    }
+    if (!active) return;
+    uint16_t* out = a.dqkv + t * ld3 + (int64_t)n * D;
+    store_rows(dv, 1.f, out + 2 * (int64_t)a.H);
+    if (a.cosv != nullptr) rotate_back(dk, a, kw + l32);
+    store_rows(dk, 1.f, out + a.H);
+}
+
+template <int SPLIT>
+static hipError_t launch(const attn::Args& a, int64_t B, hipStream_t st) {
+    using namespace attn;
+    auto dq = attention_backward_dq_kernel<SPLIT>;
+    auto dkdv = attention_backward_dkdv_kernel<SPLIT>;
+    // thread-safe one-time set-up (initialisation of a function-local static)
+    static const hipError_t cfg0 = allow_dynamic_lds(dq, LDS_BYTES);
+    if (cfg0 != hipSuccess) return cfg0;
+    static const hipError_t cfg1 = allow_dynamic_lds(dkdv, BWD_LDS_BYTES);
+    if (cfg1 != hipSuccess) return cfg1;
+    const dim3 grid((unsigned)(((int64_t)a.s + ROWS<SPLIT> - 1) / ROWS<SPLIT> * a.nh * B));
+    hipLaunchKernelGGL(dq, grid, dim3(256), LDS_BYTES, st, a);
+    hipLaunchKernelGGL(dkdv, grid, dim3(256), BWD_LDS_BYTES, st, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_attention_backward(const uint16_t* qkv, const uint16_t* o, const uint16_t* dO, const float* lse,
                                      const float* cosv, const float* sinv, float* delta, uint16_t* dqkv, int64_t B, int64_t s,
                                      int64_t nh, hipStream_t st) {
-    using namespace attn;
-    // thread-safe one-time set-up (initialisation of a function-local static)
-    static const hipError_t cfg0 = allow_dynamic_lds(attention_backward_kernel<0>, LDS_BYTES);
-    if (cfg0 != hipSuccess) return cfg0;
-    static const hipError_t cfg1 = allow_dynamic_lds(attention_backward_kernel<1>, LDS_BYTES);
-    if (cfg1 != hipSuccess) return cfg1;
-    const int64_t rows = B * s * nh;
-    hipLaunchKernelGGL(attention_delta_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, o, dO, delta, rows);
-    Args a;
+    attn::Args a;
     a.qkv = qkv; a.o = o; a.dO = dO; a.lse = lse; a.delta = delta; a.cosv = cosv; a.sinv = sinv; a.dqkv = dqkv;
-    a.s = (int)s; a.nh = (int)nh; a.H = (int)(nh * D);
-    const dim3 grid((unsigned)((s / BLK) * nh * B));
-    hipLaunchKernelGGL(attention_backward_kernel<0>, grid, dim3(256), LDS_BYTES, st, a);
-    hipLaunchKernelGGL(attention_backward_kernel<1>, grid, dim3(256), LDS_BYTES, st, a);
-    return hipGetLastError();
+    a.s = (int)s; a.nh = (int)nh; a.H = (int)(nh * attn::D);
+    return attn::attention_waves(B, s, nh) < 8 * cu_count() ? launch<2>(a, B, st) : launch<1>(a, B, st);
 }
 
 }  // namespace lomo

@@ -1,5 +1,13 @@
-// Pieces shared by the attention forward and backward kernels: tile geometry, the chunk swizzle of the
-// [64 x 128] LDS tiles, tile fetch / stash and the transposing LDS read.
+// Pieces shared by the attention forward and backward kernels: tile geometry, the chunk swizzle of the [64 x 128] LDS tiles,
+// their direct-to-LDS loads, fragment reads, and the way from accumulators to fragments and to memory.
+//
+// All three kernels have one shape: a workgroup of four waves owns 128 rows (queries, or keys in the dk / dv kernel), 32 per
+// wave, whose operands stay in registers as MFMA fragments; the waves share a pair of [64 x 128] tiles that moves along the
+// sequence, double-buffered in LDS, one barrier per pair.  Scores are formed so that a lane owns one of the wave's own rows;
+// what they become (probabilities, their gradients) reaches the next product through registers, so nothing but the
+// moving tiles passes through LDS and waves meet only where a tile changes.
+// SPLIT = 2, for calls that give too few of these: a workgroup owns 64 rows, two waves have the same 32, each takes one half
+// of every moving tile, and their sums are put together at the end.
 #pragma once
 #include "lomo_gemm_common.h"
 
@@ -9,13 +17,15 @@ typedef short short4a __attribute__((ext_vector_type(4)));
 
 namespace attn {
 
-constexpr int D = 128;        // head width
-constexpr int BLK = 64;       // queries / keys per block
-constexpr int PD = D;         // LDS pitch of a [64 x 128] fp16 tile (halves): unpadded, 16-byte chunks swizzled
-constexpr int PS = BLK + 8;   // LDS pitch of a [64 x 64] fp16 tile
-constexpr int PO = D + 4;     // LDS pitch of the fp32 output tile (floats)
-constexpr int TILE = BLK * PD;
-constexpr int LDS_BYTES = 2 * TILE * 2 + 2 * BLK * PS * 2 + 2 * BLK * 4;
+constexpr int D = 128;                 // head width
+template <int SPLIT>
+constexpr int ROWS = 128 / SPLIT;      // rows of a workgroup
+constexpr int BLK = 64;                // rows of a moving tile
+constexpr int TILE = BLK * D;          // halves
+constexpr int PAIR = 2 * TILE;
+constexpr int LDS_BYTES = 2 * PAIR * 2;      // two pairs
+constexpr float SCALE = 0.08838834764831845f;      // 1 / sqrt(128)
+constexpr float LOG2E = 1.4426950408889634f;
 
 __device__ __forceinline__ half8 read_tr8(const uint16_t* p0, const uint16_t* p1) {
     typedef __attribute__((address_space(3))) short4a* lds_p;
@@ -24,27 +34,159 @@ __device__ __forceinline__ half8 read_tr8(const uint16_t* p0, const uint16_t* p1
     return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// A [64 x 128] fp16 tile: thread tid owns the 16-byte chunks tid, tid + 256, tid + 512, tid + 768
-// (row = chunk / 16, column = 8 * (chunk % 16)).
-__device__ __forceinline__ void fetch_tile(u32x4 (&r)[4], const uint16_t* g, int64_t ld) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int c = threadIdx.x + 256 * u;
-        r[u] = *reinterpret_cast<const u32x4*>(g + (int64_t)(c >> 4) * ld + (c & 15) * 8);
-    }
-}
 // Chunk swizzle of the [64 x 128] tiles: 16-byte chunk c of row r sits at position c ^ swz(r).  Rows that
 // differ in their low two bits are 4 chunks apart (the four rows of a transposing read fall on disjoint banks,
 // and so do its two 16-column halves), rows that differ in the next two bits are 1..3 chunks apart (sixteen
 // consecutive rows read at the same column hit sixteen different chunks).
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 
-__device__ __forceinline__ void stash_tile(const u32x4 (&r)[4], uint16_t* s) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int c = threadIdx.x + 256 * u;
-        *reinterpret_cast<u32x4*>(s + (c >> 4) * PD + (((c & 15) ^ swz(c >> 4)) * 8)) = r[u];
+// 16 bytes per lane from base + voff to LDS address m0 + 16 * lane.
+__device__ __forceinline__ void load_lds16(uint32_t voff, const void* base, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
+}
+
+// The loads of a [64 x 128] tile with rows of `ld` elements: wave w of the four fetches rows 16 w .. 16 w + 15 with four instructions of
+// four rows.  A row is a multiple of 256 bytes, so the chunk's place in it is the low byte of the offset, where the swizzles
+// of the four instructions differ by their number.
+struct TileLoad {
+    uint32_t voff;
+    int64_t step;      // four rows
+    __device__ __forceinline__ TileLoad(int64_t ld) {
+        const int lane = threadIdx.x & 63, rr = lane >> 4;
+        voff = (uint32_t)rr * (uint32_t)ld * 2u + (uint32_t)(((lane & 15) ^ swz(rr)) * 16);
+        step = 4 * ld;
     }
+    // `tile`: LDS address; `wave` uniform
+    __device__ __forceinline__ void issue(const uint16_t* base, uint32_t tile, int wave) const {
+        base += 4 * wave * step;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) load_lds16(voff ^ (uint32_t)(16 * it), base + it * step, tile + (uint32_t)(4 * wave + it) * 1024u);
+    }
+};
+
+// Fragment reads from a tile.  The places of the fragments differ in a few low bits; they are formed again for every tile
+// (one instruction each), which costs less than keeping them in registers.
+struct TileRead {
+    int row_rd, tr0, tr1;
+    __device__ __forceinline__ TileRead() {
+        const int lane = threadIdx.x & 63;
+        const int l32 = lane & 31, lh = lane >> 5;
+        const int g4 = lane >> 4, j16 = lane & 15;
+        const int mhalf = g4 & 1, kh = g4 >> 1, rib = j16 >> 2, piece = j16 & 3;
+        const int tr_row = 8 * kh + rib, tr_col = 16 * mhalf + 4 * piece;
+        row_rd = l32 * D + ((8 * lh) ^ (swz(l32) << 3));
+        tr0 = tr_row * D + (tr_col ^ (swz(tr_row) << 3));
+        tr1 = (tr_row + 4) * D + (tr_col ^ (swz(tr_row + 4) << 3));
+    }
+    // the same for a tile `halves` further on
+    __device__ __forceinline__ TileRead at(int halves) const {
+        TileRead t = *this;
+        t.row_rd += halves;
+        t.tr0 += halves;
+        t.tr1 += halves;
+        asm volatile("" : "+v"(t.row_rd), "+v"(t.tr0), "+v"(t.tr1));
+        return t;
+    }
+    // rows 0 .. 31, columns 16 ks .. + 15: a lane holds eight consecutive columns of its row
+    __device__ __forceinline__ half8 rows(const uint16_t* tile, int ks) const {
+        return *reinterpret_cast<const half8*>(tile + (row_rd ^ (16 * ks)));
+    }
+    // columns 32 i .. + 31, rows 16 ks .. + 15: a lane holds eight consecutive rows of its column
+    __device__ __forceinline__ half8 columns(const uint16_t* tile, int i, int ks) const {
+        return read_tr8(tile + ((tr0 ^ (32 * i)) + 16 * ks * D), tile + ((tr1 ^ (32 * i)) + 16 * ks * D));
+    }
+};
+
+template <int N, typename F>
+__device__ __forceinline__ void repeat(F&& f) {
+    if constexpr (N > 0) {
+        f();
+        repeat<N - 1>(f);
+    }
+}
+// Order of a run of matrix instructions and of the LDS reads that feed them: AHEAD reads in front, then READS behind every MFMAS.
+template <int AHEAD, int MFMAS, int READS, int TIMES, int REST>
+__device__ __forceinline__ void interleave() {
+    __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+    repeat<TIMES>([] {
+        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+    });
+    __builtin_amdgcn_sched_group_barrier(0x008, REST, 0);
+}
+
+// This wave's 32 rows, straight from memory: a lane holds eight consecutive columns of its row per fragment.
+__device__ __forceinline__ void load_fragments(half8 (&f)[D / 16], const uint16_t* row) {
+    const int lh = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) f[ks] = *reinterpret_cast<const half8*>(row + 16 * ks + 8 * lh);
+}
+
+// A lane's sixteen values of a 32 x 32 block, as packed fp16 pairs of neighbouring rows of the block: pk[r / 2] holds the
+// rows 8 (r / 4) + 4 lh + r % 4 and the next.  Lane halves exchange so that each holds eight consecutive rows 16 ks + 8 lh ..:
+// the fragment of the next product's second operand.
+__device__ __forceinline__ half8 fragment_of(const uint32_t (&pk)[8], int ks) {
+    typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+    const u32x2v s0 = __builtin_amdgcn_permlane32_swap(pk[4 * ks + 0], pk[4 * ks + 2], false, false);
+    const u32x2v s1 = __builtin_amdgcn_permlane32_swap(pk[4 * ks + 1], pk[4 * ks + 3], false, false);
+    const u32x4 w = {s0[0], s1[0], s0[1], s1[1]};
+    return __builtin_bit_cast(half8, w);
+}
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    const half2v h = {(_Float16)a, (_Float16)b};
+    return __builtin_bit_cast(uint32_t, h);
+}
+
+// acc[i][r]: column 32 i + 8 (r / 4) + 4 lh + r % 4 of the lane's row, scaled by f and rounded once.
+__device__ __forceinline__ void store_rows(const floatx16 (&acc)[4], float f, uint16_t* row) {
+    const int lh = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t pk[8];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) pk[r >> 1] = pack2(acc[i][r] * f, acc[i][r + 1] * f);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) *reinterpret_cast<half8*>(row + 32 * i + 16 * a + 8 * lh) = fragment_of(pk, a);
+    }
+}
+
+// The second half's accumulators on their way to the first's wave: [register][lane].
+__device__ __forceinline__ void put_registers(const floatx16 (&acc)[4], float* lds) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) lds[(16 * i + r) * 64] = acc[i][r];
+}
+__device__ __forceinline__ void add_registers(floatx16 (&acc)[4], const float* lds) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] += lds[(16 * i + r) * 64];
+}
+
+// Waves of a call that is not split.  Below four per CU (one on every SIMD) forward, below eight backward, a call is split, which
+// halves the longest walk.  Measured, us, not split / split: forward 1 x 1024 tokens, 32 heads (1024 waves) 29.5 / 32, 3 x 320
+// (960) 15.8 / 13.7; backward 88.8 / 78, 50.0 / 40; 8 x 512 (4096) 46 and 145 not split (one kernel before this: 55, 170).
+inline int64_t attention_waves(int64_t B, int64_t s, int64_t nh) { return s / 32 * nh * B; }
+
+// Zeros the values of a diagonal block that the mask takes; the branch around it stays one (most blocks have no mask).
+template <typename F>
+__device__ __forceinline__ void mask(floatx16& x, F&& masked) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float v = masked(r) ? 0.f : x[r];
+        asm volatile("" : "+v"(v));
+        x[r] = v;
+    }
+}
+
+// Position of this workgroup in launch order when each XCD (blockIdx % 8) takes a contiguous run of (sequence, head) pairs,
+// so that the blocks of one head, which read the same rows, meet in one L2.
+__device__ __forceinline__ int xcd_position() {
+    const int G = gridDim.x, x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
+    const int q = G >> 3, r = G & 7;
+    return x * q + (x < r ? x : r) + local;
 }
 
 }  // namespace attn

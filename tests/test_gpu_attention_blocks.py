@@ -1,0 +1,59 @@
+"""The attention kernels at the edges of their blocks and on both sides of the rule that splits a call: 128 rows per workgroup or 64 with
+the tiles split over the waves, sequences that end in the middle of a block, one block alone.  Against 64 bits on the GPU, every
+sequence and head by itself: fp16 outputs and fp16 P and dS are each off by at most half a unit in the last place, 2^-11 of
+their size, so a head's relative error in the Frobenius norm stays below 2^-10.  (Element-wise bars: test_gpu_attention.py,
+test_gpu_forward.py.)"""
+import os
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2306_09782_amd as L
+    if not os.path.exists(L.library_path()):
+        from paper_2306_09782_amd.build import build
+        build(verbose=False)
+    L.load_library()
+    return L
+
+
+def reference(q, k, v, do):
+    """One head of one sequence in 64 bits: o, lse, dq, dk, dv."""
+    s = q.shape[0]
+    scores = (q @ k.t().contiguous()) / 128 ** 0.5
+    scores = scores.masked_fill(torch.ones(s, s, device=DEV, dtype=torch.bool).triu(1), -float("inf"))
+    P, lse = scores.softmax(-1), scores.logsumexp(-1)
+    o = P @ v
+    dS = P * (do @ v.t().contiguous() - (do * o).sum(-1, keepdim=True)) / 128 ** 0.5
+    return o, lse, dS @ k, dS.t().contiguous() @ q, P.t().contiguous() @ do
+
+
+# waves of 32 rows per call: 2 ... 34 (split), 1280 (forward not, backward split), 2048 and more (not split)
+@pytest.mark.parametrize("B,s,nh", [(1, 64, 1), (2, 192, 1), (1, 1088, 1), (4, 320, 32), (32, 64, 32), (12, 192, 32), (8, 320, 32), (2, 1088, 32)])
+def test_blocks(L, B, s, nh):
+    T, H = B * s, nh * 128
+    gen = torch.Generator(device=DEV).manual_seed(s + nh)
+    normal = lambda *shape: torch.randn(shape, generator=gen, device=DEV, dtype=torch.float16)
+    qkv, do = normal(T, 3 * H), normal(T, H)
+    guard = torch.full((T + 256, 3 * H), 9.0, dtype=torch.float16, device=DEV)      # rows in front of and behind the gradient
+    o, grad = torch.full((T, H), 9.0, dtype=torch.float16, device=DEV), guard[128:128 + T]
+    lse, delta = torch.empty(T, nh, device=DEV), torch.empty(T, nh, device=DEV)
+    L.lomo_attention_forward(qkv, o, lse, B, s, nh)
+    L.lomo_attention_backward(qkv, o, do, lse.view(-1), None, None, delta.view(-1), grad, B, s, nh)
+    assert bool((guard[:128] == 9).all()) and bool((guard[128 + T:] == 9).all())
+    off = lambda got, want: float((got.double() - want).norm() / want.norm())
+    for b in sorted({0, B // 2, B - 1}):
+        for n in sorted({0, nh // 2, nh - 1}):
+            rows, cols = slice(b * s, (b + 1) * s), slice(n * 128, (n + 1) * 128)
+            part = lambda x, i: x[rows, i * H + n * 128:i * H + (n + 1) * 128].double()
+            want = reference(part(qkv, 0), part(qkv, 1), part(qkv, 2), do[rows, cols].double())
+            assert float((lse[rows, n].double() - want[1]).abs().max()) < 1e-5
+            got = (o[rows, cols], None, *(grad[rows, i * H + n * 128:i * H + (n + 1) * 128] for i in range(3)))
+            for name, g, w in zip(("o", "lse", "dq", "dk", "dv"), got, want):
+                if g is not None:
+                    assert off(g, w) < 2.0 ** -10, (name, b, n, off(g, w))
