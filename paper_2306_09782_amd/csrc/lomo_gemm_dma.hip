@@ -74,16 +74,13 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     const int wm = wave & 1, wn = wave >> 1;
     const int G = gridDim.x;
 
-    const int pos = window_position(G);
 
-    // round alignment (update kernels): this XCD's run of positions and how many of them have a tile in round k
+    // round alignment (update kernels): how many workgroups of this XCD have a tile in round k
     constexpr bool ALIGN_ROUNDS = EPI == EPI_UPDATE || EPI == EPI_CLIPV;
     const int xcd = (int)(blockIdx.x & 7);
-    const int xcd_first = xcd * (G >> 3) + (xcd < (G & 7) ? xcd : (G & 7));
-    const int xcd_count = (G >> 3) + (xcd < (G & 7) ? 1 : 0);
     auto xcd_tiles_in_round = [&](int k) {
-        const int v = ga.total_tiles - k * G - xcd_first;
-        return v < 0 ? 0 : (v > xcd_count ? xcd_count : v);
+        const int n = round_tiles(k, G, ga.total_tiles);
+        return (n >> 3) + (xcd < (n & 7) ? 1 : 0);
     };
     bool align_rounds = ALIGN_ROUNDS;      // cleared after a wait that ran into its bound
     int round = 0;
@@ -244,8 +241,8 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         }
     };
 
-    // ---- walk the tile list: tile w = round * G + pos; every workgroup leaves through `break`
-    int w = pos;
+    // ---- walk the tile list, one tile a round; every workgroup leaves through `break`
+    int w = round_tile(0, G, ga.total_tiles);
     if (w >= ga.total_tiles) return;   // cannot happen with grid <= total_tiles; nothing was issued yet
     int tensor = 0;
     int64_t m0, n0;
@@ -314,9 +311,8 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         const int64_t em0 = m0, en0 = n0;
 
         // request the first blocks of W (update), then the first slices of the next tile, then finish this one
-        w += G;
+        w = round_tile(++round, G, ga.total_tiles);
         const bool more = w < ga.total_tiles;
-        ++round;
         if constexpr (ALIGN_ROUNDS) {
             if (more && round < SYNC_ROUNDS && tid == 0) atomicAdd(&g_round_arrive[round][xcd], 1);
         }

@@ -15,13 +15,20 @@ constexpr int LDS_BYTES = NS * STAGE_HALVES * 2 + 8 * EPI_UNIT_HALVES * 2;
 
 __device__ __forceinline__ int swz_s(int r) { return ((r & 1) * 10) + ((r & 2) * 2); }
 
-// Position of this workgroup inside a window of G consecutive tiles: workgroups of one XCD (blockIdx % 8) take a
-// contiguous run, which the band order of locate_tile turns into an 8 x 4 block of tiles that share operand panels in
-// that XCD's L2.
-__device__ __forceinline__ int window_position(int G) {
+// Tiles of round k of a list that G workgroups walk: G, in the last round what is left.
+__device__ __forceinline__ int round_tiles(int k, int G, int total) {
+    const int left = total - k * G;
+    return left < 0 ? 0 : (left < G ? left : G);
+}
+// This workgroup's tile of round k, `total` where it has none.  The workgroups of one XCD (blockIdx % 8) take a contiguous
+// run, which the band order of locate_tile turns into an 8 x 4 block of tiles that share operand panels in that XCD's L2;
+// a last round is dealt out to all XCDs alike: left to the first of them, a round of 96 tiles runs at the speed of three XCDs' memory
+// paths.  Measured, us, first XCDs -> all: update of 8192 x 5120 x 5120 (400 tiles) 430 -> 364, its Y and dX (640) 400 -> 354; norm of
+// 4096 x 4096 x 22016 (1376) 623 -> 598, its update 654 -> 630; dX of 4096 x 11008 x 4096 (688) 325 -> 298.
+__device__ __forceinline__ int round_tile(int k, int G, int total) {
     const int x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
-    const int q = G >> 3, r = G & 7;
-    return x * q + (x < r ? x : r) + local;
+    const int n = round_tiles(k, G, total), q = n >> 3, r = n & 7;
+    return local < q + (x < r ? 1 : 0) ? k * G + x * q + (x < r ? x : r) + local : total;
 }
 
 // Tensor and origin of tile number w of the concatenated list.  A workgroup's tile numbers only grow, so the search for

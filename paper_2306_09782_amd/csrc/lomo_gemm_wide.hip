@@ -46,7 +46,6 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
     const int wm = wave & 1, wn = wave >> 1;
     const int l32 = lane & 31, lh = lane >> 5;
     const int G = gridDim.x;
-    const int pos = window_position(G);
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
 
@@ -248,8 +247,9 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
         }
     };
 
-    // ---- walk the tile list: tile w = round * G + pos; every workgroup leaves through `break`
-    int w = pos;
+    // ---- walk the tile list, one tile a round; every workgroup leaves through `break`
+    int round = 0;
+    int w = round_tile(round, G, ga.total_tiles);
     if (w >= ga.total_tiles) return;   // cannot happen with grid <= total_tiles; nothing was issued yet
     int tensor = 0;
     int64_t m0, n0;
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
             re.fill(1);
             re.fill(2);
         }
-        w += G;
+        w = round_tile(++round, G, ga.total_tiles);
         const bool more = w < ga.total_tiles;
         if (more) {
             setup(w, tensor, m0, n0);
