@@ -19,6 +19,7 @@
 // With A on the MFMA row side, each lane's four consecutive accumulator registers are four
 // consecutive m, i.e. an 8-byte run of W / dX: the read-modify-write epilogue is vectorised.
 #include "lomo_gemm_common.h"
+#include "lomo_gemm_dma_common.h"
 
 #include <stdlib.h>
 
@@ -237,19 +238,20 @@ static bool fast_enabled() {
 }
 
 // ---- which kernel runs a tensor -----------------------------------------------------------
-// Four shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip), and in lomo_gemm_tile.hip 128 x 128, 128 x 64 and
-// 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the CUs and walk the contraction faster.
+// Five shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip and lomo_gemm_wide.hip), and in lomo_gemm_tile.hip 256 x 128,
+// 128 x 128, 128 x 64 and 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the CUs and walk the
+// contraction faster.
 // The kernels of a pass run one behind the other, so what counts is the sum of their times over the whole list: tensors that
 // would leave most of the chip idle alone fill each other's rounds in the persistent kernel, and one leaves it only where
 // that makes the pass shorter (a long contraction with few tiles).  All kernels give the same bits, so the list a tensor
 // comes in does not show in its result.
 //
-// The times, in microseconds, are fitted to 65 shapes of output (256 x 256 to 11008 x 4096) and contraction (256 to 11008) in
-// each kernel and product: root mean square error 7 to 13 %; choosing by them costs 1 % on average over the best kernel of
-// each.  A tile takes a fixed part (ramp-up and epilogue) and a part per contraction index; the latter is at least `latency`
-// and, with every CU busy, `through` for each tile that a CU has.  Measured at C = 4096, dX (us; in the order above):
-//   1024 x 1024 outputs 65, 41, 34, 17;   4096 x 1024: 70, 36, 46, 55;   4096 x 4096: 118, 132, 166, 222.
-// Lists, measured with all of one shape of tile against the former choice by each tensor alone (dX, us): 7B layers at 1024
+// The times, in microseconds, are fitted to 270 shapes of output and contraction (128 to 8192 tokens of layers 1024 to 8192 wide
+// and their vocabularies) in each kernel and product: root mean square error 4 to 13 %; choosing by them costs 0.1 to 0.3 % on
+// average over the best kernel of each.  A tile takes a fixed part (ramp-up and epilogue) and a part per contraction index; the
+// latter is at least `latency` and, with every CU busy, `through` for each tile that a CU has.  Measured at C = 4096, dX (us; in
+// the order of the table): 1024 x 4096 outputs 67, 47, 38, 47, 57;   2048 x 4096: 83, 73, 83, -, -;   4096 x 4096: 108, 130, 132, 166, 222.
+// Lists, measured with all of one shape of tile against the choice by each tensor alone (dX, us): 7B layers at 1024
 // tokens 1528 against 1960 for four, at 2048 tokens 2647 against 3642; 24 layers of width 1024 at 2048 tokens 1443 against
 // 2077, their updates 1219 against 1826.
 struct TileCost {
@@ -258,12 +260,13 @@ struct TileCost {
     double latency, through;
 };
 static const TileCost kTile[N_TILES] = {
-    {256, 256, 1, {7.0, 9.0, 4.8}, 0.0135, 0.0260},
+    {256, 256, 1, {3.0, 10.0, 4.1}, 0.0140, 0.0244},
+    {256, 128, 1, {6.0, 8.5, 5.2}, 0.0098, 0.0158},
     {128, 128, 1, {2.8, 4.2, 2.5}, 0.0057, 0.0082},
     {128, 64, 2, {1.9, 2.9, 3.0}, 0.0043, 0.0055},
     {64, 64, 2, {1.4, 2.0, 3.0}, 0.0027, 0.0036},
 };
-constexpr double kLaunch = 4.0;          // launch and drain
+constexpr double kLaunch = 10.0;         // launch, ramp-up and drain
 constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take one of the two starting choices as it is
 
 namespace {
@@ -275,7 +278,7 @@ struct Shape {
 };
 }  // namespace
 
-// Time of the launches of one tile shape.
+// Time of the launches of one tile shape; shapes come longest contraction first.
 static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int product, double cus) {
     const TileCost& k = kTile[tile];
     double tiles = 0.0, indices = 0.0, longest = 0.0;       // indices: contraction indices walked by all tiles together
@@ -290,15 +293,54 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
     if (tiles == 0.0) return 0.0;
     const double per_cu = tiles / cus, mean = indices / tiles, f = k.fixed[product];
     if (tile == TILE_256) {
-        // one round: a tile is faster when it has the memory system to itself.  More: whole rounds
-        if (per_cu <= 1.0) return kLaunch + f + (k.latency + (k.through - k.latency) * per_cu) * longest;
-        return kLaunch + std::max(ceil(per_cu) * (f + k.through * mean), f + k.through * longest);
+        // A workgroup walks one tile per round, so a round takes as long as its first tile; a round that is not full takes less
+        // (a tile is faster when it has the memory system to itself).
+        double time = kLaunch, seen = 0.0;
+        for (size_t i = 0; i < n_shapes; ++i) {
+            const Shape& s = shapes[i];
+            if (s.tile != tile) continue;
+            const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
+            const double from = ceil(seen / cus), to = ceil((seen + n) / cus);      // the rounds that begin with this shape
+            const double full = std::max(0.0, std::min(to, floor(per_cu)) - from);
+            time += full * (f + k.through * (double)s.C);
+            if (to - from > full) time += f + (k.latency + (k.through - k.latency) * (per_cu - floor(per_cu))) * (double)s.C;
+            seen += n;
+        }
+        return time;
     }
     // a partly filled round costs 0.7 of a full one, or what it has of it
     const double rounds = std::max(per_cu, floor(per_cu) + (per_cu > floor(per_cu) ? 0.7 : 0.0));
     const double waves = ceil(per_cu / k.per_cu);
+    // the longest walk of a mixed list goes on alone when the rest is done
+    const double busy = std::min(longest, mean * per_cu);
     return kLaunch + std::max(waves * f + mean * std::max(k.latency * waves, k.through * rounds),
-                              f + longest * std::max(k.latency, 0.7 * k.through));
+                              f + (longest > mean ? k.through * busy + k.latency * (longest - busy) : longest * std::max(k.latency, 0.7 * k.through)));
+}
+
+// Contraction indices of the longest walk when the persistent kernels take a list in this order: tile t of a round goes to the
+// workgroup that has tile t of every round (of a last round to others, which is left out of account).
+static double longest_walk(const GemmArgs* list, size_t n) {
+    const int64_t cus = cu_count();
+    std::vector<double> step((size_t)cus + 1, 0.0);      // of the walks, from one workgroup to the next
+    double all = 0.0;
+    int64_t at = 0;
+    for (size_t i = 0; i < n; ++i) {
+        const double c = (double)list[i].C;
+        int64_t tiles = ((list[i].M + 255) / 256) * ((list[i].Nn + 255) / 256);
+        all += c * (double)(tiles / cus);
+        tiles %= cus;
+        const int64_t to = at + tiles;
+        step[(size_t)at] += c;
+        step[(size_t)(to < cus ? to : cus)] -= c;
+        if (to > cus) {
+            step[0] += c;
+            step[(size_t)(to - cus)] -= c;
+        }
+        at = to % cus;
+    }
+    double walk = 0.0, longest = 0.0;
+    for (double s : step) longest = std::max(longest, walk += s);
+    return all + longest;
 }
 
 static double pass_time(const std::vector<Shape>& shapes, int product, double cus) {
@@ -311,7 +353,7 @@ static int best_alone(Shape one, int product, double cus) {
     int to = one.tile = TILE_256;
     if (one.fixed) return to;
     double best = launch_time(&one, 1, TILE_256, product, cus);
-    for (one.tile = TILE_128; one.tile < N_TILES; ++one.tile) {
+    for (one.tile = TILE_256 + 1; one.tile < N_TILES; ++one.tile) {
         const double t = launch_time(&one, 1, one.tile, product, cus);
         if (t < best) {
             best = t;
@@ -326,23 +368,19 @@ static int best_alone(Shape one, int product, double cus) {
 void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     const double cus = (double)cu_count();
     std::vector<Shape> shapes;
-    std::vector<size_t> shape_of(n);
+    auto same = [&](const Shape& s, const GemmArgs& a) { return s.M == a.M && s.Nn == a.Nn && s.C == a.C; };
     for (size_t i = 0; i < n; ++i) {
-        const GemmArgs& a = list[i];
         size_t k = 0;
-        while (k < shapes.size() && !(shapes[k].M == a.M && shapes[k].Nn == a.Nn && shapes[k].C == a.C)) ++k;
-        if (k == shapes.size()) shapes.push_back({a.M, a.Nn, a.C, 0.0, TILE_256, a.persistent_only});
+        while (k < shapes.size() && !same(shapes[k], list[i])) ++k;
+        if (k == shapes.size()) shapes.push_back({list[i].M, list[i].Nn, list[i].C, 0.0, TILE_256, list[i].persistent_only});
         shapes[k].count += 1.0;
-        shape_of[i] = k;
     }
-    std::vector<size_t> order(shapes.size());
-    for (size_t k = 0; k < order.size(); ++k) order[k] = k;
-    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return shapes[x].C > shapes[y].C; });
+    std::stable_sort(shapes.begin(), shapes.end(), [](const Shape& x, const Shape& y) { return x.C > y.C; });
     auto improve = [&](std::vector<Shape>& v) {
         double best = pass_time(v, product, cus);
         for (int sweep = 0; sweep < 3 && v.size() <= kGreedyShapes; ++sweep) {
             bool moved = false;
-            for (size_t k : order) {
+            for (size_t k = 0; k < v.size(); ++k) {
                 if (v[k].fixed) continue;
                 const int was = v[k].tile;
                 int to = was;
@@ -365,7 +403,57 @@ void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     std::vector<Shape> alone = shapes;
     for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0, s.fixed}, product, cus);
     if (shapes.size() == 1 || improve(alone) < improve(shapes)) shapes.swap(alone);
-    for (size_t i = 0; i < n; ++i) tile_of[i] = shapes[shape_of[i]].tile;
+    for (size_t i = 0; i < n; ++i)
+        tile_of[i] = std::find_if(shapes.begin(), shapes.end(), [&](const Shape& s) { return same(s, list[i]); })->tile;
+}
+
+// A last round of a few tiles takes nearly as long as a full one (the workgroups have few neighbours to share panels with and wait
+// for memory), small tiles spread the same work over the chip.  Measured, us, norm of T = 4096 and 4096 columns: 512 + 16, + 32, + 64
+// tiles 315, 315, 325 against 224 for the 512; a list of 12 rounds and 16 tiles 1361.
+Leftover cut_leftover(const GemmArgs* list, int n, int product, bool a_strided, bool b_strided) {
+    Leftover best;
+    const int64_t cus = cu_count();
+    auto tiles = [](int64_t x) { return (x + 255) / 256; };
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) total += tiles(list[i].M) * tiles(list[i].Nn);
+    const int64_t left = total % cus;
+    if (total < cus || left == 0 || 4 * left > cus) return best;
+    double shortest = 1e30;
+    for (int i = 0; i < n; ++i) {
+        const GemmArgs& a = list[i];
+        if (a.persistent_only) continue;
+        for (bool columns : {true, false}) {
+            const int64_t along = tiles(columns ? a.M : a.Nn), across = tiles(columns ? a.Nn : a.M);
+            const int64_t k = (left + across - 1) / across;      // columns or rows of tiles to take away
+            if (k >= along) continue;
+            const int64_t at = (along - k) * 256;
+            Shape piece{columns ? a.M - at : a.M, columns ? a.Nn : a.Nn - at, a.C, 1.0, TILE_256, false};
+            // the round that is saved, by the measurements above
+            double time = kTile[TILE_256].fixed[product] + 0.0215 * (double)list[n - 1].C;
+            int tile = TILE_256;
+            for (piece.tile = TILE_256 + 1; piece.tile < N_TILES; ++piece.tile) {
+                const double t = launch_time(&piece, 1, piece.tile, product, (double)cus);
+                if (t < time) {
+                    time = t;
+                    tile = piece.tile;
+                }
+            }
+            if (tile == TILE_256 || time >= shortest) continue;
+            shortest = time;
+            best.tensor = i;
+            best.tile = tile;
+            best.kept = best.piece = a;
+            (columns ? best.kept.M : best.kept.Nn) = at;
+            best.piece.M = piece.M;
+            best.piece.Nn = piece.Nn;
+            const int64_t m0 = columns ? at : 0, n0 = columns ? 0 : at;
+            best.piece.A += a_strided ? m0 : m0 * a.lda;
+            best.piece.B += b_strided ? n0 : n0 * a.ldb;
+            if (a.Out != nullptr) best.piece.Out += n0 * a.ldo + m0;
+            if (a.Res != nullptr) best.piece.Res += n0 * a.ldo + m0;
+        }
+    }
+    return best;
 }
 
 void tile_size(int tile, int32_t* m, int32_t* n) {
@@ -376,8 +464,20 @@ void tile_size(int tile, int32_t* m, int32_t* n) {
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_with(int tile, const GemmArgs* list, size_t n, hipStream_t st) {
     if (tile != TILE_256) return launch_tile_group<B_STRIDED, EPI, A_STRIDED>(list, (int)n, tile, st);
-    if constexpr (B_STRIDED) return launch_dma_group<EPI>(list, (int)n, st);
-    else return launch_wide_group<EPI, A_STRIDED>(list, (int)n, st);
+    constexpr int product = EPI == EPI_SQNORM ? PRODUCT_NORM : EPI == EPI_STORE ? PRODUCT_STORE : PRODUCT_UPDATE;
+    GemmArgs group[dma::MAX_GROUP];
+    for (size_t first = 0; first < n; first += dma::MAX_GROUP) {
+        const int cnt = (int)(n - first < (size_t)dma::MAX_GROUP ? n - first : (size_t)dma::MAX_GROUP);
+        std::copy(list + first, list + first + cnt, group);
+        const Leftover l = cut_leftover(group, cnt, product, A_STRIDED, B_STRIDED);
+        if (l.tensor >= 0) group[l.tensor] = l.kept;
+        hipError_t e;
+        if constexpr (B_STRIDED) e = launch_dma_group<EPI>(group, cnt, st);
+        else e = launch_wide_group<EPI, A_STRIDED>(group, cnt, st);
+        if (e == hipSuccess && l.tensor >= 0) e = launch_tile_group<B_STRIDED, EPI, A_STRIDED>(&l.piece, 1, l.tile, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // A list of one allocates no host memory; for longer ones a failed allocation is an error code like a refused launch.
@@ -387,8 +487,10 @@ static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) tr
     auto any_shape = [](const GemmArgs& a) { return !fast_enabled() || !dma_eligible<B_STRIDED, A_STRIDED>(a); };
     if (n == 1) {
         if (any_shape(*list)) return launch_generic<B_STRIDED, EPI, A_STRIDED>(*list, st);
-        const Shape s{list->M, list->Nn, list->C, 1.0, TILE_256, beyond_descriptor<B_STRIDED, A_STRIDED>(*list)};
-        return launch_with<B_STRIDED, EPI, A_STRIDED>(best_alone(s, product, (double)cu_count()), list, 1, st);
+        GemmArgs one = *list;
+        one.persistent_only = beyond_descriptor<B_STRIDED, A_STRIDED>(one);
+        const Shape s{one.M, one.Nn, one.C, 1.0, TILE_256, one.persistent_only};
+        return launch_with<B_STRIDED, EPI, A_STRIDED>(best_alone(s, product, (double)cu_count()), &one, 1, st);
     }
     std::vector<GemmArgs> fit, by[N_TILES];
     for (size_t i = 0; i < n; ++i) {
@@ -405,9 +507,12 @@ static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) tr
     for (size_t i = 0; i < fit.size(); ++i) by[tile_of[i]].push_back(fit[i]);
     for (int tile = 0; tile < N_TILES; ++tile) {
         if (by[tile].empty()) continue;
-        // workgroups of the small tiles start in list order: the longest walks first
-        if (tile != TILE_256)
-            std::stable_sort(by[tile].begin(), by[tile].end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
+        // workgroups of the small tiles start in list order: the longest walks first.  In the persistent kernels that is done where
+        // it makes the longest walk shorter; otherwise the order does not matter much (dX of a 7B layer at 4096 tokens 1339 us as
+        // listed, 1337 sorted; at 2999 tokens 1070 and 1078; of two 13B layers at 1070 tokens 1286 and 1339).
+        std::vector<GemmArgs> sorted = by[tile];
+        std::stable_sort(sorted.begin(), sorted.end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
+        if (tile != TILE_256 || longest_walk(sorted.data(), sorted.size()) < 0.98 * longest_walk(by[tile].data(), by[tile].size())) by[tile].swap(sorted);
         const hipError_t e = launch_with<B_STRIDED, EPI, A_STRIDED>(tile, by[tile].data(), by[tile].size(), st);
         if (e != hipSuccess) return e;
     }

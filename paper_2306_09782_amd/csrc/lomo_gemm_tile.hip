@@ -11,7 +11,7 @@
 //     lanes of a contraction-contiguous operand that lie behind the last index are masked in the last slice.
 //   * A ring of slices in LDS, two slices per barrier (one per barrier: 128 x 128 tiles 10 % slower); their fragments are read
 //     into registers while the previous two are multiplied, so all of the ring but those two holds loads in flight.
-//   * 128 x 128: eight waves of 64 x 32, two on every SIMD (one's LDS reads run behind the other's MFMAs), 128 KiB of LDS.
+//   * 256 x 128: eight waves of 64 x 64, two on every SIMD, 144 KiB.  128 x 128: eight waves of 64 x 32, two on every SIMD (one's LDS reads run behind the other's MFMAs), 128 KiB of LDS.
 //     128 x 64: four waves of 64 x 32, 72 KiB; 64 x 64: four waves of 32 x 32, 80 KiB: two workgroups on a CU, so that
 //     one's ramp-up and epilogue run behind the other's main loop.
 // One launch takes a list of tensors; workgroups start in list order, longest contraction first.
@@ -19,6 +19,8 @@
 // Measured, us per call, against the same tiles with the contraction split over two or four groups of waves (which adds in
 // another order) and against the persistent kernel:
 //   dX of 1024 x 4096, C = 22016, 128 x 128 tiles: 178 (1037 TFLOP/s), 196, 350;  Y of 1024 x 4096, C = 11008: 95, 117, 190
+//   dX of 2048 x 4096, C = 4096: 256 x 128 tiles 73, 128 x 128 83, persistent 82;  2048 x 4096, C = 11008: 170, 191, 184;
+//   dX of 1024 x 5120, C = 13824: 157, 205, 244
 //   dX of 777 x 2048, C = 32000, 128 x 64 tiles: 168, 166, 475;               update of 777 x 2048 x 2048: 14.6, 18, 28
 //   dX of 256 x 1024, C = 32000, 64 x 64 tiles: 127, 138, 470;                Y of 777 x 2048, C = 2048: 15.0, 19.7, 40
 #include "lomo_gemm_common.h"
@@ -399,6 +401,7 @@ static hipError_t launch_tile(const GemmArgs* list, int n, hipStream_t st) {
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t st) {
     switch (tile) {
+        case TILE_256_128: return launch_tile<2, 2, 4, 2, 6, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
         case TILE_128: return launch_tile<2, 1, 2, 4, 8, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
         case TILE_128_64: return launch_tile<2, 1, 2, 2, 6, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
         default: return launch_tile<1, 1, 2, 2, 10, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);

@@ -54,11 +54,20 @@ hipError_t launch_wide_group(const GemmArgs* list, int n, hipStream_t st);
 
 // Kernel of smaller tiles (lomo_gemm_tile.hip), one workgroup per tile; takes lists and shapes as the persistent kernel does and
 // gives the same bits.  Tiles are (m) x (n) as in GemmArgs.
-enum { TILE_256, TILE_128, TILE_128_64, TILE_64, N_TILES };
+enum { TILE_256, TILE_256_128, TILE_128, TILE_128_64, TILE_64, N_TILES };
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t st);
 
 int cu_count();      // of the current device; 256 where there is none
+
+// The few tiles that a launch of the persistent kernels would have in a round of their own, as a piece of one tensor (the columns
+// m >= M of `kept`, or its rows n >= Nn) for the small tiles.
+struct Leftover {
+    int tensor = -1;          // of the list; none
+    GemmArgs kept, piece;     // the tensor without the piece; the piece
+    int tile;                 // the shape of tile for it
+};
+Leftover cut_leftover(const GemmArgs* list, int n, int product, bool a_strided, bool b_strided);
 
 // The tile shape of every tensor of a pass (M, Nn, C and persistent_only are read).  Product: what the epilogue does.
 enum Product { PRODUCT_STORE, PRODUCT_UPDATE, PRODUCT_NORM };
