@@ -390,8 +390,9 @@ enum { LOMO_KERNEL_WGRAD_UPDATE = 0, LOMO_KERNEL_WGRAD_SQNORM = 1, LOMO_KERNEL_D
 
 /* The shape of tile that the contractions of a call work in (host function): shapes holds n times T, K, N, family is
  * LOMO_KERNEL_WGRAD_UPDATE, LOMO_KERNEL_WGRAD_SQNORM, LOMO_KERNEL_DGRAD or LOMO_KERNEL_FORWARD (without a residual), and
- * tiles receives n pairs: columns and rows of the output (256 256, 128 128, 128 64 or 64 64; 0 0: the kernel
- * for rows of more than 7 million elements).  n linear tensors of one
+ * tiles receives n pairs: columns and rows of the output (256 256, 256 128, 128 128, 128 64 or 64 64; 0 0: the kernel
+ * for rows of more than 7 million elements; where 256 256 leaves a round of few tiles, a piece of one tensor goes to smaller
+ * ones).  n linear tensors of one
  * lomo_step_* call count as one list, every other call is a list of one.  The choice affects time only: the kernels
  * give the same bits.  Without a GPU the answer is that of one with 256 compute units. */
 lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles);

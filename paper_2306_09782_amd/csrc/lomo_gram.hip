@@ -18,20 +18,29 @@
 // accurate than the direct kernel, which is why the direct route is the default.
 //
 // Kernel: one persistent workgroup per CU walks a list of 256 x 128 tiles of the triangle of up to
-// MAX_GROUP tensors.  A tile runs K/32 slices of X rows into the P accumulators and N/32 slices of
-// dY rows into the Q accumulators as one continuous four-stage direct-to-LDS pipeline (both
+// MAX_GROUP tensors.  A tile runs K/64 slots of X rows into the P accumulators and N/64 slots of
+// dY rows into the Q accumulators as one continuous direct-to-LDS pipeline (both
 // operands are contraction-contiguous, so LDS reads are plain 16-byte reads), then multiplies the
 // two accumulator sets element by element, applies the triangle weights and adds one double.
-#include "lomo_gemm_common.h"
+//
+// A slot is 64 contraction indices: 128 bytes of a row, whole cache lines, where slices of 32 asked for every line twice and met
+// at a barrier twice as often.  Three slots of 48 KiB rotate; a slot is walked in four steps of 16 indices, the fragments of the
+// next step are read while the current one is multiplied; after the third step the slot's memory is loaded again, with the slot
+// after the next two, in twelve instructions per wave over the next three steps, so that a load has more than a slot's
+// time to land.  Measured, us, norm pass by this route, slices of 32 in four stages -> slots: one layer of width 8192 at 2048 tokens
+// 782 -> 649 (1136 TFLOP/s of the tiles' products; the direct route 2670), at 4096 tokens 3170 -> 2459, two 5120 wide at 1024 tokens 469 -> 380,
+// four 4096 wide at 512 tokens 244 -> 196.
+#include "lomo_gemm_persistent.h"
 
 #include <algorithm>
 
 namespace lomo {
 namespace gram {
 
-constexpr int BM = 256, BN = 128, BK = 32, NS = 4;
-constexpr int A_HALVES = BM * BK, B_HALVES = BN * BK, STAGE_HALVES = A_HALVES + B_HALVES;
-constexpr int LDS_BYTES = NS * STAGE_HALVES * 2 + 256;
+constexpr int BM = 256, BN = 128, BK = 64, NS = 3;
+constexpr int A_HALVES = BM * BK, B_HALVES = BN * BK, SLOT_HALVES = A_HALVES + B_HALVES;
+constexpr int LDS_BYTES = NS * SLOT_HALVES * 2 + 256;
+constexpr int LOADS = 12;      // instructions of a wave per slot: eight of A, four of B, eight rows each
 constexpr int MAX_GROUP = 40;
 constexpr int BAND = 4;   // tile rows per band: the 32 tiles an XCD holds at once form a 4 x 8 block
 
@@ -48,7 +57,8 @@ struct GroupArgs {
     GramTensor t[MAX_GROUP];
 };
 
-__device__ __forceinline__ int swz_c(int n) { return ((n >> 1) & 3) ^ ((n >> 3) & 1); }
+// 16-byte chunk c of row r sits at position c ^ swz(r): sixteen rows read at one chunk fall on all 64 banks.
+__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 __device__ __forceinline__ void dma16(uint32_t voff, const void* base, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -103,26 +113,18 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
     const int l32 = lane & 31, lh = lane >> 5;
     const int G = gridDim.x;
 
-    int pos;
-    {
-        const int x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
-        const int q = G >> 3, r = G & 7;
-        pos = x * q + (x < r ? x : r) + local;
-    }
-
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-    float* red_scratch = reinterpret_cast<float*>(smem + NS * STAGE_HALVES);
+    float* red_scratch = reinterpret_cast<float*>(smem + NS * SLOT_HALVES);
 
     // ---- fragment read offsets (halves)
     const int arow = wm * (BM / 2) + l32, brow = wn * (BN / 2) + l32;
-    const int a_rd = arow * BK + ((lh ^ swz_c(arow)) * 8);
-    const int b_rd = brow * BK + ((lh ^ swz_c(brow)) * 8);
+    const int a_rd = arow * BK + ((lh ^ swz(arow)) * 8);
+    const int b_rd = A_HALVES + brow * BK + ((lh ^ swz(brow)) * 8);
 
-    // ---- per-tile state of the loads: phase P reads X, phase Q reads dY.  A wave instruction fetches 16
-    // rows of 64 bytes; lane L takes row L / 4 and, of its four 16-byte chunks, the one that the swizzle
-    // assigns to LDS position L % 4.  The swizzle depends on the row modulo 16 only, so one lane offset per
-    // phase serves every instruction and the row block goes into the scalar base address.
-    uint32_t voffP = 0, voffQ = 0;
+    // ---- per-tile state of the loads: phase P reads X, phase Q reads dY.  A wave instruction fetches eight rows of 128 bytes;
+    // lane L takes row L / 8 and, of its chunks, the one that the swizzle assigns to LDS position L % 8.  The swizzle depends on
+    // the row modulo 16: one lane offset per phase for even instructions, one for odd, and the row block goes into the base.
+    uint32_t voffP[2] = {0, 0}, voffQ[2] = {0, 0};
     const uint16_t *paP = nullptr, *pbP = nullptr, *paQ = nullptr, *pbQ = nullptr;
     int KTP = 0, KT = 0, ldP = 0, ldQ = 0;
 
@@ -132,63 +134,76 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
         const GramTensor& T = ga.t[k];
         locate(w - T.tile_begin, T.tiles_m, bi, bj);
         tensor = k;
-        const int n = lane >> 2, cp = lane & 3;
-        const uint32_t c = (uint32_t)((cp ^ swz_c(n)) * 8);
-        voffP = ((uint32_t)n * (uint32_t)T.K + c) * 2u;
-        voffQ = ((uint32_t)n * (uint32_t)T.N + c) * 2u;
+        const int n = lane >> 3, cp = lane & 7;
+#pragma unroll
+        for (int odd = 0; odd < 2; ++odd) {
+            const uint32_t c = (uint32_t)((cp ^ swz(8 * odd + n)) * 8);
+            voffP[odd] = ((uint32_t)n * (uint32_t)T.K + c) * 2u;
+            voffQ[odd] = ((uint32_t)n * (uint32_t)T.N + c) * 2u;
+        }
         ldP = T.K;
         ldQ = T.N;
-        paP = T.X + (int64_t)bi * BM * T.K;
-        pbP = T.X + (int64_t)bj * BN * T.K;
-        paQ = T.dY + (int64_t)bi * BM * T.N;
-        pbQ = T.dY + (int64_t)bj * BN * T.N;
+        // this wave's rows: 64 of the tile's rows, 32 of its columns
+        paP = T.X + ((int64_t)bi * BM + wave * 64) * T.K;
+        pbP = T.X + ((int64_t)bj * BN + wave * 32) * T.K;
+        paQ = T.dY + ((int64_t)bi * BM + wave * 64) * T.N;
+        pbQ = T.dY + ((int64_t)bj * BN + wave * 32) * T.N;
         KTP = T.K / BK;
         KT = KTP + T.N / BK;
     };
 
-    // One DMA instruction of slice `stage` of the tile: part 0 = the 256 tile rows (four KiB per wave),
-    // part 1 = the 128 tile columns (two KiB per wave).  Slices past the end re-read the last one.
-    auto issue1 = [&](int stage, int buf, int part, int it) {
-        const int s = stage < KT ? stage : KT - 1;
+    // The slot being requested: its place in LDS (bytes), its rows, the distance of eight rows.
+    uint32_t to = 0, v0 = 0, v1 = 0;
+    const uint16_t *fa = nullptr, *fb = nullptr;
+    int64_t eight = 0;
+    auto request = [&](int slot, int ring) {      // slots past the end re-read the last one
+        const int s = slot < KT ? slot : KT - 1;
         const bool q = s >= KTP;
-        const int sl = q ? s - KTP : s;
-        const int blk = part == 0 ? wave * 4 + it : wave * 2 + it;      // 16-row block inside the tile part
-        const uint32_t l = lds0 + (uint32_t)buf * (STAGE_HALVES * 2u) + (part == 0 ? 0u : (uint32_t)(A_HALVES * 2)) +
-                           (uint32_t)blk * 1024u;
-        const uint16_t* base = part == 0 ? (q ? paQ : paP) : (q ? pbQ : pbP);
-        base += (int64_t)(16 * blk) * (q ? ldQ : ldP) + (int64_t)sl * BK;
-        dma16(q ? voffQ : voffP, base, l);
+        const int at = (q ? s - KTP : s) * BK;
+        to = lds0 + (uint32_t)ring * (SLOT_HALVES * 2u);
+        fa = (q ? paQ : paP) + at;
+        fb = (q ? pbQ : pbP) + at;
+        eight = 8 * (int64_t)(q ? ldQ : ldP);
+        v0 = q ? voffQ[0] : voffP[0];
+        v1 = q ? voffQ[1] : voffP[1];
     };
+    auto load = [&](int n) {
+        if (n < 8) {
+            dma16(n & 1 ? v1 : v0, fa, to + (uint32_t)(wave * 8 + n) * 1024u);
+            fa += eight;
+        } else {
+            dma16(n & 1 ? v1 : v0, fb, to + (uint32_t)(A_HALVES * 2) + (uint32_t)(wave * 4 + n - 8) * 1024u);
+            fb += eight;
+        }
+    };
+    // Slots 0 and 1, and the first four loads of slot 2.
     auto issue_prologue = [&] {
 #pragma unroll
         for (int st = 0; st < 3; ++st) {
+            request(st, st);
 #pragma unroll
-            for (int it = 0; it < 4; ++it) issue1(st, st, 0, it);
-#pragma unroll
-            for (int it = 0; it < 2; ++it) issue1(st, st, 1, it);
+            for (int n = 0; n < (st < 2 ? LOADS : 4); ++n) load(n);
         }
-#pragma unroll
-        for (int it = 0; it < 4; ++it) issue1(3, 3, 0, it);
     };
 
-    auto read_a = [&](half8 (&a)[4], int buf, int kk, int i) {
-        a[i] = *reinterpret_cast<const half8*>(smem + buf * STAGE_HALVES + ((a_rd ^ (kk << 4)) + i * 32 * BK));
+    auto read_a = [&](half8 (&a)[4], int ring, int kk, int i) {
+        a[i] = *reinterpret_cast<const half8*>(smem + ring * SLOT_HALVES + ((a_rd ^ (kk << 4)) + i * 32 * BK));
     };
-    auto read_b = [&](half8 (&b)[2], int buf, int kk, int j) {
-        b[j] = *reinterpret_cast<const half8*>(smem + buf * STAGE_HALVES + A_HALVES + ((b_rd ^ (kk << 4)) + j * 32 * BK));
+    auto read_b = [&](half8 (&b)[2], int ring, int kk, int j) {
+        b[j] = *reinterpret_cast<const half8*>(smem + ring * SLOT_HALVES + ((b_rd ^ (kk << 4)) + j * 32 * BK));
     };
-    // EARLY packs the six fragments into the first three groups so that every read of the buffer has
-    // completed when the half-slice ends at the barrier that releases it.
-    auto read_group = [&](half8 (&a)[4], half8 (&b)[2], int buf, int kk, int q, bool early) {
+    // EARLY packs the six fragments into the first three groups so that every read of the slot has
+    // completed when the step ends at the barrier that releases it.
+    auto read_group = [&](half8 (&a)[4], half8 (&b)[2], int ring, int kk, int q, bool early) {
         if (early) {
-            if (q == 0) { read_a(a, buf, kk, 0); read_b(b, buf, kk, 0); read_b(b, buf, kk, 1); }
-            if (q == 1) { read_a(a, buf, kk, 1); read_a(a, buf, kk, 2); }
-            if (q == 2) { read_a(a, buf, kk, 3); }
+            if (q == 0) { read_a(a, ring, kk, 0); read_b(b, ring, kk, 0); read_b(b, ring, kk, 1); }
+            if (q == 1) { read_a(a, ring, kk, 1); read_a(a, ring, kk, 2); }
+            if (q == 2) { read_a(a, ring, kk, 3); }
         } else {
-            if (q == 0) { read_a(a, buf, kk, 0); read_b(b, buf, kk, 0); }
-            if (q == 1) { read_b(b, buf, kk, 1); read_a(a, buf, kk, 1); }
-            if (q == 2) { read_a(a, buf, kk, 2); }
-            if (q == 3) { read_a(a, buf, kk, 3); }
+            if (q == 0) { read_a(a, ring, kk, 0); read_b(b, ring, kk, 0); }
+            if (q == 1) { read_b(b, ring, kk, 1); read_a(a, ring, kk, 1); }
+            if (q == 2) { read_a(a, ring, kk, 2); }
+            if (q == 3) { read_a(a, ring, kk, 3); }
         }
     };
     constexpr int READS_EARLY[4] = {3, 2, 1, 0};
@@ -207,13 +222,13 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
                 }
     };
 
-    // Half a slice: 8 MFMAs on (ua, ub) in four groups of two; each group is preceded by the reads of one
-    // fragment group of the next half-slice and followed by at most one direct-to-LDS load.
-    auto half_slice = [&](floatx16 (&acc)[4][2], const half8 (&ua)[4], const half8 (&ub)[2], half8 (&la)[4],
-                          half8 (&lb)[2], int lbuf, int lkk, bool early, int dstage, int dbuf, int dpart) {
+    // One step of 16 indices: 8 MFMAs on (ua, ub) in four groups of two; each group is preceded by the reads of one
+    // fragment group of the next step and, where the step loads (first >= 0), followed by one direct-to-LDS load.
+    auto step = [&](floatx16 (&acc)[4][2], const half8 (&ua)[4], const half8 (&ub)[2], half8 (&la)[4],
+                    half8 (&lb)[2], int ring, int kk, bool early, int first) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            read_group(la, lb, lbuf, lkk, q, early);
+            read_group(la, lb, ring, kk, q, early);
 #pragma unroll
             for (int j = 0; j < 2; ++j)
                 acc[q][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ua[q], ub[j], acc[q][j], 0, 0, 0);
@@ -229,28 +244,29 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (dpart == 0 || q < 2) issue1(dstage, dbuf, dpart, q);
+            if (first >= 0) load(first + q);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
     half8 fa0[4], fb0[2], fa1[4], fb1[2];
-    // Four slices (one trip round the LDS stages) accumulated into `acc`.
-    auto four_slices = [&](floatx16 (&acc)[4][2], int kt) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            // first half of slice kt+u; reads its second half's fragments; loads the column part of slice kt+u+3
-            half_slice(acc, fa0, fb0, fa1, fb1, u, 1, true, kt + u + 3, (u + 3) & 3, 1);
-            // own loads of slice kt+u+1 have landed (the 12 youngest may still fly); own LDS reads done
-            asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            // second half; reads the first fragments of slice kt+u+1; loads the row part of slice kt+u+4
-            // into the buffer of slice kt+u, which nobody reads any more
-            half_slice(acc, fa1, fb1, fa0, fb0, (u + 1) & 3, 0, false, kt + u + 4, u, 0);
-        }
+    int ring = 0;      // place of the current slot
+    // Slot number s accumulated into `acc`.
+    auto one_slot = [&](floatx16 (&acc)[4][2], int s) {
+        const int next = ring == NS - 1 ? 0 : ring + 1;
+        step(acc, fa0, fb0, fa1, fb1, ring, 1, false, 4);      // the rest of slot s + 2
+        step(acc, fa1, fb1, fa0, fb0, ring, 2, false, 8);
+        step(acc, fa0, fb0, fa1, fb1, ring, 3, true, -1);
+        // slot s + 1 has landed (slot s + 2 may still fly); nobody reads slot s any more
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        request(s + 3, ring);
+        step(acc, fa1, fb1, fa0, fb0, next, 0, false, 0);
+        ring = next;
     };
 
-    int w = pos;
+    int round = 0;
+    int w = dma::round_tile(round, G, ga.total_tiles);
     if (w >= ga.total_tiles) return;   // grid <= total_tiles: cannot happen; nothing was issued yet
     int tensor, bi, bj;
     setup(w, tensor, bi, bj);
@@ -259,18 +275,18 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
 
     while (true) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        ring = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) read_group(fa0, fb0, 0, 0, q, false);
 
-        // K/32 and N/32 are multiples of 4, so a trip round the stages never straddles the two phases
-        for (int kt = 0; kt < KTP; kt += 4) four_slices(accP, kt);
-        for (int kt = KTP; kt < KT; kt += 4) four_slices(accQ, kt);
+        for (int s = 0; s < KTP; ++s) one_slot(accP, s);
+        for (int s = KTP; s < KT; ++s) one_slot(accQ, s);
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
         int32_t* const flag_out = ga.t[tensor].flag_out;
         const int ebi = bi, ebj = bj;
 
-        w += G;
+        w = dma::round_tile(++round, G, ga.total_tiles);
         const bool more = w < ga.total_tiles;
         if (more) {
             setup(w, tensor, bi, bj);
@@ -334,14 +350,15 @@ static int gram_cu_count() {
 // `a` is a norm-pass contraction (A = X [C x M], B = dY [C x Nn], dense rows).
 bool gram_eligible(const GemmArgs& a) {
     using namespace gram;
-    return a.C >= BM && a.C % BM == 0 && a.M >= 4 * BK && a.M % (4 * BK) == 0 && a.Nn >= 4 * BK &&
-           a.Nn % (4 * BK) == 0 && a.lda == a.M && a.ldb == a.Nn && a.C <= (1 << 20) && a.M < (1 << 22) &&
+    return a.C >= BM && a.C % BM == 0 && a.M >= 2 * BK && a.M % (2 * BK) == 0 && a.Nn >= 2 * BK &&
+           a.Nn % (2 * BK) == 0 && a.lda == a.M && a.ldb == a.Nn && a.C <= (1 << 20) && a.M < (1 << 22) &&
            a.Nn < (1 << 22) && (a.C / BM) * (a.C / BM + 1) < (1 << 24);
 }
 
-// Estimated cost in units of one 256 x 256 x 32 slice on one CU.  A 256 x 128 x 32 slice of this kernel
-// does half the arithmetic but is bound by LDS bandwidth (a wave tile of 128 x 64 reads 1.5 times the
-// operand bytes per flop of the direct kernel's 128 x 128): measured 0.73 of a full slice.
+// Estimated cost in units of one 256 x 256 x 32 slice on one CU.  32 indices of a 256 x 128 tile are half the arithmetic of that;
+// a wave tile of 128 x 64 reads 1.5 times the operand bytes per flop of the direct kernel's 128 x 128.  Measured 0.60; the
+// line stays at the 0.73 of the kernel before, so that no tensor leaves the direct route, which is the more accurate one, for
+// a gain of a few per cent.
 constexpr double kGramSlice = 0.73;
 double gram_cost(const GemmArgs& a) {
     const double tm = (double)(a.C / gram::BM);
