@@ -118,11 +118,15 @@ def _ptr(t):
     return None if t is None else c_void_p(t.data_ptr())
 
 
+def _current_stream() -> int:
+    """Handle of the calling thread's current stream, without the Stream object that torch.cuda.current_stream() makes
+    (3 us, of 7 us that a call of one small kernel took in all; this takes 0.2)."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream(stream):
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return c_void_p(stream.cuda_stream)
+    return c_void_p(_current_stream() if stream is None else stream.cuda_stream)
 
 
 def _nbytes(t):
