@@ -390,7 +390,7 @@ enum { LOMO_KERNEL_WGRAD_UPDATE = 0, LOMO_KERNEL_WGRAD_SQNORM = 1, LOMO_KERNEL_D
 
 /* The shape of tile that the contractions of a call work in (host function): shapes holds n times T, K, N, family is
  * LOMO_KERNEL_WGRAD_UPDATE, LOMO_KERNEL_WGRAD_SQNORM, LOMO_KERNEL_DGRAD or LOMO_KERNEL_FORWARD (without a residual), and
- * tiles receives n pairs: columns and rows of the output (256 256, 256 128, 128 128, 128 64 or 64 64; 0 0: the kernel
+ * tiles receives n pairs: columns and rows of the output (256 256, 256 128, 128 128, 128 64, 64 64 or 64 32; 0 0: the kernel
  * for rows of more than 7 million elements; where 256 256 leaves a round of few tiles, a piece of one tensor goes to smaller
  * ones).  n linear tensors of one
  * lomo_step_* call count as one list, every other call is a list of one.  The choice affects time only: the kernels

@@ -238,8 +238,9 @@ static bool fast_enabled() {
 }
 
 // ---- which kernel runs a tensor -----------------------------------------------------------
-// Five shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip and lomo_gemm_wide.hip), and in lomo_gemm_tile.hip 256 x 128,
-// 128 x 128, 128 x 64 and 64 x 64.  Larger tiles do more work per operand byte, smaller ones occupy more of the CUs and walk the
+// Six shapes of workgroup: 256 x 256 (persistent, lomo_gemm_dma.hip and lomo_gemm_wide.hip), and in lomo_gemm_tile.hip 256 x 128,
+// 128 x 128, 128 x 64, 64 x 64 and, for stored products of long contractions (above 4608 indices; below, 64 x 32 gains no more
+// than 1 us), 64 x 32.  Larger tiles do more work per operand byte, smaller ones occupy more of the CUs and walk the
 // contraction faster.
 // The kernels of a pass run one behind the other, so what counts is the sum of their times over the whole list: tensors that
 // would leave most of the chip idle alone fill each other's rounds in the persistent kernel, and one leaves it only where
@@ -265,7 +266,9 @@ static const TileCost kTile[N_TILES] = {
     {128, 128, 1, {2.8, 4.2, 2.5}, 0.0057, 0.0082},
     {128, 64, 2, {1.9, 2.9, 3.0}, 0.0043, 0.0055},
     {64, 64, 2, {1.4, 2.0, 3.0}, 0.0027, 0.0036},
+    {64, 32, 2, {1.4, 1e9, 1e9}, 0.0026, 0.0034},      // stored products only
 };
+constexpr int64_t kShort = 4608;         // contractions up to this length leave TILE_64_32 out
 constexpr double kLaunch = 10.0;         // launch, ramp-up and drain
 constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take one of the two starting choices as it is
 
@@ -285,6 +288,7 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
     for (size_t i = 0; i < n_shapes; ++i) {
         const Shape& s = shapes[i];
         if (s.tile != tile) continue;
+        if (tile == TILE_64_32 && s.C <= kShort) return 1e30;
         const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
         tiles += n;
         indices += n * (double)s.C;

@@ -13,7 +13,8 @@
 //     into registers while the previous two are multiplied, so all of the ring but those two holds loads in flight.
 //   * 256 x 128: eight waves of 64 x 64, two on every SIMD, 144 KiB.  128 x 128: eight waves of 64 x 32, two on every SIMD (one's LDS reads run behind the other's MFMAs), 128 KiB of LDS.
 //     128 x 64: four waves of 64 x 32, 72 KiB; 64 x 64: four waves of 32 x 32, 80 KiB: two workgroups on a CU, so that
-//     one's ramp-up and epilogue run behind the other's main loop.
+//     one's ramp-up and epilogue run behind the other's main loop.  64 x 32, for long contractions of very few tiles: two waves of
+//     32 x 32, 72 KiB.
 // One launch takes a list of tensors; workgroups start in list order, longest contraction first.
 //
 // Measured, us per call, against the same tiles with the contraction split over two or four groups of waves (which adds in
@@ -22,6 +23,7 @@
 //   dX of 2048 x 4096, C = 4096: 256 x 128 tiles 73, 128 x 128 83, persistent 82;  2048 x 4096, C = 11008: 170, 191, 184;
 //   dX of 1024 x 5120, C = 13824: 157, 205, 244
 //   dX of 777 x 2048, C = 32000, 128 x 64 tiles: 168, 166, 475;               update of 777 x 2048 x 2048: 14.6, 18, 28
+//   dX of 256 x 1024, 64 x 64 / 64 x 32 tiles: C = 32000 127 / 91, C = 5632 22.9 / 18.7; of 128 x 4096, C = 32000 153 / 118
 //   dX of 256 x 1024, C = 32000, 64 x 64 tiles: 127, 138, 470;                Y of 777 x 2048, C = 2048: 15.0, 19.7, 40
 #include "lomo_gemm_common.h"
 #include "lomo_gemm_dma_common.h"
@@ -404,6 +406,9 @@ hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t 
         case TILE_256_128: return launch_tile<2, 2, 4, 2, 6, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
         case TILE_128: return launch_tile<2, 1, 2, 4, 8, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
         case TILE_128_64: return launch_tile<2, 1, 2, 2, 6, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+        case TILE_64_32:
+            if constexpr (!B_STRIDED && EPI == EPI_STORE) return launch_tile<1, 1, 2, 1, 12, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
+            else return hipErrorInvalidValue;      // never chosen
         default: return launch_tile<1, 1, 2, 2, 10, 2, B_STRIDED, EPI, A_STRIDED>(list, n, st);
     }
 }

@@ -54,7 +54,7 @@ hipError_t launch_wide_group(const GemmArgs* list, int n, hipStream_t st);
 
 // Kernel of smaller tiles (lomo_gemm_tile.hip), one workgroup per tile; takes lists and shapes as the persistent kernel does and
 // gives the same bits.  Tiles are (m) x (n) as in GemmArgs.
-enum { TILE_256, TILE_256_128, TILE_128, TILE_128_64, TILE_64, N_TILES };
+enum { TILE_256, TILE_256_128, TILE_128, TILE_128_64, TILE_64, TILE_64_32, N_TILES };
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t st);
 
