@@ -247,30 +247,40 @@ static bool fast_enabled() {
 // that makes the pass shorter (a long contraction with few tiles).  All kernels give the same bits, so the list a tensor
 // comes in does not show in its result.
 //
-// The times, in microseconds, are fitted to 270 shapes of output and contraction (128 to 8192 tokens of layers 1024 to 8192 wide
-// and their vocabularies) in each kernel and product: root mean square error 4 to 13 %; choosing by them costs 0.1 to 0.3 % on
-// average over the best kernel of each.  A tile takes a fixed part (ramp-up and epilogue) and a part per contraction index; the
-// latter is at least `latency` and, with every CU busy, `through` for each tile that a CU has.  Measured at C = 4096, dX (us; in
-// the order of the table): 1024 x 4096 outputs 67, 47, 38, 47, 57;   2048 x 4096: 83, 73, 83, -, -;   4096 x 4096: 108, 130, 132, 166, 222.
+// A tile takes a fixed part (ramp-up and epilogue) and a part per contraction index; the latter is at least `latency` and, with
+// every CU busy, `through` for each tile that a CU has.  Times in microseconds.
+//   * Gradients: fitted to 270 shapes of output and contraction (128 to 8192 tokens of layers 1024 to 8192 wide and their
+//     vocabularies); root mean square error 4 to 13 %, choosing by them costs 0.1 to 0.3 % on average over the best kernel of each.
+//   * Stored products read weights, which come from HBM in every pass of a model larger than the Infinity Cache, and a workgroup
+//     that waits for HBM takes 1.2 to 1.4 times as long per index: about 2.4 ns for each 128-byte line that its CU fetches, against
+//     1.75 ns from the cache.  A ring twice as deep does not change that (128 x 64, 128 x 128, 64 x 64 and 64 x 32 tiles of 64 to 1024
+//     tokens, one workgroup on a CU: all within 1 %), fewer lines per index and more CUs do.  So they are fitted to products that
+//     go through 2 GiB of weights in turn, 77 shapes of 64 to 1024 tokens; there the choice is the fastest tile of every shape
+//     (with the times from warm weights 2.4 % above it on average, 36 % at the worst: dX of 512 x 13824, C = 5120, 116 against 85).
+//   * 256 x 128 tiles take the same time as the persistent kernel over several rounds, but more power: dX of a 13B layer at 874
+//     tokens 655 us either way, while the norm and the update behind it go from 546 and 657 to 574 and 700.  `through` of 0.0166
+//     instead of the fitted 0.0142 leaves such lists to the persistent kernel (the pass 1900 -> 1855 us).
+// dX at C = 4096, warm, in the order of the table: 1024 x 4096 outputs 67, 47, 38, 47, 57;   2048 x 4096: 83, 73, 83, -, -;
+// 4096 x 4096: 108, 130, 132, 166, 222.
 // Lists, measured with all of one shape of tile against the choice by each tensor alone (dX, us): 7B layers at 1024
 // tokens 1528 against 1960 for four, at 2048 tokens 2647 against 3642; 24 layers of width 1024 at 2048 tokens 1443 against
 // 2077, their updates 1219 against 1826.
 struct TileCost {
     int m, n, per_cu;             // tile; workgroups that a CU holds
     double fixed[3];              // by Product
-    double latency, through;
+    double latency[2], through[2];      // gradients; stored products, whose weights come from HBM in every pass
 };
 static const TileCost kTile[N_TILES] = {
-    {256, 256, 1, {3.0, 10.0, 4.1}, 0.0140, 0.0244},
-    {256, 128, 1, {6.0, 8.5, 5.2}, 0.0098, 0.0158},
-    {128, 128, 1, {2.8, 4.2, 2.5}, 0.0057, 0.0082},
-    {128, 64, 2, {1.9, 2.9, 3.0}, 0.0043, 0.0055},
-    {64, 64, 2, {1.4, 2.0, 3.0}, 0.0027, 0.0036},
-    {64, 32, 2, {1.4, 1e9, 1e9}, 0.0026, 0.0034},      // stored products only
+    {256, 256, 1, {3.0, 10.0, 4.1}, {0.0140, 0.0174}, {0.0244, 0.0244}},
+    {256, 128, 1, {7.0, 8.5, 5.2}, {0.0098, 0.0114}, {0.0158, 0.0166}},
+    {128, 128, 1, {2.8, 4.2, 2.5}, {0.0057, 0.0075}, {0.0082, 0.0091}},
+    {128, 64, 2, {1.9, 2.9, 3.0}, {0.0043, 0.0061}, {0.0055, 0.0062}},
+    {64, 64, 2, {1.4, 2.0, 3.0}, {0.0027, 0.0046}, {0.0036, 0.0045}},
+    {64, 32, 2, {1.4, 1e9, 1e9}, {0.0026, 0.0042}, {0.0034, 0.0037}},      // stored products only
 };
 constexpr int64_t kShort = 4608;         // contractions up to this length leave TILE_64_32 out
 constexpr double kLaunch = 10.0;         // launch, ramp-up and drain
-constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take one of the two starting choices as it is
+constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take one of the starting choices as it is
 
 namespace {
 struct Shape {
@@ -296,6 +306,7 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
     }
     if (tiles == 0.0) return 0.0;
     const double per_cu = tiles / cus, mean = indices / tiles, f = k.fixed[product];
+    const double latency = k.latency[product == PRODUCT_STORE], through = k.through[product == PRODUCT_STORE];
     if (tile == TILE_256) {
         // A workgroup walks one tile per round, so a round takes as long as its first tile; a round that is not full takes less
         // (a tile is faster when it has the memory system to itself).
@@ -306,8 +317,8 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
             const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
             const double from = ceil(seen / cus), to = ceil((seen + n) / cus);      // the rounds that begin with this shape
             const double full = std::max(0.0, std::min(to, floor(per_cu)) - from);
-            time += full * (f + k.through * (double)s.C);
-            if (to - from > full) time += f + (k.latency + (k.through - k.latency) * (per_cu - floor(per_cu))) * (double)s.C;
+            time += full * (f + through * (double)s.C);
+            if (to - from > full) time += f + (latency + (through - latency) * (per_cu - floor(per_cu))) * (double)s.C;
             seen += n;
         }
         return time;
@@ -317,8 +328,8 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
     const double waves = ceil(per_cu / k.per_cu);
     // the longest walk of a mixed list goes on alone when the rest is done
     const double busy = std::min(longest, mean * per_cu);
-    return kLaunch + std::max(waves * f + mean * std::max(k.latency * waves, k.through * rounds),
-                              f + (longest > mean ? k.through * busy + k.latency * (longest - busy) : longest * std::max(k.latency, 0.7 * k.through)));
+    return kLaunch + std::max(waves * f + mean * std::max(latency * waves, through * rounds),
+                              f + (longest > mean ? through * busy + latency * (longest - busy) : longest * std::max(latency, 0.7 * through)));
 }
 
 // Contraction indices of the longest walk when the persistent kernels take a list in this order: tile t of a round goes to the
@@ -367,8 +378,9 @@ static int best_alone(Shape one, int product, double cus) {
     return to;
 }
 
-// Two starting choices, all tensors in the persistent kernel and each in the one that is best for it alone; from both, one
-// shape after the other (longest contraction first) moves to where the pass is shortest.
+// Starting choices: all tensors in the persistent kernel, all in the shape of tile that is best for all together, and each in the
+// one that is best for it alone; from each, one shape after the other (longest contraction first) moves to where the pass is
+// shortest.
 void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     const double cus = (double)cu_count();
     std::vector<Shape> shapes;
@@ -406,7 +418,32 @@ void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     };
     std::vector<Shape> alone = shapes;
     for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0, s.fixed}, product, cus);
-    if (shapes.size() == 1 || improve(alone) < improve(shapes)) shapes.swap(alone);
+    if (shapes.size() > 1) {
+        std::vector<Shape> same_tile = shapes;
+        auto all_in = [&](int tile) {
+            for (Shape& s : same_tile) s.tile = s.fixed ? TILE_256 : tile;
+            return pass_time(same_tile, product, cus);
+        };
+        int uniform = TILE_256;
+        double best = all_in(TILE_256);
+        for (int tile = TILE_256 + 1; tile < N_TILES; ++tile) {
+            const double t = all_in(tile);
+            if (t < best) {
+                best = t;
+                uniform = tile;
+            }
+        }
+        all_in(uniform);
+        const double in_one = uniform == TILE_256 ? 1e30 : improve(same_tile);
+        best = improve(shapes);
+        if (in_one < best) {
+            best = in_one;
+            shapes.swap(same_tile);
+        }
+        if (improve(alone) < best) shapes.swap(alone);
+    } else {
+        shapes.swap(alone);
+    }
     for (size_t i = 0; i < n; ++i)
         tile_of[i] = std::find_if(shapes.begin(), shapes.end(), [&](const Shape& s) { return same(s, list[i]); })->tile;
 }
