@@ -27,12 +27,14 @@ constexpr int LDS_BYTES = 2 * PAIR * 2;      // two pairs
 constexpr float SCALE = 0.08838834764831845f;      // 1 / sqrt(128)
 constexpr float LOG2E = 1.4426950408889634f;
 
-__device__ __forceinline__ half8 read_tr8(const uint16_t* p0, const uint16_t* p1) {
-    typedef __attribute__((address_space(3))) short4a* lds_p;
-    const short4a lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p0));
-    const short4a hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(p1));
+typedef __attribute__((address_space(3))) short4a* lds_p;
+// at LDS addresses
+__device__ __forceinline__ half8 read_tr8(uint32_t p0, uint32_t p1) {
+    const short4a lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)p0);
+    const short4a hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)p1);
     return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
+__device__ __forceinline__ half8 read8(uint32_t p) { return *(__attribute__((address_space(3))) const half8*)p; }
 
 // Chunk swizzle of the [64 x 128] tiles: 16-byte chunk c of row r sits at position c ^ swz(r).  Rows that
 // differ in their low two bits are 4 chunks apart (the four rows of a transposing read fall on disjoint banks,
@@ -64,36 +66,36 @@ struct TileLoad {
     }
 };
 
-// Fragment reads from a tile.  The places of the fragments differ in a few low bits; they are formed again for every tile
-// (one instruction each), which costs less than keeping them in registers.
+// Fragment reads from a tile, by LDS address (of tiles that begin at multiples of 256 bytes).  The places of the fragments differ
+// in a few low bits; they are formed again for every tile (one instruction each), which costs less than keeping them in registers.
 struct TileRead {
-    int row_rd, tr0, tr1;
-    __device__ __forceinline__ TileRead() {
+    uint32_t row_rd, tr0, tr1;
+    __device__ __forceinline__ TileRead(uint32_t tile) {
         const int lane = threadIdx.x & 63;
         const int l32 = lane & 31, lh = lane >> 5;
         const int g4 = lane >> 4, j16 = lane & 15;
         const int mhalf = g4 & 1, kh = g4 >> 1, rib = j16 >> 2, piece = j16 & 3;
         const int tr_row = 8 * kh + rib, tr_col = 16 * mhalf + 4 * piece;
-        row_rd = l32 * D + ((8 * lh) ^ (swz(l32) << 3));
-        tr0 = tr_row * D + (tr_col ^ (swz(tr_row) << 3));
-        tr1 = (tr_row + 4) * D + (tr_col ^ (swz(tr_row + 4) << 3));
+        row_rd = tile + 2u * (uint32_t)(l32 * D + ((8 * lh) ^ (swz(l32) << 3)));
+        tr0 = tile + 2u * (uint32_t)(tr_row * D + (tr_col ^ (swz(tr_row) << 3)));
+        tr1 = tile + 2u * (uint32_t)((tr_row + 4) * D + (tr_col ^ (swz(tr_row + 4) << 3)));
     }
     // the same for a tile `halves` further on
     __device__ __forceinline__ TileRead at(int halves) const {
         TileRead t = *this;
-        t.row_rd += halves;
-        t.tr0 += halves;
-        t.tr1 += halves;
+        t.row_rd += 2u * (uint32_t)halves;
+        t.tr0 += 2u * (uint32_t)halves;
+        t.tr1 += 2u * (uint32_t)halves;
         asm volatile("" : "+v"(t.row_rd), "+v"(t.tr0), "+v"(t.tr1));
         return t;
     }
+    // `off`: halves from the tile of this to the one that is read.
     // rows 0 .. 31, columns 16 ks .. + 15: a lane holds eight consecutive columns of its row
-    __device__ __forceinline__ half8 rows(const uint16_t* tile, int ks) const {
-        return *reinterpret_cast<const half8*>(tile + (row_rd ^ (16 * ks)));
-    }
+    __device__ __forceinline__ half8 rows(int off, int ks) const { return read8((row_rd ^ (uint32_t)(32 * ks)) + 2u * (uint32_t)off); }
     // columns 32 i .. + 31, rows 16 ks .. + 15: a lane holds eight consecutive rows of its column
-    __device__ __forceinline__ half8 columns(const uint16_t* tile, int i, int ks) const {
-        return read_tr8(tile + ((tr0 ^ (32 * i)) + 16 * ks * D), tile + ((tr1 ^ (32 * i)) + 16 * ks * D));
+    __device__ __forceinline__ half8 columns(int off, int i, int ks) const {
+        const uint32_t o = 2u * (uint32_t)(off + 16 * ks * D);
+        return read_tr8((tr0 ^ (uint32_t)(64 * i)) + o, (tr1 ^ (uint32_t)(64 * i)) + o);
     }
 };
 
@@ -165,9 +167,7 @@ __device__ __forceinline__ void add_registers(floatx16 (&acc)[4], const float* l
         for (int r = 0; r < 16; ++r) acc[i][r] += lds[(16 * i + r) * 64];
 }
 
-// Waves of a call that is not split.  Below four per CU (one on every SIMD) forward, below eight backward, a call is split, which
-// halves the longest walk.  Measured, us, not split / split: forward 1 x 1024 tokens, 32 heads (1024 waves) 29.5 / 32, 3 x 320
-// (960) 15.8 / 13.7; backward 88.8 / 78, 50.0 / 40; 8 x 512 (4096) 46 and 145 not split (one kernel before this: 55, 170).
+// Waves of a call that is not split.
 inline int64_t attention_waves(int64_t B, int64_t s, int64_t nh) { return s / 32 * nh * B; }
 
 // Zeros the values of a diagonal block that the mask takes; the branch around it stays one (most blocks have no mask).

@@ -4,22 +4,20 @@
 // the layout the backward kernel reads.
 //
 // One workgroup per (sequence, head, block of queries) walks the key blocks (64 keys) up to the diagonal; a wave owns 32
-// queries, with a running maximum, sum and output accumulator per query.  The score tile is computed transposed (keys are
-// the MFMA rows): a lane owns one query, its maximum is a scan of the lane's registers plus one exchange with lane + 32, and
-// the probabilities become the B operand of o^T += v^T p^T through a v_permlane32_swap.  Probabilities are rounded to fp16
-// relative to the running maximum; accumulation is fp32; o is rounded once.  Deterministic.
-// The first 64 queries of a sequence see so few keys that a probability's rounding shows in their outputs, which are also the
-// largest: in their own block the roundings' remainders are multiplied as well (o is 2.27e-4 off a 64-bit result at 8 x 512 tokens,
-// 2.46e-4 without).  They are 2 of a head's s / 32 waves.
+// queries.  The keys of the even and of the odd halves of the blocks (32 each) have a running maximum, a sum and an output
+// accumulator of their own per query, put together at the end: with two maxima two probabilities of every query are exactly 1, which
+// takes 6 to 10 % off what the roundings of the others do to o.  A workgroup of 128 queries holds both in one wave, one of 64
+// has a wave for each (SPLIT = 2); the operations on a query and their order are the same, so o and lse do not depend on the
+// size of the call.  The score tile is computed transposed (keys are the MFMA rows): a lane owns one query, its maximum is a
+// scan of the lane's registers plus one exchange with lane + 32, and the probabilities become the B operand of o^T += v^T p^T
+// through a v_permlane32_swap.  Probabilities are rounded to fp16 relative to the running maximum; accumulation is fp32; o is rounded
+// once.  Deterministic.
 //
-// Measured, us, against the kernel before (64 queries per workgroup, keys split over the waves, tiles through registers): 1 x 8192
-// tokens, 32 heads 945 -> 772 (713 TFLOP/s); 8 x 1024, 40 heads 236 -> 192; 8 x 512, 32 heads 55 -> 46; 3 x 320 13.1 -> 13.7.  At 8192
-// tokens the matrix pipes are 38 % busy at 1.94 GHz: vector instructions (54 % of the issue slots) and products of a SIMD's two
-// waves overlap only in part, and the clock is already lowered by the power limit.  Not leaving it to chance which wave
-// issues first (s_setprio by the wave's place on its SIMD) changed nothing.
+// Measured, us, against a workgroup of 64 queries with the halves on different waves and tiles through registers: 1 x 8192 tokens, 32 heads
+// 835 -> 681 (808 TFLOP/s); 8 x 1024, 40 heads 211 -> 200; 8 x 512, 32 heads 61 -> 51; 1 x 1024 32 -> 28.5; 3 x 320 13.2 -> 13.8.  (One
+// maximum for both halves: 677, 184, 48, 29.4, 13.4; it rescales the output half as often.)  Vector instructions are the limit:
+// at short sequences most blocks move some query's maximum, which is 128 products a lane beside about 250 for the probabilities.
 #include "lomo_attention_common.h"
-
-#include <type_traits>
 
 namespace lomo {
 
@@ -32,12 +30,14 @@ struct FwdArgs {
     int s, nh, H;
 };
 
+constexpr float C2 = SCALE * LOG2E;
+
 }  // namespace attn
 
 template <int SPLIT>
 __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs a) {
     using namespace attn;
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];      // two pairs of tiles: K, V
+    extern __shared__ __attribute__((aligned(256))) uint16_t smem[];      // two pairs of tiles: K, V
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -59,11 +59,10 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     const uint16_t* gq = a.qkv + (int64_t)n * D;
     const uint16_t* gk = gq + a.H + t0 * ld3;
     const uint16_t* gv = gk + a.H;
-    constexpr float C2 = SCALE * LOG2E;
     const int query = qw + l32;
 
     const TileLoad load(ld3);
-    const TileRead rd;
+    const TileRead rd(lds0);
     auto fetch = [&](int blk, int buf) {
         const int64_t off = (int64_t)blk * BLK * ld3;
         load.issue(gk + off, lds0 + (uint32_t)buf * (PAIR * 2u), wave);
@@ -74,134 +73,139 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     half8 fq[D / 16];
     if (active) load_fragments(fq, gq + (t0 + query) * ld3);
 
-    floatx16 accO[4];
+    // by half of the blocks that this wave has; log2 domain; l_run is this lane's share (its half of the keys)
+    constexpr int STATES = 2 / SPLIT;
+    floatx16 accO[STATES][4];
+    float m_run[STATES], l_run[STATES];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int h = 0; h < STATES; ++h) {
+        m_run[h] = -INFINITY;
+        l_run[h] = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) accO[i][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;      // log2 domain; l_run is this lane's share (its half of the keys)
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) accO[h][i][r] = 0.f;
+    }
 
-    // HALVES x 32 keys of the pair in `buf`, from key 32 h on, against this wave's queries; DIAG: the last 32 of them have the
-    // queries' positions.
-    auto block = [&](int buf, int h0, auto halves_t, auto diag_t) {
-        constexpr int HALVES = decltype(halves_t)::value;
-        constexpr bool DIAG = decltype(diag_t)::value;
-        const TileRead r0 = rd.at(buf * PAIR + 32 * h0 * D);
-        floatx16 S[HALVES];
+    // Scores of keys 32 h .. + 31 of the pair in `buf` against this wave's queries.
+    auto scores = [&](const TileRead& r0, floatx16& S) {
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h)
+        for (int r = 0; r < 16; ++r) S[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) S[h][r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks)
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h) S[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(smem + 32 * h * D, ks), fq[ks], S[h], 0, 0, 0);
-        // S[h][r] <-> key 32 (h0 + h) + 8 (r / 4) + 4 lh + r % 4 of the block
-        float bmax = -INFINITY;
-#pragma unroll
-        for (int h = 0; h < HALVES; ++h)
+        for (int ks = 0; ks < D / 16; ++ks) S = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.rows(0, ks), fq[ks], S, 0, 0, 0);
+    };
+    // What they add to sum and output; diag: the block has the queries' positions among its own.
+    auto half = [&](const TileRead& r0, int h, floatx16& S, floatx16 (&O)[4], float& m_run, float& l_run, bool diag) {
+        // S[r] <-> key 32 h + 8 (r / 4) + 4 lh + r % 4 of the block
+        float scale = C2, bmax = -INFINITY;
+        if (diag) {      // scaled and masked; the branch stays one
+            scale = 1.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                if (DIAG && h == HALVES - 1 && 8 * (r >> 2) + 4 * lh + (r & 3) > l32) S[h][r] = -INFINITY;
-                bmax = fmaxf(bmax, S[h][r]);
+                float x = 32 * h + 8 * (r >> 2) + 4 * lh + (r & 3) > (qw & 32) + l32 ? -INFINITY : S[r] * C2;
+                asm volatile("" : "+v"(x));
+                S[r] = x;
             }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, S[r]);
         {
             typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
             const u32x2v sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bmax), __float_as_uint(bmax), false, false);
             bmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
         }
-        const float m_new = fmaxf(m_run, bmax * C2);
-        const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;      // a query whose scores are all -inf so far
+        const float m_new = fmaxf(m_run, bmax * scale);
+        const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;      // a query that has seen no key yet
+        float alpha = 1.f;
         if (__any(m_new > m_run)) {
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
-            l_run *= alpha;
+            alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) accO[i][r] *= alpha;
+                for (int r = 0; r < 16; ++r) O[i][r] *= alpha;
             m_run = m_new;
         }
         float psum = 0.f;
+        uint32_t pk[8];
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) {
-            uint32_t pk[8];
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                S[h][r] = __builtin_amdgcn_exp2f(fmaf(S[h][r], C2, -m_ref));
-                S[h][r + 1] = __builtin_amdgcn_exp2f(fmaf(S[h][r + 1], C2, -m_ref));
-                psum += S[h][r] + S[h][r + 1];
-                pk[r >> 1] = pack2(S[h][r], S[h][r + 1]);
-            }
-            // o^T[dcol][query] += v^T[dcol][key] p^T[key][query], 16 keys at a time
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const half8 fp = fragment_of(pk, ks);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    accO[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(smem + TILE, i, 2 * h + ks), fp, accO[i], 0, 0, 0);
-            }
-            if constexpr (DIAG) {
-                if (qw < BLK) {      // the roundings' remainders
-#pragma unroll
-                    for (int r = 0; r < 16; r += 2) pk[r >> 1] = pack2(S[h][r] - (float)(_Float16)S[h][r], S[h][r + 1] - (float)(_Float16)S[h][r + 1]);
-#pragma unroll
-                    for (int ks = 0; ks < 2; ++ks) {
-                        const half8 fp = fragment_of(pk, ks);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            accO[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(smem + TILE, i, 2 * h + ks), fp, accO[i], 0, 0, 0);
-                    }
-                }
-            }
+        for (int r = 0; r < 16; r += 2) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(S[r], scale, -m_ref)), p1 = __builtin_amdgcn_exp2f(fmaf(S[r + 1], scale, -m_ref));
+            psum += p0 + p1;
+            pk[r >> 1] = pack2(p0, p1);
         }
-        l_run += psum;
+        l_run = fmaf(l_run, alpha, psum);
+        // o^T[dcol][query] += v^T[dcol][key] p^T[key][query], 16 keys at a time
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const half8 fp = fragment_of(pk, ks);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) O[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(r0.columns(TILE, i, ks), fp, O[i], 0, 0, 0);
+        }
     };
 
-    using one = std::integral_constant<int, 1>;
-    using two = std::integral_constant<int, 2>;
     for (int blk = 0; blk <= last; ++blk) {
         const int buf = blk & 1;
         // the block's tiles have landed; everybody is done with the other pair
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (blk < last) fetch(blk + 1, buf ^ 1);      // in flight while this block is multiplied
         if (!active || blk > own_last) continue;
+        const bool diag = blk == own_last;      // where the even waves' queries come before the second half
+        const bool second = !diag || (wave & 1) != 0;
         if constexpr (SPLIT == 1) {
-            if (blk < own_last) block(buf, 0, two{}, std::false_type{});
-            else if (wave & 1) block(buf, 0, two{}, std::true_type{});
-            else block(buf, 0, one{}, std::true_type{});
-        } else {
-            const int ahead = qw / 32 - (2 * blk + part);      // of this half's keys
-            if (ahead > 0) block(buf, part, one{}, std::false_type{});
-            else if (ahead == 0) block(buf, part, one{}, std::true_type{});
+            const TileRead r0 = rd.at(buf * PAIR), r1 = rd.at(buf * PAIR + 32 * D);
+            floatx16 S0, S1;
+            scores(r0, S0);
+            scores(r1, S1);
+            half(r0, 0, S0, accO[0], m_run[0], l_run[0], diag);
+            if (second) half(r1, 1, S1, accO[1], m_run[1], l_run[1], diag);
+        } else if (part == 0 || second) {
+            const TileRead r0 = rd.at(buf * PAIR + 32 * part * D);
+            floatx16 S;
+            scores(r0, S);
+            half(r0, part, S, accO[0], m_run[0], l_run[0], diag);
         }
     }
 
+    // ---- the two halves' common maximum and total sum (finite: key 0 is visible to every query), then o
     typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
-    const u32x2v sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-    float l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]), m = m_run;
-    if constexpr (SPLIT == 2) {      // common maximum and total sum of the two halves
-        float* xch = reinterpret_cast<float*>(smem) + (wave & 1) * 66 * 64 + lane;
+    float m[2], l[2];
+#pragma unroll
+    for (int h = 0; h < STATES; ++h) {
+        const u32x2v sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[h]), __float_as_uint(l_run[h]), false, false);
+        m[h] = m_run[h];
+        l[h] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+    float* xch = reinterpret_cast<float*>(smem) + (wave & 1) * 66 * 64 + lane;
+    if constexpr (SPLIT == 2) {
         __syncthreads();             // the tiles are free
         if (part == 1) {
-            put_registers(accO, xch);
-            xch[64 * 64] = m_run;
-            xch[65 * 64] = l;
+            put_registers(accO[0], xch);
+            xch[64 * 64] = m[0];
+            xch[65 * 64] = l[0];
         }
         __syncthreads();
         if (part == 1) return;
-        const float m_other = xch[64 * 64], l_other = xch[65 * 64];
-        m = fmaxf(m_run, m_other);
-        const float m_ref = (m == -INFINITY) ? 0.f : m;
-        const float f = __builtin_amdgcn_exp2f(m_run - m_ref), f_other = __builtin_amdgcn_exp2f(m_other - m_ref);
-        l = fmaf(l, f, l_other * f_other);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) accO[i][r] = fmaf(accO[i][r], f, xch[(16 * i + r) * 64] * f_other);
+        m[1] = xch[64 * 64];
+        l[1] = xch[65 * 64];
     }
     if (!active) return;
-    store_rows(accO, 1.0f / l, a.o + (t0 + query) * a.H + (int64_t)n * D);
-    if (lh == 0) a.lse[(t0 + query) * a.nh + n] = (((m == -INFINITY) ? 0.f : m) + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+    const float mt = fmaxf(m[0], m[1]);
+    const float e0 = __builtin_amdgcn_exp2f(m[0] - mt), e1 = __builtin_amdgcn_exp2f(m[1] - mt);
+    const float lt = fmaf(l[0], e0, l[1] * e1);
+    const float f0 = e0 / lt, f1 = e1 / lt;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float other;
+            if constexpr (SPLIT == 2) other = xch[(16 * i + r) * 64];
+            else other = accO[1][i][r];
+            float x = fmaf(accO[0][i][r], f0, other * f1);
+            asm volatile("" : "+v"(x));      // rounded to fp32 before it is to fp16
+            accO[0][i][r] = x;
+        }
+    store_rows(accO[0], 1.f, a.o + (t0 + query) * a.H + (int64_t)n * D);
+    if (lh == 0) a.lse[(t0 + query) * a.nh + n] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
 }
 
 template <int SPLIT>
@@ -221,7 +225,10 @@ hipError_t launch_attention_forward(const uint16_t* qkv, uint16_t* o, float* lse
     attn::FwdArgs a;
     a.qkv = qkv; a.o = o; a.lse = lse;
     a.s = (int)s; a.nh = (int)nh; a.H = (int)(nh * attn::D);
-    return attn::attention_waves(B, s, nh) < 4 * cu_count() ? launch<2>(a, B, st) : launch<1>(a, B, st);
+    // Below a wave per SIMD the chip has room for twice as many; with a little more than that a call of long walks still ends sooner
+    // when they are halved.  Not split / split, us: 3 x 448 tokens, 32 heads (1344 waves) 22.2 / 23.8, 1 x 1216 (1216) 42.7 / 32.2, 5 x 448,
+    // 16 heads (1120) 21.4 / 19.0, 1 x 1024, 32 heads (1024) 34.5 / 28.5, but 4 x 256 (1024) 12.6 / 13.3, 8 x 128 9.0 / 10.8.
+    return attn::attention_waves(B, s, nh) < (s < 384 ? 4 : 5) * cu_count() ? launch<2>(a, B, st) : launch<1>(a, B, st);
 }
 
 }  // namespace lomo
