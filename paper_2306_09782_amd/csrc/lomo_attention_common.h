@@ -6,8 +6,10 @@
 // sequence, double-buffered in LDS, one barrier per pair.  Scores are formed so that a lane owns one of the wave's own rows;
 // what they become (probabilities, their gradients) reaches the next product through registers, so nothing but the
 // moving tiles passes through LDS and waves meet only where a tile changes.
-// SPLIT = 2, for calls that give too few of these: a workgroup owns 64 rows, two waves have the same 32, each takes one half
-// of every moving tile, and their sums are put together at the end.
+// SPLIT = 2, for calls that give too few of these: a workgroup owns 64 rows, two waves have the same 32, and each takes one half
+// of every moving tile.  The forward puts their sums together at the end, as it does with the halves of one wave; the
+// backward kernels hand P and dS over through LDS, each wave having a part of the sums.  Every sum has the same terms in the
+// same order either way, so a call's size does not show in its results.
 #pragma once
 #include "lomo_gemm_common.h"
 
@@ -18,8 +20,8 @@ typedef short short4a __attribute__((ext_vector_type(4)));
 namespace attn {
 
 constexpr int D = 128;                 // head width
-template <int SPLIT>
-constexpr int ROWS = 128 / SPLIT;      // rows of a workgroup
+template <int SPLIT, int WAVES = 4>
+constexpr int ROWS = 32 * WAVES / SPLIT;      // rows of a workgroup
 constexpr int BLK = 64;                // rows of a moving tile
 constexpr int TILE = BLK * D;          // halves
 constexpr int PAIR = 2 * TILE;
@@ -59,10 +61,14 @@ struct TileLoad {
         step = 4 * ld;
     }
     // `tile`: LDS address; `wave` uniform
+    template <int WAVES = 4>
     __device__ __forceinline__ void issue(const uint16_t* base, uint32_t tile, int wave) const {
+        if constexpr (WAVES == 2) issue(base, tile, wave + 2);
         base += 4 * wave * step;
+        uint32_t v = voff;
+        asm volatile("" : "+v"(v));      // formed again each time, not kept in registers
 #pragma unroll
-        for (int it = 0; it < 4; ++it) load_lds16(voff ^ (uint32_t)(16 * it), base + it * step, tile + (uint32_t)(4 * wave + it) * 1024u);
+        for (int it = 0; it < 4; ++it) load_lds16(v ^ (uint32_t)(16 * it), base + it * step, tile + (uint32_t)(4 * wave + it) * 1024u);
     }
 };
 
@@ -87,6 +93,19 @@ struct TileRead {
         t.tr0 += 2u * (uint32_t)halves;
         t.tr1 += 2u * (uint32_t)halves;
         asm volatile("" : "+v"(t.row_rd), "+v"(t.tr0), "+v"(t.tr1));
+        return t;
+    }
+    __device__ __forceinline__ void move(int halves) {
+        row_rd += 2u * (uint32_t)halves;
+        tr0 += 2u * (uint32_t)halves;
+        tr1 += 2u * (uint32_t)halves;
+        asm volatile("" : "+v"(row_rd), "+v"(tr0), "+v"(tr1));
+    }
+    // the same with column tiles counted from `i` on
+    __device__ __forceinline__ TileRead column_tile(int i) const {
+        TileRead t = *this;
+        t.tr0 ^= (uint32_t)(64 * i);
+        t.tr1 ^= (uint32_t)(64 * i);
         return t;
     }
     // `off`: halves from the tile of this to the one that is read.
@@ -140,53 +159,39 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, h);
 }
 
-// acc[i][r]: column 32 i + 8 (r / 4) + 4 lh + r % 4 of the lane's row, scaled by f and rounded once.
-__device__ __forceinline__ void store_rows(const floatx16 (&acc)[4], float f, uint16_t* row) {
+// acc[i][r]: column 32 c + 8 (r / 4) + 4 lh + r % 4 of the lane's row, rounded once; c = i, of two accumulators first + 2 i.
+template <int N>
+__device__ __forceinline__ void store_rows(const floatx16 (&acc)[N], uint16_t* row, int first = 0) {
     const int lh = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
         uint32_t pk[8];
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) pk[r >> 1] = pack2(acc[i][r] * f, acc[i][r + 1] * f);
+        for (int r = 0; r < 16; r += 2) pk[r >> 1] = pack2(acc[i][r], acc[i][r + 1]);
 #pragma unroll
-        for (int a = 0; a < 2; ++a) *reinterpret_cast<half8*>(row + 32 * i + 16 * a + 8 * lh) = fragment_of(pk, a);
+        for (int a = 0; a < 2; ++a) *reinterpret_cast<half8*>(row + 32 * (N == 4 ? i : first + 2 * i) + 16 * a + 8 * lh) = fragment_of(pk, a);
     }
 }
 
-// The second half's accumulators on their way to the first's wave: [register][lane].
-__device__ __forceinline__ void put_registers(const floatx16 (&acc)[4], float* lds) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) lds[(16 * i + r) * 64] = acc[i][r];
-}
-__device__ __forceinline__ void add_registers(floatx16 (&acc)[4], const float* lds) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] += lds[(16 * i + r) * 64];
-}
+// Waves of a call that is not split, per CU.  Below four, one for every SIMD, the chip has room for twice as many; with more a call of
+// long walks still ends sooner when they are halved.
+inline double waves_per_cu(int64_t B, int64_t s, int64_t nh) { return (double)(s / 32 * nh * B) / (double)cu_count(); }
 
-// Waves of a call that is not split.
-inline int64_t attention_waves(int64_t B, int64_t s, int64_t nh) { return s / 32 * nh * B; }
-
-// Zeros the values of a diagonal block that the mask takes; the branch around it stays one (most blocks have no mask).
-template <typename F>
-__device__ __forceinline__ void mask(floatx16& x, F&& masked) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        float v = masked(r) ? 0.f : x[r];
-        asm volatile("" : "+v"(v));
-        x[r] = v;
-    }
-}
-
-// Position of this workgroup in launch order when each XCD (blockIdx % 8) takes a contiguous run of (sequence, head) pairs,
-// so that the blocks of one head, which read the same rows, meet in one L2.
-__device__ __forceinline__ int xcd_position() {
+// This workgroup's (sequence, head) pair and its place among the pair's `nb` blocks, 0 the first to start.  Each XCD (blockIdx % 8)
+// takes a contiguous run of pairs, so that the blocks that read the same rows meet in one L2.  Where they divide evenly, the
+// first blocks of all its pairs start first, the heaviest there are; pair by pair, the 32 blocks of 4096 tokens fall on
+// the 32 CUs of an XCD alike for every pair, and one CU has all the heaviest.
+__device__ __forceinline__ void locate_block(int nb, int& pair, int& place) {
     const int G = gridDim.x, x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
-    const int q = G >> 3, r = G & 7;
-    return x * q + (x < r ? x : r) + local;
+    if (G % (8 * nb) == 0) {
+        const int pairs = G / (8 * nb);
+        place = local / pairs;
+        pair = x * pairs + (local - place * pairs);
+    } else {
+        const int q = G >> 3, r = G & 7, pos = x * q + (x < r ? x : r) + local;
+        pair = pos / nb;
+        place = pos - pair * nb;
+    }
 }
 
 }  // namespace attn

@@ -14,9 +14,9 @@
 // once.  Deterministic.
 //
 // Measured, us, against a workgroup of 64 queries with the halves on different waves and tiles through registers: 1 x 8192 tokens, 32 heads
-// 835 -> 681 (808 TFLOP/s); 8 x 1024, 40 heads 211 -> 200; 8 x 512, 32 heads 61 -> 51; 1 x 1024 32 -> 28.5; 3 x 320 13.2 -> 13.8.  (One
-// maximum for both halves: 677, 184, 48, 29.4, 13.4; it rescales the output half as often.)  Vector instructions are the limit:
-// at short sequences most blocks move some query's maximum, which is 128 products a lane beside about 250 for the probabilities.
+// 839 -> 673 (817 TFLOP/s); 8 x 1024, 40 heads 210 -> 172; 8 x 512, 32 heads 61 -> 43.6; 1 x 1024 31.5 -> 24.7; 3 x 320 13.2 -> 13.3.  Vector
+// instructions are the limit: at short sequences most blocks move some query's maximum, which is 128 products a lane beside about
+// 250 for the probabilities.
 #include "lomo_attention_common.h"
 
 namespace lomo {
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
 
     const int nb = (a.s + ROWS<SPLIT> - 1) / ROWS<SPLIT>;
-    const int pos = xcd_position();
-    const int head = pos / nb, within = pos - head * nb;
+    int head, within;
+    locate_block(nb, head, within);
     const int n = head % a.nh, b = head / a.nh;
     const int q0 = (nb - 1 - within) * ROWS<SPLIT>;          // heaviest blocks first
     const int qw = q0 + 32 * (SPLIT == 2 ? wave & 1 : wave);      // this wave's queries
@@ -179,7 +179,10 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     if constexpr (SPLIT == 2) {
         __syncthreads();             // the tiles are free
         if (part == 1) {
-            put_registers(accO[0], xch);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xch[(16 * i + r) * 64] = accO[0][i][r];
             xch[64 * 64] = m[0];
             xch[65 * 64] = l[0];
         }
@@ -204,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
             asm volatile("" : "+v"(x));      // rounded to fp32 before it is to fp16
             accO[0][i][r] = x;
         }
-    store_rows(accO[0], 1.f, a.o + (t0 + query) * a.H + (int64_t)n * D);
+    store_rows(accO[0], a.o + (t0 + query) * a.H + (int64_t)n * D);
     if (lh == 0) a.lse[(t0 + query) * a.nh + n] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
 }
 
@@ -225,10 +228,10 @@ hipError_t launch_attention_forward(const uint16_t* qkv, uint16_t* o, float* lse
     attn::FwdArgs a;
     a.qkv = qkv; a.o = o; a.lse = lse;
     a.s = (int)s; a.nh = (int)nh; a.H = (int)(nh * attn::D);
-    // Below a wave per SIMD the chip has room for twice as many; with a little more than that a call of long walks still ends sooner
-    // when they are halved.  Not split / split, us: 3 x 448 tokens, 32 heads (1344 waves) 22.2 / 23.8, 1 x 1216 (1216) 42.7 / 32.2, 5 x 448,
-    // 16 heads (1120) 21.4 / 19.0, 1 x 1024, 32 heads (1024) 34.5 / 28.5, but 4 x 256 (1024) 12.6 / 13.3, 8 x 128 9.0 / 10.8.
-    return attn::attention_waves(B, s, nh) < (s < 384 ? 4 : 5) * cu_count() ? launch<2>(a, B, st) : launch<1>(a, B, st);
+    // not split / split, us: 3 x 320 tokens, 32 heads 14.5 / 13.3, 8 x 128 (4 waves per CU) 8.9 / 10.9, 4 x 256 (4) 12.4 / 12.0, 5 x 256 (5) 14.7 / 18.0;
+    // 3 x 512 (6) 23.4 / 23.8, 4 x 512 (8) 25.4 / 29.2;  1 x 1024 (4) 34.7 / 24.7, 1 x 1536 (6) 54.4 / 39.1, 1 x 2048 (8) 75 / 61, 3 x 768 (9) 33.9 / 40.2
+    const double waves = attn::waves_per_cu(B, s, nh);
+    return waves < 4.0 || (s >= 384 && waves <= 5.0) || (s >= 768 && waves <= 8.0) ? launch<2>(a, B, st) : launch<1>(a, B, st);
 }
 
 }  // namespace lomo

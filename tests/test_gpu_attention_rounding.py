@@ -27,17 +27,27 @@ def forward(L, qkv, B, s, nh):
     return o, lse
 
 
+def backward(L, qkv, o, do, lse, angle, B, s, nh):
+    grad, delta = torch.empty_like(qkv), torch.empty_like(lse).view(-1)
+    L.lomo_attention_backward(qkv, o, do, lse.view(-1), angle.cos().contiguous(), angle.sin().contiguous(), delta, grad, B, s, nh)
+    return grad
+
+
 # a few waves per call against thousands, ends of sequences at both halves of a workgroup's rows
 @pytest.mark.parametrize("s,nh", [(64, 4), (192, 4), (512, 8), (1088, 4)])
 def test_call_size_does_not_show(L, s, nh):
     B, H = -(-65536 // (s // 32 * nh)) // 4, nh * 128
     gen = torch.Generator(device=DEV).manual_seed(s)
-    qkv = torch.randn(B * s, 3 * H, generator=gen, device=DEV, dtype=torch.float16)
+    qkv, do = (torch.randn(B * s, n * H, generator=gen, device=DEV, dtype=torch.float16) for n in (3, 1))
+    angle = torch.rand(s, 64, generator=gen, device=DEV)
     o, lse = forward(L, qkv, B, s, nh)
+    grad = backward(L, qkv, o, do, lse, angle, B, s, nh)
     for b in (0, B // 2, B - 1):
         rows = slice(b * s, (b + 1) * s)
-        one_o, one_lse = forward(L, qkv[rows].contiguous(), 1, s, nh)
+        one = qkv[rows].contiguous()
+        one_o, one_lse = forward(L, one, 1, s, nh)
         assert torch.equal(one_o, o[rows]) and torch.equal(one_lse, lse[rows]), b
+        assert torch.equal(backward(L, one, one_o, do[rows].contiguous(), one_lse, angle, 1, s, nh), grad[rows]), b
 
 
 def two_maxima(q, k, v):
