@@ -620,8 +620,7 @@ lomo_status lomo_cross_entropy_mean(const lomo_half* logits, const int32_t* targ
 
 lomo_status lomo_attention_forward(const lomo_half* qkv, lomo_half* o, float* lse, int64_t B, int64_t s, int64_t n_heads,
                                    int64_t head_dim, void* stream) {
-    // four rows of q, k, v have to fit 32-bit offsets
-    if (B < 0 || s < 0 || n_heads <= 0 || n_heads > (1 << 20) || head_dim != 128 || (s % 64) != 0) return LOMO_ERR_SHAPE;
+    if (B < 0 || s < 0 || n_heads <= 0 || head_dim != 128 || (s % 64) != 0) return LOMO_ERR_SHAPE;
     if (B * s * n_heads > (int64_t)1 << 31 || (s / 64) * n_heads * B > 0x7fffffff) return LOMO_ERR_SHAPE;
     if (B == 0 || s == 0) return LOMO_OK;
     if (!qkv || !o || !lse) return LOMO_ERR_NULL;

@@ -51,7 +51,8 @@ __device__ __forceinline__ void load_lds16(uint32_t voff, const void* base, uint
 
 // The loads of a [64 x 128] tile with rows of `ld` elements: wave w of the four fetches rows 16 w .. 16 w + 15 with four instructions of
 // four rows.  A row is a multiple of 256 bytes, so the chunk's place in it is the low byte of the offset, where the swizzles
-// of the four instructions differ by their number.
+// of the four instructions differ by their number.  Four rows have to fit 32-bit offsets: up to FAR heads.
+constexpr int64_t FAR = 1 << 20;
 struct TileLoad {
     uint32_t voff;
     int64_t step;      // four rows
@@ -69,6 +70,25 @@ struct TileLoad {
         asm volatile("" : "+v"(v));      // formed again each time, not kept in registers
 #pragma unroll
         for (int it = 0; it < 4; ++it) load_lds16(v ^ (uint32_t)(16 * it), base + it * step, tile + (uint32_t)(4 * wave + it) * 1024u);
+    }
+};
+
+// The same for rows of any length, by 64-bit addresses.
+struct TileLoadFar {
+    int64_t row;       // bytes from one row to the next
+    uint32_t chunk;
+    __device__ __forceinline__ TileLoadFar(int64_t ld) {
+        const int lane = threadIdx.x & 63, rr = lane >> 4;
+        row = 2 * ld;
+        chunk = (uint32_t)(((lane & 15) ^ swz(rr)) * 16);
+    }
+    __device__ __forceinline__ void issue(const uint16_t* base, uint32_t tile, int wave) const {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const char* at = reinterpret_cast<const char*>(base) + (16 * wave + 4 * it + ((threadIdx.x & 63) >> 4)) * row + (chunk ^ (uint32_t)(16 * it));
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(at), "s"(tile + (uint32_t)(4 * wave + it) * 1024u)
+                         : "memory", "m0");
+        }
     }
 };
 

@@ -34,7 +34,7 @@ constexpr float C2 = SCALE * LOG2E;
 
 }  // namespace attn
 
-template <int SPLIT>
+template <int SPLIT, typename Load>
 __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs a) {
     using namespace attn;
     extern __shared__ __attribute__((aligned(256))) uint16_t smem[];      // two pairs of tiles: K, V
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     const uint16_t* gv = gk + a.H;
     const int query = qw + l32;
 
-    const TileLoad load(ld3);
+    const Load load(ld3);
     const TileRead rd(lds0);
     auto fetch = [&](int blk, int buf) {
         const int64_t off = (int64_t)blk * BLK * ld3;
@@ -211,10 +211,10 @@ __global__ __launch_bounds__(256, 2) void attention_forward_kernel(attn::FwdArgs
     if (lh == 0) a.lse[(t0 + query) * a.nh + n] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
 }
 
-template <int SPLIT>
+template <int SPLIT, typename Load = attn::TileLoad>
 static hipError_t launch(const attn::FwdArgs& a, int64_t B, hipStream_t st) {
     using namespace attn;
-    auto kern = attention_forward_kernel<SPLIT>;
+    auto kern = attention_forward_kernel<SPLIT, Load>;
     // thread-safe one-time set-up (initialisation of a function-local static)
     static const hipError_t cfg0 = allow_dynamic_lds(kern, LDS_BYTES);
     if (cfg0 != hipSuccess) return cfg0;
@@ -228,6 +228,7 @@ hipError_t launch_attention_forward(const uint16_t* qkv, uint16_t* o, float* lse
     attn::FwdArgs a;
     a.qkv = qkv; a.o = o; a.lse = lse;
     a.s = (int)s; a.nh = (int)nh; a.H = (int)(nh * attn::D);
+    if (nh > attn::FAR) return launch<1, attn::TileLoadFar>(a, B, st);
     // not split / split, us: 3 x 320 tokens, 32 heads 14.5 / 13.3, 8 x 128 (4 waves per CU) 8.9 / 10.9, 4 x 256 (4) 12.4 / 12.0, 5 x 256 (5) 14.7 / 18.0;
     // 3 x 512 (6) 23.4 / 23.8, 4 x 512 (8) 25.4 / 29.2;  1 x 1024 (4) 34.7 / 24.7, 1 x 1536 (6) 54.4 / 39.1, 1 x 2048 (8) 75 / 61, 3 x 768 (9) 33.9 / 40.2
     const double waves = attn::waves_per_cu(B, s, nh);

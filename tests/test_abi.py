@@ -82,6 +82,9 @@ def test_shape_errors_are_reported_before_any_launch(lib):
     assert lib.lomo_wgrad_sqnorm_route(P, P, 4, 8, 8, P, P, 9, P) == 2
     assert lib.lomo_probe_mfma(P, 1, 3, 0, 0, P, 0, None, P) == 2 and lib.lomo_probe_copy(P, P, 24, P) == 2
     assert lib.lomo_cross_entropy_mean(P, P, 1.0, P, P, P, 4, 8, P) == 1                # stats missing
+    assert lib.lomo_attention_forward(P, P, P, 1, 64, 32, 64, P) == 2 and lib.lomo_attention_forward(P, P, P, 1, 96, 32, 128, P) == 2
+    assert lib.lomo_attention_forward(P, P, P, 1, 64, 32, 128, P) == 1
+    assert lib.lomo_attention_forward(P, P, P, 1, 64, (1 << 20) + 1, 128, P) == 1       # rows beyond 32-bit offsets are taken
     vec = (binding.LomoTensor * 2)()
     for v in vec:
         v.kind, v.T, v.K, v.N = 2, 4096, 4096, 1

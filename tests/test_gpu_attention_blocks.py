@@ -57,3 +57,24 @@ def test_blocks(L, B, s, nh):
             for name, g, w in zip(("o", "lse", "dq", "dk", "dv"), got, want):
                 if g is not None:
                     assert off(g, w) < 2.0 ** -10, (name, b, n, off(g, w))
+
+
+def test_rows_beyond_32_bit_offsets(L):
+    """More heads than a wave's 32-bit offsets reach over four rows (48 GiB of q, k and v, most of it never looked at)."""
+    s, nh = 64, (1 << 20) + 8
+    qkv = torch.empty(s, 3, nh, 128, dtype=torch.float16, device=DEV)
+    o, lse = torch.empty(s, nh, 128, dtype=torch.float16, device=DEV), torch.empty(s, nh, device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    heads = (0, 1, nh // 2 + 5, nh - 1)
+    for n in heads:
+        qkv[:, :, n] = torch.randn(s, 3, 128, generator=gen, device=DEV, dtype=torch.float16)
+    L.lomo_attention_forward(qkv.view(s, -1), o.view(s, -1), lse, 1, s, nh)
+    for n in heads:
+        q, k, v = (qkv[:, i, n].contiguous() for i in range(3))
+        one, one_lse = torch.empty(s, 128, dtype=torch.float16, device=DEV), torch.empty(s, 1, device=DEV)
+        L.lomo_attention_forward(torch.cat((q, k, v), 1), one, one_lse, 1, s, 1)
+        assert torch.equal(one, o[:, n]) and torch.equal(one_lse[:, 0], lse[:, n]), n
+        want = reference(q.double(), k.double(), v.double(), q.double())[0]
+        assert float((one.double() - want).norm() / want.norm()) < 2.0 ** -10
+    del qkv, o, lse
+    torch.cuda.empty_cache()
