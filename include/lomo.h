@@ -397,6 +397,12 @@ enum { LOMO_KERNEL_WGRAD_UPDATE = 0, LOMO_KERNEL_WGRAD_SQNORM = 1, LOMO_KERNEL_D
  * give the same bits.  Without a GPU the answer is that of one with 256 compute units. */
 lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles);
 
+/* The same, with `residual` != 0 for a forward product with one (LOMO_KERNEL_FORWARD), and, where `last` is not null, what the first launch
+ * with 256 256 tiles does with a last round that is not full, in last[6]: the tensor of which a piece goes to smaller tiles (its place
+ * in the list; -1: none), columns and rows of that piece, columns and rows of its tiles, and 1 if the round is dealt out to all XCDs, 0 if
+ * not (-1: no such launch). */
+lomo_status lomo_contraction_plan(int family, int residual, const int64_t* shapes, int64_t n, int32_t* tiles, int32_t* last);
+
 /* Per-kernel timing for benchmarks: while enabled, each launch of a kernel family is bracketed
  * by two HIP events recorded on the launch stream (the only host-side state the library keeps;
  * events are created on first use and reused).  Enabling or disabling resets the counters.

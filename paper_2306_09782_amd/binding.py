@@ -24,6 +24,7 @@ EXPORTED_SYMBOLS = (
     "lomo_linear_forward", "lomo_rmsnorm_forward", "lomo_swiglu_forward", "lomo_rope_forward", "lomo_attention_forward",
     "lomo_cross_entropy", "lomo_embedding_forward", "lomo_linear_forward_residual", "lomo_cross_entropy_mean",
     "lomo_probe_mfma", "lomo_probe_copy", "lomo_vector_update_static", "lomo_contraction_tiles",
+    "lomo_contraction_plan",
 )
 
 
@@ -104,6 +105,7 @@ def load_library():
         "lomo_probe_mfma": (c_int, [P, I64, c_int, c_int, c_int, P, I64, POINTER(c_double), P]),
         "lomo_probe_copy": (c_int, [P, P, c_size_t, P]),
         "lomo_contraction_tiles": (c_int, [c_int, POINTER(c_int64), I64, POINTER(c_int32)]),
+        "lomo_contraction_plan": (c_int, [c_int, c_int, POINTER(c_int64), I64, POINTER(c_int32), POINTER(c_int32)]),
         "lomo_timing_enable": (c_int, [c_int]),
         "lomo_timing_read": (c_int, [c_int, POINTER(c_double), POINTER(c_int64)]),
     }
@@ -273,6 +275,16 @@ def lomo_contraction_tiles(family: int, shapes):
     arr, out = (c_int64 * max(1, len(flat)))(*flat), (c_int32 * max(1, 2 * len(shapes)))()
     _check(load_library().lomo_contraction_tiles(family, arr, len(shapes), out))
     return [(out[2 * i], out[2 * i + 1]) for i in range(len(shapes))]
+
+
+def lomo_contraction_plan(family: int, shapes, residual=False):
+    """The tiles as lomo_contraction_tiles gives them (of a forward product with a residual too), and the last round of the first
+    launch with 256 x 256 tiles: (tensor cut or None, (columns, rows) of the piece, its tile, dealt out to all XCDs or None)."""
+    flat = [int(v) for s in shapes for v in s]
+    arr, out, last = (c_int64 * max(1, len(flat)))(*flat), (c_int32 * max(1, 2 * len(shapes)))(), (c_int32 * 6)()
+    _check(load_library().lomo_contraction_plan(family, int(residual), arr, len(shapes), out, last))
+    cut = (None, None, None) if last[0] < 0 else (last[0], (last[1], last[2]), (last[3], last[4]))
+    return [(out[2 * i], out[2 * i + 1]) for i in range(len(shapes))], (*cut, None if last[5] < 0 else bool(last[5]))
 
 
 def make_tensor_list(tensors):

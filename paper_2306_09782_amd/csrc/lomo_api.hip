@@ -462,10 +462,14 @@ lomo_status lomo_step_update_pass_clip_value(const lomo_tensor* tensors, int64_t
     return from_hip(launch_reduce_flags(flags, n, flags + n, st));
 }
 
-lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles) try {
+lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n, int32_t* tiles) {
+    return lomo_contraction_plan(family, 0, shapes, n, tiles, nullptr);
+}
+
+lomo_status lomo_contraction_plan(int family, int residual, const int64_t* shapes, int64_t n, int32_t* tiles, int32_t* last) try {
     if (n < 0) return LOMO_ERR_SHAPE;
     const bool forward = family == LOMO_KERNEL_FORWARD, dgrad = family == LOMO_KERNEL_DGRAD;
-    if (!forward && !dgrad && family != LOMO_KERNEL_WGRAD_SQNORM && family != LOMO_KERNEL_WGRAD_UPDATE) return LOMO_ERR_SHAPE;
+    if (!forward && (residual || (!dgrad && family != LOMO_KERNEL_WGRAD_SQNORM && family != LOMO_KERNEL_WGRAD_UPDATE))) return LOMO_ERR_SHAPE;
     if (n > 0 && (!shapes || !tiles)) return LOMO_ERR_NULL;
     std::vector<GemmArgs> list;
     std::vector<int64_t> at;
@@ -479,6 +483,7 @@ lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n,
         a.lda = K;
         a.ldb = forward ? K : N;
         a.ldo = forward ? N : K;
+        a.family = (int)i;
         tiles[2 * i] = tiles[2 * i + 1] = 0;
         if (!(forward ? dma_eligible<false, false>(a) : dgrad ? dma_eligible<false, true>(a) : dma_eligible<true, true>(a))) continue;
         a.persistent_only = !forward && (dgrad ? beyond_descriptor<false, true>(a) : beyond_descriptor<true, true>(a));
@@ -486,9 +491,20 @@ lomo_status lomo_contraction_tiles(int family, const int64_t* shapes, int64_t n,
         at.push_back(i);
     }
     std::vector<int> tile_of(list.size());
-    const int product = forward || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE;
+    const int product = (forward && !residual) || dgrad ? PRODUCT_STORE : family == LOMO_KERNEL_WGRAD_SQNORM ? PRODUCT_NORM : PRODUCT_UPDATE;
     choose_tiles(list.data(), list.size(), product, tile_of.data());
     for (size_t k = 0; k < list.size(); ++k) tile_size(tile_of[k], tiles + 2 * at[k], tiles + 2 * at[k] + 1);
+    if (last != nullptr) {
+        const LastRound r = last_round(list.data(), list.size(), tile_of.data(), product, !forward, !forward && !dgrad);
+        for (int k = 0; k < 5; ++k) last[k] = 0;
+        last[0] = r.tensor;
+        last[5] = r.dealt;
+        if (r.tensor >= 0) {
+            last[1] = (int32_t)r.cut.piece.M;
+            last[2] = (int32_t)r.cut.piece.Nn;
+            tile_size(r.cut.tile, last + 3, last + 4);
+        }
+    }
     return LOMO_OK;
 } catch (const std::bad_alloc&) {
     return LOMO_ERR_LAUNCH;

@@ -19,7 +19,7 @@
 // With A on the MFMA row side, each lane's four consecutive accumulator registers are four
 // consecutive m, i.e. an 8-byte run of W / dX: the read-modify-write epilogue is vectorised.
 #include "lomo_gemm_common.h"
-#include "lomo_gemm_dma_common.h"
+#include "lomo_gemm_persistent.h"
 
 #include <stdlib.h>
 
@@ -332,30 +332,57 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
                               f + (longest > mean ? through * busy + latency * (longest - busy) : longest * std::max(latency, 0.7 * through)));
 }
 
-// Contraction indices of the longest walk when the persistent kernels take a list in this order: tile t of a round goes to the
-// workgroup that has tile t of every round (of a last round to others, which is left out of account).
-static double longest_walk(const GemmArgs* list, size_t n) {
-    const int64_t cus = cu_count();
-    std::vector<double> step((size_t)cus + 1, 0.0);      // of the walks, from one workgroup to the next
+// Contraction indices of the longest walk of G workgroups of a persistent kernel over tensors of tiles(i) tiles with contractions of
+// length(i): tile t of a full round goes to the same workgroup in every one, the last round as xcd_run says.
+template <typename Tiles, typename Length>
+static double longest_walk(size_t n, int G, bool deal, Tiles&& tiles, Length&& length) {
+    constexpr int MOST = 1024;
+    if (G > MOST) G = MOST;      // no such device
+    double load[MOST + 1] = {};      // in full rounds: from one workgroup to the next
+    int64_t total = 0;
+    for (size_t i = 0; i < n; ++i) total += tiles(i);
+    const int64_t full = total / G * G;
     double all = 0.0;
     int64_t at = 0;
-    for (size_t i = 0; i < n; ++i) {
-        const double c = (double)list[i].C;
-        int64_t tiles = ((list[i].M + 255) / 256) * ((list[i].Nn + 255) / 256);
-        all += c * (double)(tiles / cus);
-        tiles %= cus;
-        const int64_t to = at + tiles;
-        step[(size_t)at] += c;
-        step[(size_t)(to < cus ? to : cus)] -= c;
-        if (to > cus) {
-            step[0] += c;
-            step[(size_t)(to - cus)] -= c;
+    size_t i = 0;
+    for (; i < n; ++i) {
+        const int64_t end = std::min(at + tiles(i), full), count = end - at;
+        const double c = (double)length(i);
+        all += c * (double)(count / G);
+        const int64_t from = at % G, to = from + count % G;
+        load[from] += c;
+        load[to < G ? to : G] -= c;
+        if (to > G) {
+            load[0] += c;
+            load[to - G] -= c;
         }
-        at = to % cus;
+        if (end == full) break;
+        at = end;
     }
-    double walk = 0.0, longest = 0.0;
-    for (double s : step) longest = std::max(longest, walk += s);
+    for (int p = 1; p < G; ++p) load[p] += load[p - 1];
+    at = 0;
+    for (size_t k = 0; k < i; ++k) at += tiles(k);
+    const int left = (int)(total - full);
+    for (int x = 0; x < 8 && i < n; ++x) {
+        const dma::Run run = dma::xcd_run(x, left, G, deal);
+        for (int l = 0; l < run.count; ++l) {
+            while (at + tiles(i) <= full + run.first + l) at += tiles(i++);
+            load[dma::xcd_run(x, G, G, true).first + l] += (double)length(i);
+        }
+    }
+    double longest = 0.0;
+    for (int p = 0; p < G; ++p) longest = std::max(longest, load[p]);
     return all + longest;
+}
+
+// Dealt out, unless that makes the longest walk longer.
+int choose_deal(const dma::GroupArgs& ga, int workgroups) {
+    bool same = true;
+    for (int i = 1; i < ga.n; ++i) same &= ga.t[i].C == ga.t[0].C;
+    if (same || ga.total_tiles % workgroups == 0) return 1;
+    auto tiles = [&](size_t i) { return (int64_t)ga.t[i].tiles_m * ga.t[i].tiles_n; };
+    auto length = [&](size_t i) { return ga.t[i].C; };
+    return longest_walk((size_t)ga.n, workgroups, true, tiles, length) <= longest_walk((size_t)ga.n, workgroups, false, tiles, length);
 }
 
 static double pass_time(const std::vector<Shape>& shapes, int product, double cus) {
@@ -521,6 +548,39 @@ static hipError_t launch_with(int tile, const GemmArgs* list, size_t n, hipStrea
     return hipSuccess;
 }
 
+// Workgroups of the small tiles start in list order: the longest walks first.  In the persistent kernels that is done where
+// it makes the longest walk shorter; otherwise the order does not matter much (dX of a 7B layer at 4096 tokens 1339 us as
+// listed, 1337 sorted; at 2999 tokens 1070 and 1078; of two 13B layers at 1070 tokens 1286 and 1339).
+static void order_list(int tile, std::vector<GemmArgs>& list) {
+    std::vector<GemmArgs> sorted = list;
+    std::stable_sort(sorted.begin(), sorted.end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
+    auto walk = [&](const std::vector<GemmArgs>& v) {
+        auto tiles = [&](size_t i) { return ((v[i].M + 255) / 256) * ((v[i].Nn + 255) / 256); };
+        auto length = [&](size_t i) { return v[i].C; };
+        return std::min(longest_walk(v.size(), cu_count(), true, tiles, length), longest_walk(v.size(), cu_count(), false, tiles, length));
+    };
+    if (tile != TILE_256 || walk(sorted) < 0.98 * walk(list)) list.swap(sorted);
+}
+
+LastRound last_round(const GemmArgs* list, size_t n, const int* tile_of, int product, bool a_strided, bool b_strided) {
+    LastRound r;
+    std::vector<GemmArgs> v;
+    for (size_t i = 0; i < n; ++i)
+        if (tile_of[i] == TILE_256) v.push_back(list[i]);
+    if (v.empty()) return r;
+    if (n > 1) order_list(TILE_256, v);
+    const int cnt = (int)std::min(v.size(), (size_t)dma::MAX_GROUP);
+    r.cut = cut_leftover(v.data(), cnt, product, a_strided, b_strided);
+    if (r.cut.tensor >= 0) {
+        v[r.cut.tensor] = r.cut.kept;
+        r.tensor = r.cut.kept.family;      // its place in the list
+    }
+    dma::GroupArgs ga{};
+    dma::fill_group(ga, v.data(), cnt, 256, 256);
+    r.dealt = choose_deal(ga, std::min(ga.total_tiles, cu_count()));
+    return r;
+}
+
 // A list of one allocates no host memory; for longer ones a failed allocation is an error code like a refused launch.
 template <bool B_STRIDED, int EPI, bool A_STRIDED>
 static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) try {
@@ -548,12 +608,7 @@ static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) tr
     for (size_t i = 0; i < fit.size(); ++i) by[tile_of[i]].push_back(fit[i]);
     for (int tile = 0; tile < N_TILES; ++tile) {
         if (by[tile].empty()) continue;
-        // workgroups of the small tiles start in list order: the longest walks first.  In the persistent kernels that is done where
-        // it makes the longest walk shorter; otherwise the order does not matter much (dX of a 7B layer at 4096 tokens 1339 us as
-        // listed, 1337 sorted; at 2999 tokens 1070 and 1078; of two 13B layers at 1070 tokens 1286 and 1339).
-        std::vector<GemmArgs> sorted = by[tile];
-        std::stable_sort(sorted.begin(), sorted.end(), [](const GemmArgs& x, const GemmArgs& y) { return x.C > y.C; });
-        if (tile != TILE_256 || longest_walk(sorted.data(), sorted.size()) < 0.98 * longest_walk(by[tile].data(), by[tile].size())) by[tile].swap(sorted);
+        order_list(tile, by[tile]);
         const hipError_t e = launch_with<B_STRIDED, EPI, A_STRIDED>(tile, by[tile].data(), by[tile].size(), st);
         if (e != hipSuccess) return e;
     }

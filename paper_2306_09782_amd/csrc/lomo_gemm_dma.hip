@@ -79,8 +79,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     constexpr bool ALIGN_ROUNDS = EPI == EPI_UPDATE || EPI == EPI_CLIPV;
     const int xcd = (int)(blockIdx.x & 7);
     auto xcd_tiles_in_round = [&](int k) {
-        const int n = round_tiles(k, G, ga.total_tiles);
-        return (n >> 3) + (xcd < (n & 7) ? 1 : 0);
+        return xcd_run(xcd, round_tiles(k, G, ga.total_tiles), G, ga.deal != 0).count;
     };
     bool align_rounds = ALIGN_ROUNDS;      // cleared after a wait that ran into its bound
     int round = 0;
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     };
 
     // ---- walk the tile list, one tile a round; every workgroup leaves through `break`
-    int w = round_tile(0, G, ga.total_tiles);
+    int w = round_tile(0, G, ga.total_tiles, ga.deal != 0);
     if (w >= ga.total_tiles) return;   // cannot happen with grid <= total_tiles; nothing was issued yet
     int tensor = 0;
     int64_t m0, n0;
@@ -311,7 +310,8 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         const int64_t em0 = m0, en0 = n0;
 
         // request the first blocks of W (update), then the first slices of the next tile, then finish this one
-        w = round_tile(++round, G, ga.total_tiles);
+        ++round;
+        w = next_tile(w, round, G, ga.total_tiles, ga.deal != 0);
         const bool more = w < ga.total_tiles;
         if constexpr (ALIGN_ROUNDS) {
             if (more && round < SYNC_ROUNDS && tid == 0) atomicAdd(&g_round_arrive[round][xcd], 1);
@@ -391,6 +391,7 @@ static hipError_t launch_dma(const GemmArgs* list, int n, hipStream_t st) {
         fill_group(ga, list + first, cnt, BM, BN);
         const int tiles = ga.total_tiles;
         const int grid = tiles < cu_count() ? tiles : cu_count();
+        ga.deal = choose_deal(ga, grid);
         // the kernels that align their rounds; a single round reads no counter
         if ((EPI == EPI_UPDATE || EPI == EPI_CLIPV) && tiles > grid) {
             int rounds = (tiles + grid - 1) / grid;

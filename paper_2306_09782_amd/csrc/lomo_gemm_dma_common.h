@@ -60,6 +60,7 @@ struct GroupArgs {
     float s, lr, inv_s, clipv;
     const float* s_dev;
     int n, total_tiles;
+    int deal;      // persistent kernels: the last round is dealt out to all XCDs
     GroupTensor t[MAX_GROUP];
 };
 

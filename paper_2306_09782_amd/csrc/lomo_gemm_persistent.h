@@ -20,15 +20,31 @@ __device__ __forceinline__ int round_tiles(int k, int G, int total) {
     const int left = total - k * G;
     return left < 0 ? 0 : (left < G ? left : G);
 }
-// This workgroup's tile of round k, `total` where it has none.  The workgroups of one XCD (blockIdx % 8) take a contiguous
+// Tiles that the workgroups of XCD x (blockIdx % 8) take in a round of n, of which the first is number `first`.
+struct Run {
+    int first, count;
+};
+__host__ __device__ __forceinline__ Run xcd_run(int x, int n, int G, bool deal) {
+    const int m = deal ? n : G, q = m >> 3, r = m & 7, first = x * q + (x < r ? x : r), own = q + (x < r ? 1 : 0);
+    const int left = n - first;
+    return {first, left < 0 ? 0 : (left < own ? left : own)};
+}
+// This workgroup's tile of round k, `total` where it has none.  The workgroups of one XCD take a contiguous
 // run, which the band order of locate_tile turns into an 8 x 4 block of tiles that share operand panels in that XCD's L2;
 // a last round is dealt out to all XCDs alike: left to the first of them, a round of 96 tiles runs at the speed of three XCDs' memory
 // paths.  Measured, us, first XCDs -> all: update of 8192 x 5120 x 5120 (400 tiles) 430 -> 364, its Y and dX (640) 400 -> 354; norm of
-// 4096 x 4096 x 22016 (1376) 623 -> 598, its update 654 -> 630; dX of 4096 x 11008 x 4096 (688) 325 -> 298.
-__device__ __forceinline__ int round_tile(int k, int G, int total) {
-    const int x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
-    const int n = round_tiles(k, G, total), q = n >> 3, r = n & 7;
-    return local < q + (x < r ? 1 : 0) ? k * G + x * q + (x < r ? x : r) + local : total;
+// 4096 x 4096 x 22016 (1376) 623 -> 598, its update 654 -> 630; dX of 4096 x 11008 x 4096 (688) 325 -> 298.  Where contractions differ and
+// that gives a workgroup with long tiles one more (choose_deal), it is left to the first: dX of a layer 8192 wide at 1280
+// tokens 1884 dealt out, 1800 not.
+__device__ __forceinline__ int round_tile(int k, int G, int total, bool deal) {
+    const Run run = xcd_run((int)(blockIdx.x & 7), round_tiles(k, G, total), G, deal);
+    const int local = (int)(blockIdx.x >> 3);
+    return local < run.count ? k * G + run.first + local : total;
+}
+// The tile of round k of a workgroup that had `w` in the round before: in a full round its place is the same.
+__device__ __forceinline__ int next_tile(int w, int k, int G, int total, bool deal) {
+    if (__builtin_expect((k + 1) * G <= total, 1)) return w + G;
+    return round_tile(k, G, total, deal);
 }
 
 // Tensor and origin of tile number w of the concatenated list.  A workgroup's tile numbers only grow, so the search for

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
 
     // ---- walk the tile list, one tile a round; every workgroup leaves through `break`
     int round = 0;
-    int w = round_tile(round, G, ga.total_tiles);
+    int w = round_tile(round, G, ga.total_tiles, ga.deal != 0);
     if (w >= ga.total_tiles) return;   // cannot happen with grid <= total_tiles; nothing was issued yet
     int tensor = 0;
     int64_t m0, n0;
@@ -301,7 +301,8 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
             re.fill(1);
             re.fill(2);
         }
-        w = round_tile(++round, G, ga.total_tiles);
+        ++round;
+        w = next_tile(w, round, G, ga.total_tiles, ga.deal != 0);
         const bool more = w < ga.total_tiles;
         if (more) {
             setup(w, tensor, m0, n0);
@@ -326,6 +327,7 @@ static hipError_t launch_wide(const GemmArgs* list, int n, hipStream_t st) {
         GroupArgs ga{};
         fill_group(ga, list + first, n - first < MAX_GROUP ? n - first : MAX_GROUP, BM, BN);
         const int grid = ga.total_tiles < cu_count() ? ga.total_tiles : cu_count();
+        ga.deal = choose_deal(ga, grid);
         hipError_t e = launch_timed(list[first].family, kern, dim3((unsigned)grid), dim3(NT), (size_t)LDS_BYTES, st, ga);
         if (e != hipSuccess) return e;
     }

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
     };
 
     int round = 0;
-    int w = dma::round_tile(round, G, ga.total_tiles);
+    int w = dma::round_tile(round, G, ga.total_tiles, true);
     if (w >= ga.total_tiles) return;   // grid <= total_tiles: cannot happen; nothing was issued yet
     int tensor, bi, bj;
     setup(w, tensor, bi, bj);
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
         int32_t* const flag_out = ga.t[tensor].flag_out;
         const int ebi = bi, ebj = bj;
 
-        w = dma::round_tile(++round, G, ga.total_tiles);
+        w = dma::round_tile(++round, G, ga.total_tiles, true);
         const bool more = w < ga.total_tiles;
         if (more) {
             setup(w, tensor, bi, bj);

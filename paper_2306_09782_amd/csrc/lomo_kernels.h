@@ -60,6 +60,12 @@ hipError_t launch_tile_group(const GemmArgs* list, int n, int tile, hipStream_t 
 
 int cu_count();      // of the current device; 256 where there is none
 
+// Whether the persistent kernels deal the last round of a launch out to all XCDs.
+namespace dma {
+struct GroupArgs;
+}
+int choose_deal(const dma::GroupArgs& ga, int workgroups);
+
 // The few tiles that a launch of the persistent kernels would have in a round of their own, as a piece of one tensor (the columns
 // m >= M of `kept`, or its rows n >= Nn) for the small tiles.
 struct Leftover {
@@ -68,6 +74,14 @@ struct Leftover {
     int tile;                 // the shape of tile for it
 };
 Leftover cut_leftover(const GemmArgs* list, int n, int product, bool a_strided, bool b_strided);
+
+// What the first launch of the persistent kernels does with its last round (for queries; `family` of the list's entries holds their
+// place).
+struct LastRound {
+    Leftover cut;
+    int tensor = -1, dealt = -1;      // the tensor that is cut; whether the round is dealt out, -1: no launch
+};
+LastRound last_round(const GemmArgs* list, size_t n, const int* tile_of, int product, bool a_strided, bool b_strided);
 
 // The tile shape of every tensor of a pass (M, Nn, C and persistent_only are read).  Product: what the epilogue does.
 enum Product { PRODUCT_STORE, PRODUCT_UPDATE, PRODUCT_NORM };

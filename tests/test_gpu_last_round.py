@@ -1,6 +1,8 @@
-"""The persistent contraction kernels deal the last round of a list, which has fewer tiles than there are CUs, out to all XCDs, and a
-round of up to a quarter of the CUs goes to small tiles as a piece of one tensor: counts one step off a multiple of the eight XCDs, of
-a quarter and of a round.  Every tile has to be computed once: norms against 64 bits (one of 300
+"""The persistent contraction kernels deal the last round of a list, which has fewer tiles than there are CUs, out to all XCDs, unless
+that makes the longest walk longer; where contractions are long enough to pay for it, a round of up to a quarter of the CUs goes to
+small tiles as a piece of one tensor.  Counts one step off a multiple of the eight XCDs, of a quarter and of a round: short
+contractions for the rounds (mostly no piece), longer ones for the pieces, which lomo_contraction_plan confirms.
+Every tile has to be computed once: norms against 64 bits (one of 300
 tiles is 0.3 % of the sum; fp32 sums over a tile, 2e-5 as in test_gpu_edges.py), stored outputs against 64 bits in full, updates against
 the same tensor in two calls."""
 import os
@@ -98,3 +100,70 @@ def test_piece_of_a_list(L, cut_tensor):
     L.lomo_step_update_pass(lst, 2.0 ** -6, 1.0, 1.0, flags[-1:], ws)
     for t, W in zip(tensors, alone):
         assert torch.equal(t["W"].view(torch.int16), W.view(torch.int16))
+
+
+FAMILY = {"norm": "wgrad_sqnorm", "update": "wgrad_update", "dgrad": "dgrad", "forward": "forward", "residual": "forward"}
+
+
+# tiles of rows and columns, ragged ends; the piece that is cut: two columns of tiles, or one row
+@pytest.mark.parametrize("rows,columns,piece", [(5, 53, (504, 1272)), (52, 5, (1272, 248))])
+@pytest.mark.parametrize("product", sorted(FAMILY))
+def test_piece(L, rows, columns, piece, product):
+    n, m, C = 256 * rows - 8, 256 * columns - 8, 1032
+    T, K, N = {"dgrad": (n, m, C), "forward": (n, C, m), "residual": (n, C, m)}.get(product, (C, m, n))
+    tiles, (tensor, cut, small, _) = L.lomo_contraction_plan(L.KERNEL_FAMILIES.index(FAMILY[product]), [(T, K, N)], product == "residual")
+    assert tiles == [(256, 256)] and tensor == 0 and cut == piece and small != (256, 256)
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    if product in ("norm", "update"):
+        X, dY = normal(gen, T, K), normal(gen, T, N)
+        G = dY.double().t().contiguous() @ X.double()
+        if product == "norm":
+            acc, flag = torch.zeros(1, dtype=torch.float64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+            L.lomo_wgrad_sqnorm(X, dY, acc, flag)
+            assert abs(float(acc.item()) / float(G.pow(2).sum()) - 1) < 2e-5 and int(flag.item()) == 0
+            # an element of the piece alone raises the flag
+            (dY if cut[1] < cut[0] else X)[3, -1] = float("inf")
+            L.lomo_wgrad_sqnorm(X, dY, acc, flag)
+            assert int(flag.item()) == 1
+        else:
+            W = normal(gen, N, K)
+            whole, half = W.clone(), N // 16 * 8
+            L.lomo_linear_backward_update(X, dY, whole, None, 2.0 ** -6, 1.0, 1.0)
+            for part in (slice(0, half), slice(half, N)):
+                one = W[part].clone()
+                L.lomo_linear_backward_update(X, dY[:, part].contiguous(), one, None, 2.0 ** -6, 1.0, 1.0)
+                assert torch.equal(one.view(torch.int16), whole[part].view(torch.int16))
+            want = W.double() - 2.0 ** -6 * G
+            assert bool(((whole.double() - want).abs() <= 2.0 ** -11 * want.abs() + 2.0 ** -20 * 2.0 ** -6 * T * 8).all())
+        return
+    B, W, out, R = normal(gen, T, C), normal(gen, N, K), torch.full((T, m), 7.0, dtype=torch.float16, device=DEV), None
+    if product == "residual":
+        R = normal(gen, T, m)
+        L.lomo_linear_forward_residual(B, W, R, out)
+    else:
+        (L.lomo_linear_dgrad if product == "dgrad" else L.lomo_linear_forward)(B, W, out)
+    b, w = B.double(), W.double() if product == "dgrad" else W.double().t().contiguous()
+    want, mag = b @ w, b.abs() @ w.abs()
+    if R is not None:
+        want, mag = want + R.double(), mag + R.double().abs()
+    assert bool(((out.double() - want).abs() <= 2.0 ** -11 * want.abs() + 2.0 ** -20 * mag).all())
+
+
+@pytest.mark.parametrize("order", ["dealt out", "left to the first XCDs"])
+def test_last_round_of_a_list_of_different_contractions(L, order):
+    """96 tiles in the last round: where the first XCDs' workgroups have had short contractions in every round, and dealt out some would
+    come on top of long ones, they stay with the first."""
+    short, long_ = (2560, 1032), (1536, 2056)      # (K, N) of dX: 160 tiles and 96
+    shapes = [short, long_] * 2 + [(1536, 1032)] if order != "dealt out" else [long_, short] * 2 + [(1536, 1032)]
+    T, gen = 4088, torch.Generator(device=DEV).manual_seed(2)
+    tiles, (tensor, _, _, dealt) = L.lomo_contraction_plan(L.KERNEL_FAMILIES.index("dgrad"), [(T, K, N) for K, N in shapes])
+    assert set(tiles) == {(256, 256)} and tensor is None and dealt == (order == "dealt out")
+    tensors = [{"kind": "linear", "X": torch.zeros(T, K, dtype=torch.float16, device=DEV), "dY": normal(gen, T, N), "W": normal(gen, N, K),
+                "dX": torch.full((T, K), 7.0, dtype=torch.float16, device=DEV)} for K, N in shapes]
+    lst = L.make_tensor_list(tensors)
+    ws = torch.empty(max(256, L.lomo_step_workspace_bytes(lst)), dtype=torch.uint8, device=DEV)
+    L.lomo_step_update_pass(lst, 2.0 ** -6, 1.0, 1.0, torch.zeros(1, dtype=torch.int32, device=DEV), ws)      # X is zero: W stays
+    for t in tensors:
+        alone = torch.empty_like(t["dX"])
+        L.lomo_linear_dgrad(t["dY"], t["W"], alone)
+        assert torch.equal(alone.view(torch.int16), t["dX"].view(torch.int16))
