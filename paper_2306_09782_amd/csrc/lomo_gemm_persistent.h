@@ -49,11 +49,23 @@ __device__ __forceinline__ int next_tile(int w, int k, int G, int total, bool de
 
 // Tensor and origin of tile number w of the concatenated list.  A workgroup's tile numbers only grow, so the search for
 // the tile's tensor resumes at the previous tile's.
+// COLUMNS: outputs of five or six rows of tiles go column by column (dX of 1025 to 1536 tokens), so that the panel of W behind a column, which
+// comes from HBM, is read by one XCD, or two; bands of 8 x 4 tiles split such outputs over two XCDs each.  Measured, us, bands -> columns: dX
+// of two layers 5120 wide at 1070 tokens 1338 -> 1308, at 1280 1437 -> 1392, at 1536 1655 -> 1602, of one 8192 wide at 1280 1788 -> 1729; but
+// two 4096 wide at 1792 (seven rows) 1230 -> 1237, and Y of 1536 x 22016 251 -> 255: forward products keep the bands.
+template <bool COLUMNS = false>
 __device__ __forceinline__ void locate_tile(const GroupArgs& ga, int w, int& tensor, int64_t& m0, int64_t& n0) {
     int k = tensor;
     while (k + 1 < ga.n && w >= ga.t[k + 1].tile_begin) ++k;
     const GroupTensor& T = ga.t[k];
     const int t = w - T.tile_begin;
+    if (COLUMNS && (T.tiles_n == 5 || T.tiles_n == 6)) {
+        const int m = t / T.tiles_n;
+        tensor = k;
+        m0 = (int64_t)m * BM;
+        n0 = (int64_t)(t - m * T.tiles_n) * BN;
+        return;
+    }
     constexpr int GM = 8;
     const int per_band = GM * T.tiles_n;
     const int band = t / per_band;

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
     };
 
     auto setup = [&](int w, int& tensor, int64_t& m0, int64_t& n0) {
-        locate_tile(ga, w, tensor, m0, n0);
+        locate_tile<A_STRIDED>(ga, w, tensor, m0, n0);
         const GroupTensor& T = ga.t[tensor];
         const int m_left = T.M - (int)m0;
         const int row8 = lane >> 3, chunk = (lane & 7) ^ swz_w(row8);      // of eight rows of 128 bytes

@@ -40,7 +40,7 @@ def test_norm(L, tiles):
     assert abs(float(acc.item()) / want - 1) < 2e-5
 
 
-@pytest.mark.parametrize("rows,columns", [(5, 77), (5, 115), (7, 73), (7, 111), (11, 35)])       # of tiles: 385, 575, 511, 777, 385
+@pytest.mark.parametrize("rows,columns", [(5, 77), (5, 115), (6, 75), (7, 73), (7, 111), (11, 35)])       # of tiles: 385, 575, 450, 511, 777, 385
 @pytest.mark.parametrize("product", ["dgrad", "forward", "residual"])
 def test_stored(L, rows, columns, product):
     T, M, C = 256 * rows - 8, 256 * columns - 8, 248
