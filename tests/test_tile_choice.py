@@ -20,6 +20,13 @@ def test_lists_that_fill_the_chip_stay_together(H, F, T, layers, family):
     assert set(L.lomo_contraction_tiles(family, layer_stack(H, F, T, layers))) == {(256, 256)}
 
 
+@pytest.mark.parametrize("family,H,F,T,layers,vocabulary", [(DGRAD, 5120, 13824, 2100, 1, 0), (DGRAD, 5120, 13824, 1070, 3, 32000),
+                                                            (UPDATE, 1024, 2816, 6000, 2, 32000), (NORM, 1024, 2816, 6000, 2, 32000)])
+def test_a_gain_within_the_error_of_the_times_splits_no_list(family, H, F, T, layers, vocabulary):
+    shapes = layer_stack(H, F, T, layers) + [(T, H, vocabulary)] * bool(vocabulary)
+    assert set(L.lomo_contraction_tiles(family, shapes)) == {(256, 256)}
+
+
 @pytest.mark.parametrize("family,shape", [(UPDATE, (512, 1024, 1024)), (NORM, (512, 1024, 1024)), (DGRAD, (512, 1024, 1024)),
                                           (FORWARD, (256, 1024, 3072)), (DGRAD, (1024, 4096, 4096)), (DGRAD, (256, 1024, 32000))])
 def test_a_tensor_of_few_tiles_takes_small_ones_alone(family, shape):
