@@ -288,44 +288,36 @@ constexpr size_t kGreedyShapes = 64;     // lists of more shapes than this take 
 namespace {
 struct Shape {
     int64_t M, Nn, C;
-    double count;
-    int tile;
     bool fixed;      // stays in the persistent kernel
+    int tile = TILE_256;
+    double n[N_TILES];      // tiles of each shape, of all tensors together
+    Shape(int64_t m, int64_t nn, int64_t c, bool persistent_only) : M(m), Nn(nn), C(c), fixed(persistent_only) {
+        for (int t = 0; t < N_TILES; ++t) n[t] = (double)((M + kTile[t].m - 1) / kTile[t].m) * (double)((Nn + kTile[t].n - 1) / kTile[t].n);
+    }
 };
 }  // namespace
 
-// Time of the launches of one tile shape; shapes come longest contraction first.
-static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int product, double cus) {
-    const TileCost& k = kTile[tile];
-    double tiles = 0.0, indices = 0.0, longest = 0.0;       // indices: contraction indices walked by all tiles together
-    for (size_t i = 0; i < n_shapes; ++i) {
-        const Shape& s = shapes[i];
-        if (s.tile != tile) continue;
-        if (tile == TILE_64_32 && s.C <= kShort) return 1e30;
-        const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
-        tiles += n;
-        indices += n * (double)s.C;
+namespace {
+// What a launch's time is reckoned from: its tiles, the contraction indices that they walk together, the longest contraction.
+struct Sum {
+    double tiles = 0.0, indices = 0.0, longest = 0.0;
+    bool out = false;      // a tensor that TILE_64_32 leaves out
+    void add(const Shape& s, int tile) {
+        tiles += s.n[tile];
+        indices += s.n[tile] * (double)s.C;
         longest = std::max(longest, (double)s.C);
+        out |= tile == TILE_64_32 && s.C <= kShort;
     }
-    if (tiles == 0.0) return 0.0;
-    const double per_cu = tiles / cus, mean = indices / tiles, f = k.fixed[product];
+};
+}  // namespace
+
+// Time of the launches of a tile shape other than the persistent kernels'.
+static double launch_time(const Sum& sum, int tile, int product, double cus) {
+    if (sum.tiles == 0.0) return 0.0;
+    if (sum.out) return 1e30;
+    const TileCost& k = kTile[tile];
+    const double per_cu = sum.tiles / cus, mean = sum.indices / sum.tiles, longest = sum.longest, f = k.fixed[product];
     const double latency = k.latency[product == PRODUCT_STORE], through = k.through[product == PRODUCT_STORE];
-    if (tile == TILE_256) {
-        // A workgroup walks one tile per round, so a round takes as long as its first tile; a round that is not full takes less
-        // (a tile is faster when it has the memory system to itself).
-        double time = kLaunch, seen = 0.0;
-        for (size_t i = 0; i < n_shapes; ++i) {
-            const Shape& s = shapes[i];
-            if (s.tile != tile) continue;
-            const double n = s.count * (double)((s.M + k.m - 1) / k.m) * (double)((s.Nn + k.n - 1) / k.n);
-            const double from = ceil(seen / cus), to = ceil((seen + n) / cus);      // the rounds that begin with this shape
-            const double full = std::max(0.0, std::min(to, floor(per_cu)) - from);
-            time += full * (f + through * (double)s.C);
-            if (to - from > full) time += f + (latency + (through - latency) * (per_cu - floor(per_cu))) * (double)s.C;
-            seen += n;
-        }
-        return time;
-    }
     // a partly filled round costs 0.7 of a full one, or what it has of it
     const double rounds = std::max(per_cu, floor(per_cu) + (per_cu > floor(per_cu) ? 0.7 : 0.0));
     const double waves = ceil(per_cu / k.per_cu);
@@ -333,6 +325,37 @@ static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int pr
     const double busy = std::min(longest, mean * per_cu);
     return kLaunch + std::max(waves * f + mean * std::max(latency * waves, through * rounds),
                               f + (longest > mean ? through * busy + latency * (longest - busy) : longest * std::max(latency, 0.7 * through)));
+}
+
+static Sum sum_of(const Shape* shapes, size_t n_shapes, int tile) {
+    Sum sum;
+    for (size_t i = 0; i < n_shapes; ++i)
+        if (shapes[i].tile == tile) sum.add(shapes[i], tile);
+    return sum;
+}
+
+// Time of the launches of one tile shape; shapes come longest contraction first (the persistent launch, whose time depends on the order,
+// mostly takes the caller's, which costs as much or less).
+static double launch_time(const Shape* shapes, size_t n_shapes, int tile, int product, double cus) {
+    const Sum sum = sum_of(shapes, n_shapes, tile);
+    if (tile != TILE_256 || sum.tiles == 0.0) return launch_time(sum, tile, product, cus);
+    const TileCost& k = kTile[tile];
+    const double per_cu = sum.tiles / cus, f = k.fixed[product];
+    const double latency = k.latency[product == PRODUCT_STORE], through = k.through[product == PRODUCT_STORE];
+    // A workgroup walks one tile per round, so a round takes as long as its first tile; a round that is not full takes less
+    // (a tile is faster when it has the memory system to itself).
+    double time = kLaunch, seen = 0.0;
+    for (size_t i = 0; i < n_shapes; ++i) {
+        const Shape& s = shapes[i];
+        if (s.tile != tile) continue;
+        const double n = s.n[tile];
+        const double from = ceil(seen / cus), to = ceil((seen + n) / cus);      // the rounds that begin with this shape
+        const double full = std::max(0.0, std::min(to, floor(per_cu)) - from);
+        time += full * (f + through * (double)s.C);
+        if (to - from > full) time += f + (latency + (through - latency) * (per_cu - floor(per_cu))) * (double)s.C;
+        seen += n;
+    }
+    return time;
 }
 
 // Contraction indices of the longest walk of G workgroups of a persistent kernel over tensors of tiles(i) tiles with contractions of
@@ -410,44 +433,79 @@ static int best_alone(Shape one, int product, double cus) {
 
 // Starting choices: all tensors in the persistent kernel, all in the shape of tile that is best for all together, and each in the
 // one that is best for it alone; from each, one shape after the other (longest contraction first) moves to where the pass is
-// shortest.
+// shortest.  A move changes two launches of the pass, and only these are reckoned again (60 different shapes 815 -> 150 us on the host,
+// two layers and a vocabulary 16 -> 12.5, the binding's part included).
 void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
     const double cus = (double)cu_count();
     std::vector<Shape> shapes;
+    std::vector<int> count;
     auto same = [&](const Shape& s, const GemmArgs& a) { return s.M == a.M && s.Nn == a.Nn && s.C == a.C; };
     for (size_t i = 0; i < n; ++i) {
         size_t k = 0;
         while (k < shapes.size() && !same(shapes[k], list[i])) ++k;
-        if (k == shapes.size()) shapes.push_back({list[i].M, list[i].Nn, list[i].C, 0.0, TILE_256, list[i].persistent_only});
-        shapes[k].count += 1.0;
+        if (k == shapes.size()) {
+            shapes.emplace_back(list[i].M, list[i].Nn, list[i].C, list[i].persistent_only);
+            count.push_back(0);
+        }
+        ++count[k];
     }
-    std::stable_sort(shapes.begin(), shapes.end(), [](const Shape& x, const Shape& y) { return x.C > y.C; });
+    std::vector<Shape> alone = shapes;      // a list of one shape is its own
+    for (size_t k = 0; k < shapes.size(); ++k) {
+        for (double& t : shapes[k].n) t *= (double)count[k];
+        alone[k].tile = best_alone(shapes.size() > 1 ? alone[k] : shapes[k], product, cus);
+        std::copy(shapes[k].n, shapes[k].n + N_TILES, alone[k].n);
+    }
+    auto longer = [](const Shape& x, const Shape& y) { return x.C > y.C; };
+    std::stable_sort(shapes.begin(), shapes.end(), longer);
+    std::stable_sort(alone.begin(), alone.end(), longer);
     auto improve = [&](std::vector<Shape>& v) {
-        double best = pass_time(v, product, cus);
+        double launch[N_TILES];
+        Sum sums[N_TILES];
+        for (int tile = 0; tile < N_TILES; ++tile) {
+            launch[tile] = launch_time(v.data(), v.size(), tile, product, cus);
+            sums[tile] = sum_of(v.data(), v.size(), tile);
+        }
+        auto sum = [&](int a, double ta, int b, double tb) {
+            double t = 0.0;
+            for (int tile = 0; tile < N_TILES; ++tile) t += tile == a ? ta : tile == b ? tb : launch[tile];
+            return t;
+        };
+        double best = sum(-1, 0.0, -1, 0.0);
         for (int sweep = 0; sweep < 3 && v.size() <= kGreedyShapes; ++sweep) {
             bool moved = false;
-            for (size_t k = 0; k < v.size(); ++k) {
-                if (v[k].fixed) continue;
-                const int was = v[k].tile;
+            for (Shape& s : v) {
+                if (s.fixed) continue;
+                const int was = s.tile;
                 int to = was;
+                s.tile = -1;
+                const double without = launch_time(v.data(), v.size(), was, product, cus);
+                double with = launch[was];
                 for (int tile = 0; tile < N_TILES; ++tile) {
                     if (tile == was) continue;
-                    v[k].tile = tile;
-                    const double t = pass_time(v, product, cus);
+                    s.tile = tile;
+                    Sum more = sums[tile];
+                    more.add(s, tile);
+                    const double there = tile == TILE_256 ? launch_time(v.data(), v.size(), tile, product, cus)
+                                                          : launch_time(more, tile, product, cus);
+                    const double t = sum(was, without, tile, there);
                     if (t < best) {
                         best = t;
                         to = tile;
+                        with = there;
                     }
                 }
-                v[k].tile = to;
-                moved |= to != was;
+                s.tile = to;
+                if (to == was) continue;
+                launch[was] = without;
+                launch[to] = with;
+                sums[was] = sum_of(v.data(), v.size(), was);
+                sums[to].add(s, to);
+                moved = true;
             }
             if (!moved) break;
         }
         return best;
     };
-    std::vector<Shape> alone = shapes;
-    for (Shape& s : alone) s.tile = best_alone({s.M, s.Nn, s.C, shapes.size() > 1 ? 1.0 : s.count, 0, s.fixed}, product, cus);
     if (shapes.size() > 1) {
         std::vector<Shape> same_tile = shapes;
         auto all_in = [&](int tile) {
@@ -503,7 +561,7 @@ Leftover cut_leftover(const GemmArgs* list, int n, int product, bool a_strided, 
             const int64_t k = (left + across - 1) / across;      // columns or rows of tiles to take away
             if (k >= along) continue;
             const int64_t at = (along - k) * 256;
-            Shape piece{columns ? a.M - at : a.M, columns ? a.Nn : a.Nn - at, a.C, 1.0, TILE_256, false};
+            Shape piece(columns ? a.M - at : a.M, columns ? a.Nn : a.Nn - at, a.C, false);
             // the round that is saved, by the measurements above
             double time = kTile[TILE_256].fixed[product] + 0.0215 * (double)list[n - 1].C;
             int tile = TILE_256;
@@ -598,7 +656,7 @@ static hipError_t launch_list(const GemmArgs* list, size_t n, hipStream_t st) tr
         if (any_shape(*list)) return launch_generic<B_STRIDED, EPI, A_STRIDED>(*list, st);
         GemmArgs one = *list;
         one.persistent_only = beyond_descriptor<B_STRIDED, A_STRIDED>(one);
-        const Shape s{one.M, one.Nn, one.C, 1.0, TILE_256, one.persistent_only};
+        const Shape s(one.M, one.Nn, one.C, one.persistent_only);
         return launch_with<B_STRIDED, EPI, A_STRIDED>(best_alone(s, product, (double)cu_count()), &one, 1, st);
     }
     std::vector<GemmArgs> fit, by[N_TILES];

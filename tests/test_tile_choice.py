@@ -1,5 +1,7 @@
 """Which shape of tile the contractions of a call take (host function, no GPU): alone, a tensor of few tiles takes small ones; in
 a list whose tensors fill the chip together, all stay in the persistent kernel, except a long contraction of few tiles."""
+import time
+
 import pytest
 
 import paper_2306_09782_amd as L
@@ -56,6 +58,22 @@ def test_only_very_long_rows_leave_the_kernels_with_descriptors():
     for family in (UPDATE, NORM, DGRAD, FORWARD):
         assert L.lomo_contraction_tiles(family, [(8, 9_000_000, 8)]) == [(0, 0)]
         assert L.lomo_contraction_tiles(family, [(8, 7_000_000, 8)])[0] != (0, 0)
+
+
+def test_host_time_of_a_list_of_many_shapes():
+    """The choice for a list of 60 different shapes takes about as long as 60 choices for one of them; reckoning the whole pass
+    again for every move that is tried took five times as long, half that before there were six shapes of tile."""
+    shapes = [(1024, 8 * (100 + 37 * i % 1400), 8 * (100 + 91 * i % 1400)) for i in range(60)]
+
+    def least(f):
+        times = []
+        for _ in range(20):
+            begin = time.perf_counter()
+            f()
+            times.append(time.perf_counter() - begin)
+        return min(times)
+
+    assert least(lambda: L.lomo_contraction_tiles(DGRAD, shapes)) < 2.5 * least(lambda: [L.lomo_contraction_tiles(DGRAD, [s]) for s in shapes])
 
 
 def test_bad_arguments():
