@@ -255,8 +255,11 @@ static bool fast_enabled() {
 //     that waits for HBM takes 1.2 to 1.4 times as long per index: about 2.4 ns for each 128-byte line that its CU fetches, against
 //     1.75 ns from the cache.  A ring twice as deep does not change that (128 x 64, 128 x 128, 64 x 64 and 64 x 32 tiles of 64 to 1024
 //     tokens, one workgroup on a CU: all within 1 %), fewer lines per index and more CUs do.  So they are fitted to products that
-//     go through 2 GiB of weights in turn, 77 shapes of 64 to 1024 tokens; there the choice is the fastest tile of every shape
-//     (with the times from warm weights 2.4 % above it on average, 36 % at the worst: dX of 512 x 13824, C = 5120, 116 against 85).
+//     go through 2 GiB of weights in turn, 77 shapes of 64 to 1024 tokens; there the choice is the fastest tile of each of
+//     them (with the times from warm weights 2.4 % above it on average, 36 % at the worst: dX of 512 x 13824, C = 5120, 116 against 85).
+//     Outside the fit they are less exact: dX of two layers 4096 wide with a vocabulary at 512 tokens is reckoned 600 in 256 x 128 tiles
+//     and takes 677, while the choice before, 128 x 128 for all but the square tensors, takes 668.
+//     Forward products with a residual are priced as updates, from warm weights.
 //   * 256 x 128 tiles take the same time as the persistent kernel over several rounds, but more power: dX of a 13B layer at 874
 //     tokens 655 us either way, while the norm and the update behind it go from 546 and 657 to 574 and 700.  `through` of 0.0166
 //     instead of the fitted 0.0142 leaves such lists to the persistent kernel (the pass 1900 -> 1855 us).
@@ -542,7 +545,7 @@ void choose_tiles(const GemmArgs* list, size_t n, int product, int* tile_of) {
 }
 
 // A last round of a few tiles takes nearly as long as a full one (the workgroups have few neighbours to share panels with and wait
-// for memory), small tiles spread the same work over the chip.  Measured, us, norm of T = 4096 and 4096 columns: 512 + 16, + 32, + 64
+// for memory, so an index takes more than `latency`), small tiles spread the same work over the chip.  Measured, us, norm of T = 4096 and 4096 columns: 512 + 16, + 32, + 64
 // tiles 315, 315, 325 against 224 for the 512; a list of 12 rounds and 16 tiles 1361.
 Leftover cut_leftover(const GemmArgs* list, int n, int product, bool a_strided, bool b_strided) {
     Leftover best;

@@ -74,7 +74,6 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     const int wm = wave & 1, wn = wave >> 1;
     const int G = gridDim.x;
 
-
     // round alignment (update kernels): how many workgroups of this XCD have a tile in round k
     constexpr bool ALIGN_ROUNDS = EPI == EPI_UPDATE || EPI == EPI_CLIPV;
     const int xcd = (int)(blockIdx.x & 7);
@@ -104,16 +103,6 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
     int64_t a_left = 0, b_left = 0;
     uint32_t a_move = ~0u, b_move = ~0u;
     int KT = 0;                            // slices walked: a multiple of 4
-
-    // Puts the base of an operand at its next slice.
-    auto move_base = [](int4v& srd, int64_t& left, uint32_t& next, uint32_t& end, uint32_t& move) {
-        left -= next;
-        const uint64_t base = (((uint64_t)(uint32_t)srd[1] << 32) | (uint32_t)srd[0]) + next;
-        srd = make_srd((const void*)base, range_bytes(left / 2));
-        next = 0;
-        end = (uint32_t)srd[2];
-        move = left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
-    };
 
     // Locate tile number w of the concatenated list; set up the load state; return its coordinates.
     // A workgroup's tile numbers only grow, so the search for the tile's tensor resumes at the previous tile's.
@@ -296,7 +285,7 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         // epilogue arguments of the tile just finished
         GemmArgs g;
         g.Out = ga.t[tensor].Out;
-        g.Res = ga.t[tensor].Res;
+        g.Res = nullptr;
         g.ldo = ga.t[tensor].ldo;
         g.M = ga.t[tensor].M;
         g.Nn = ga.t[tensor].Nn;
@@ -318,11 +307,9 @@ __global__ __launch_bounds__(NT) void lomo_contract_dma_kernel(dma::GroupArgs ga
         }
         if constexpr (EPI != EPI_SQNORM) {
             const RowEpilogue re(g, smem, wave, em0, en0);
-            if constexpr (EPI != EPI_STORE) {
-                re.fill(0);
-                re.fill(1);
-                re.fill(2);
-            }
+            re.fill(0);
+            re.fill(1);
+            re.fill(2);
             if (more) {
                 setup(w, tensor, m0, n0);
                 issue_prologue();

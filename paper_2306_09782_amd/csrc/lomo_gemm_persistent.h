@@ -77,6 +77,17 @@ __device__ __forceinline__ void locate_tile(const GroupArgs& ga, int w, int& ten
     n0 = (int64_t)(in_band / gsz) * BN;
 }
 
+// Puts the base of a contraction-strided operand larger than a descriptor covers at its next slice: bytes left to the operand's end, offset
+// of the next slice, where the slices end, and from which offset on the base moves again.
+__device__ __forceinline__ void move_base(int4v& srd, int64_t& left, uint32_t& next, uint32_t& end, uint32_t& move) {
+    left -= next;
+    const uint64_t base = (((uint64_t)(uint32_t)srd[1] << 32) | (uint32_t)srd[0]) + next;
+    srd = make_srd((const void*)base, range_bytes(left / 2));
+    next = 0;
+    end = (uint32_t)srd[2];
+    move = left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
+}
+
 // ---- row epilogue (update / store) --------------------------------------------------------------------
 // The accumulator layout gives a lane 16 bytes of one output row at a time, so a wave instruction on global
 // memory would touch 32 rows x 32 bytes.  Here each wave stages 32 x 64 blocks of its 128 x 128 sub-tile in

@@ -123,16 +123,6 @@ __global__ __launch_bounds__(NT) void lomo_contract_wide_kernel(dma::GroupArgs g
         }
     };
 
-    // Puts the base of a strided operand at its next slice.
-    auto move_base = [](int4v& srd, int64_t& left, uint32_t& next, uint32_t& end, uint32_t& move) {
-        left -= next;
-        const uint64_t base = (((uint64_t)(uint32_t)srd[1] << 32) | (uint32_t)srd[0]) + next;
-        srd = make_srd((const void*)base, range_bytes(left / 2));
-        next = 0;
-        end = (uint32_t)srd[2];
-        move = left > (int64_t)MAX_RANGE ? MOVE_BASE : ~0u;
-    };
-
     // One of this wave's eight load instructions of an operand's next slot; behind the last slot (slice) all of it is out of
     // range.  A contraction-contiguous operand goes on with its next row behind the last index: those lanes are masked from
     // the last slot on (nothing follows it).

@@ -337,16 +337,6 @@ __global__ __launch_bounds__(NT) void lomo_gram_sqnorm_kernel(gram::GroupArgs ga
 
 // ---- host side ----------------------------------------------------------------------------
 
-static int gram_cu_count() {
-    static const int n = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
-        return v;
-    }();
-    return n;
-}
-
 // `a` is a norm-pass contraction (A = X [C x M], B = dY [C x Nn], dense rows).
 bool gram_eligible(const GemmArgs& a) {
     using namespace gram;
@@ -373,12 +363,13 @@ static void gram_launch_order(std::vector<GemmArgs>& v) {
     std::stable_sort(v.begin(), v.end(), [](const GemmArgs& x, const GemmArgs& y) { return x.M + x.Nn > y.M + y.Nn; });
 }
 
-// When the Gram launches of these tensors finish, in the same units: workgroup p of a launch walks tiles p, p + G, ...
-// (the kernel's static assignment), every tile of a tensor costs the same, and a launch ends with its busiest workgroup.
+// When the Gram launches of these tensors finish, in the same units: workgroup p of a launch is taken to walk tiles p, p + G, ...,
+// every tile of a tensor costs the same, and a launch ends with its busiest workgroup.  An approximation: the kernel deals the last round,
+// whose tiles are the shortest, out to other workgroups.
 // A few hundred long tiles on 256 CUs end far later than (total work) / (number of CUs) says.
 static double gram_finish_time(std::vector<GemmArgs> v) {
     gram_launch_order(v);
-    const int cus = gram_cu_count();
+    const int cus = cu_count();
     double total = 0.0;
     std::vector<double> load;
     for (size_t first = 0; first < v.size(); first += gram::MAX_GROUP) {
@@ -414,7 +405,7 @@ void choose_norm_route(int mode, const std::vector<GemmArgs>& all, std::vector<G
     // their work), the Gram tiles are long and few.
     double work_d = 0.0;
     for (const GemmArgs& a : gram) work_d += direct_cost(a);
-    if (gram_finish_time(gram) >= work_d / (double)gram_cu_count()) {
+    if (gram_finish_time(gram) >= work_d / (double)cu_count()) {
         direct.insert(direct.end(), gram.begin(), gram.end());
         gram.clear();
     }
@@ -446,7 +437,7 @@ hipError_t launch_gram_group(const GemmArgs* list, int n, hipStream_t st) {
             tiles += t.tiles_m * (t.tiles_m + 1);
         }
         ga.total_tiles = tiles;
-        const int grid = tiles < gram_cu_count() ? tiles : gram_cu_count();
+        const int grid = tiles < cu_count() ? tiles : cu_count();
         hipError_t e = launch_timed(LOMO_KERNEL_GRAM_SQNORM, kern, dim3((unsigned)grid), dim3(NT), (size_t)LDS_BYTES, st, ga);
         if (e != hipSuccess) return e;
     }

@@ -12,6 +12,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+FAMILY = {"norm": "wgrad_sqnorm", "update": "wgrad_update", "dgrad": "dgrad", "forward": "forward", "residual": "forward"}
 
 
 @pytest.fixture(scope="module")
@@ -45,8 +46,7 @@ def test_norm(L, tiles):
 def test_stored(L, rows, columns, product):
     T, M, C = 256 * rows - 8, 256 * columns - 8, 248
     K, N = (M, C) if product == "dgrad" else (C, M)
-    if product != "residual":
-        assert L.lomo_contraction_tiles(L.KERNEL_FAMILIES.index(product), [(T, K, N)]) == [(256, 256)]
+    assert L.lomo_contraction_plan(L.KERNEL_FAMILIES.index(FAMILY[product]), [(T, K, N)], product == "residual")[0] == [(256, 256)]
     gen = torch.Generator(device=DEV).manual_seed(columns)
     B, W, out, R = normal(gen, T, C), normal(gen, N, K), torch.full((T, M), 7.0, dtype=torch.float16, device=DEV), None
     if product == "residual":
@@ -100,9 +100,6 @@ def test_piece_of_a_list(L, cut_tensor):
     L.lomo_step_update_pass(lst, 2.0 ** -6, 1.0, 1.0, flags[-1:], ws)
     for t, W in zip(tensors, alone):
         assert torch.equal(t["W"].view(torch.int16), W.view(torch.int16))
-
-
-FAMILY = {"norm": "wgrad_sqnorm", "update": "wgrad_update", "dgrad": "dgrad", "forward": "forward", "residual": "forward"}
 
 
 # tiles of rows and columns, ragged ends; the piece that is cut: two columns of tiles, or one row

@@ -19,7 +19,7 @@ def test_step(L, T, K, N):
 @pytest.mark.parametrize("T,K,N", [(1000, 2056, 5128), (2040, 2056, 2056)])
 @pytest.mark.parametrize("residual", [False, True])
 def test_forward(L, T, K, N, residual):
-    assert L.lomo_contraction_tiles(L.KERNEL_FAMILIES.index("forward"), [(T, K, N)]) == [(256, 128)]
+    assert L.lomo_contraction_plan(L.KERNEL_FAMILIES.index("forward"), [(T, K, N)], residual)[0] == [(256, 128)]
     X, W, R = f16(31, (T, K), 1.0), f16(32, (N, K), 0.05), f16(33, (T, N), 1.0)
     Y, few = Guarded((T, N)), torch.empty(8, N, dtype=torch.float16, device=DEV)
     if residual:
