@@ -38,16 +38,21 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def profiled_traffic(workload_name):
-    """HBM-side bytes per launch of the fused kernel, from the committed rocprofv3 --pmc summary of this workload."""
+def profiled_traffic(workload_name, launches_per_pass):
+    """HBM-side bytes per launch of the fused update (of all its launches in a pass, the pieces of last rounds among them), from the
+    committed rocprofv3 --pmc summary of this workload; none if the summary's passes have another number of launches."""
     rel = os.path.join("profiles", f"lomo_contract_{workload_name}_hbm_traffic.txt")
+    found = {}
     try:
         for line in open(os.path.join(ROOT, rel)):
-            if "traffic_bytes_per_launch:" in line:
-                return int(line.split("traffic_bytes_per_launch:")[1].split()[0]), rel
+            for key in ("traffic_bytes_per_pass:", "launches_per_pass:"):
+                if key in line:
+                    found[key] = int(line.split(key)[1].split()[0])
     except OSError:
         pass
-    return None, None
+    if found.get("launches_per_pass:") != launches_per_pass or "traffic_bytes_per_pass:" not in found:
+        return None, None
+    return found["traffic_bytes_per_pass:"] / launches_per_pass, rel
 
 
 def cpu_baseline(wl):
@@ -495,14 +500,15 @@ def main():
     if k1:
         # the committed counter summary describes the whole named workload, launched as this run launches it
         whole = args.workload == wl.name and not args.per_tensor_calls and not args.no_dgrad
-        traffic, traffic_src = profiled_traffic(wl.name) if whole else (None, None)
+        launches_per_pass = k1["launches"] / args.steps
+        traffic, traffic_src = profiled_traffic(wl.name, launches_per_pass) if whole else (None, None)
         algorithmic_bytes = sum(2 * s.T * (s.N + s.K) + 4 * s.N * s.K for s in wl.tensors if s.kind == "linear")
-        roofline = {"kernel": "fused wgrad + SGD update (lomo_contract_dma_kernel<EPI_UPDATE>)", "bound": "mfma",
+        roofline = {"kernel": "fused wgrad + SGD update (lomo_contract_dma_kernel<EPI_UPDATE>, and pieces of its last rounds in small tiles)", "bound": "mfma",
                     "achieved": k1["tflops"], "peak": PEAK_FP16_TFLOPS, "unit": "TFLOP/s",
                     "frac": k1["tflops"] / PEAK_FP16_TFLOPS, "traffic": traffic, "traffic_source": traffic_src,
                     "flops_per_launch": main_rec["flops_per_pass"] * args.steps / k1["launches"],
                     "algorithmic_bytes_per_launch": algorithmic_bytes * args.steps / k1["launches"],
-                    "avg_launch_ms": k1["avg_launch_ms"], "launches_timed": k1["launches"],
+                    "avg_launch_ms": k1["avg_launch_ms"], "launches_timed": k1["launches"], "launches_per_pass": launches_per_pass,
                     "timing": "HIP events attached to each dispatch on its launch stream (hipExtLaunchKernelGGL)"}
 
     out = {
