@@ -9,7 +9,8 @@
 // SPLIT = 2, for calls that give too few of these: a workgroup owns 64 rows, two waves have the same 32, and each takes one half
 // of every moving tile.  The forward puts their sums together at the end, as it does with the halves of one wave; the
 // backward kernels hand P and dS over through LDS, each wave having a part of the sums.  Every sum has the same terms in the
-// same order either way, so a call's size does not show in its results.
+// same order either way, so a call's size does not show in its results.  (The backward of sequences of one block is one kernel that does the
+// same on tiles that stay where they are.)
 #pragma once
 #include "lomo_gemm_common.h"
 
@@ -20,8 +21,8 @@ typedef short short4a __attribute__((ext_vector_type(4)));
 namespace attn {
 
 constexpr int D = 128;                 // head width
-template <int SPLIT, int WAVES = 4>
-constexpr int ROWS = 32 * WAVES / SPLIT;      // rows of a workgroup
+template <int SPLIT>
+constexpr int ROWS = 128 / SPLIT;      // rows of a workgroup
 constexpr int BLK = 64;                // rows of a moving tile
 constexpr int TILE = BLK * D;          // halves
 constexpr int PAIR = 2 * TILE;

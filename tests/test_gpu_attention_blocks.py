@@ -59,6 +59,36 @@ def test_blocks(L, B, s, nh):
                     assert off(g, w) < 2.0 ** -10, (name, b, n, off(g, w))
 
 
+@pytest.mark.parametrize("B,nh,rope", [(1, 1, True), (3, 7, True), (8, 4, False), (130, 32, True)])
+def test_sequence_of_one_block_against_longer_ones(L, B, nh, rope):
+    """Sequences of one block have a backward kernel of their own.  In sequences of two, dq of the first block depends on that block alone
+    and dk, dv of the second on the second alone (given o and lse), so the kernels for longer sequences give the same bits there."""
+    s, H = 64, nh * 128
+    gen = torch.Generator(device=DEV).manual_seed(B + nh)
+    normal = lambda *shape: torch.randn(shape, generator=gen, device=DEV, dtype=torch.float16)
+    qkv, do = normal(B, 2 * s, 3 * H), normal(B, 2 * s, H)
+    angle = torch.rand(2 * s, 64, generator=gen, device=DEV)
+    table = (angle.cos(), angle.sin()) if rope else (None, None)
+
+    def backward(rows):
+        part = lambda x: x[:, rows].contiguous()
+        n = part(qkv).shape[1]
+        guard = torch.full((B * n + 256, 3 * H), 9.0, dtype=torch.float16, device=DEV)      # rows in front of and behind the gradient
+        delta, grad = torch.full((B * n, nh), 9.0, device=DEV), guard[128:128 + B * n]
+        L.lomo_attention_backward(part(qkv).view(B * n, -1), part(o).view(B * n, -1), part(do).view(B * n, -1), part(lse).view(-1),
+                                  *(None if x is None else x[rows].contiguous() for x in table), delta.view(-1), grad, B, n, nh)
+        assert bool((guard[:128] == 9).all()) and bool((guard[128 + B * n:] == 9).all())
+        return delta.view(B, n, nh), grad.view(B, n, 3, H)
+
+    o, lse = torch.empty(B, 2 * s, H, dtype=torch.float16, device=DEV), torch.empty(B, 2 * s, nh, device=DEV)
+    L.lomo_attention_forward(qkv.view(2 * B * s, -1), o.view(2 * B * s, -1), lse.view(2 * B * s, -1), B, 2 * s, nh)
+    delta, grad = backward(slice(0, 2 * s))
+    for rows, of_block in ((slice(0, s), slice(0, 1)), (slice(s, 2 * s), slice(1, 3))):
+        one_delta, one = backward(rows)
+        assert torch.equal(one_delta, delta[:, rows])
+        assert torch.equal(one[:, :, of_block].view(torch.int16), grad[:, rows, of_block].view(torch.int16))
+
+
 def test_rows_beyond_32_bit_offsets(L):
     """More heads than a wave's 32-bit offsets reach over four rows (48 GiB of q, k and v, most of it never looked at)."""
     s, nh = 64, (1 << 20) + 8
