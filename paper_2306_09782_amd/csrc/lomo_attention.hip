@@ -217,10 +217,12 @@ __global__ __launch_bounds__(256, 2) void attention_backward_dq_kernel(attn::Arg
     int head, within;
     locate_block(nb, head, within);
     const int n = head % a.nh, b = head / a.nh;
-    const int q0 = (nb - 1 - within) * ROWS<SPLIT>;          // heaviest blocks first
+    // heaviest blocks first, counted from the sequence's end: one that is not full has the lightest rows (of 192 tokens four pairs of tiles are
+    // walked instead of five; 32 x 192 tokens, 32 heads, with the dk / dv kernel 159.5 -> 156 us, 42 x 192, 8 heads 66.6 -> 60.4)
+    const int q0 = a.s - (within + 1) * ROWS<SPLIT>;
     const int qw = q0 + 32 * (SPLIT == 2 ? wave & 1 : wave);      // this wave's queries
-    const bool active = qw < a.s;                            // s is a multiple of 64
-    const int last = ((q0 + ROWS<SPLIT> < a.s ? q0 + ROWS<SPLIT> : a.s) - 1) / BLK;      // key blocks of the workgroup
+    const bool active = qw >= 0;                             // s is a multiple of 64
+    const int last = (q0 + ROWS<SPLIT> - 1) / BLK;      // key blocks of the workgroup
     const int64_t ld3 = 3 * (int64_t)a.H, ldh = a.H;
     const int64_t t0 = (int64_t)b * a.s;
     const uint16_t* gq = a.qkv + (int64_t)n * D;
